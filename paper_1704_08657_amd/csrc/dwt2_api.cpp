@@ -263,8 +263,6 @@ int validate(const void* src, void* dst, int32_t planes, int64_t sps, int64_t dp
     return DWT2_OK;
 }
 
-bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
-
 int report(hipError_t e) {
     if (e == hipSuccess) return DWT2_OK;
     g_last_hip_error = hipGetErrorString(e);
@@ -316,10 +314,6 @@ int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, d
     return DWT2_OK;
 }
 
-// Vector access needs every plane's row bases aligned: the plane strides
-// (unused when there is one plane) as well as the pitches.
-bool stride_ok(int32_t planes, int64_t stride, int v) { return planes == 1 || stride % v == 0; }
-
 // Forward: level l reads the LL of level l-1 (src for l = 0) and writes its
 // details into dst at the level's region origin (dst itself: every level's
 // region starts at (0, 0)), its LL into the workspace or, for the last level,
@@ -370,19 +364,6 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
         lp.out_ll_pitch = last ? dp : ws_pitch((lp.w + 1) / 2);
         lp.out_ll_ps = last ? dps : buf_ps[l % 2];
         plan_grid(config_of(flags, wavelet), &lp);
-        const int32_t nEc = (lp.w + 1) / 2;
-        const int sv = dwt2::subband_vec(dwt2::kConfigs[config_of(flags, wavelet)]);
-        lp.vec = aligned(lp.in, 4 * es) && lp.in_pitch % 4 == 0 && stride_ok(planes, lp.in_ps, 4) &&
-                 aligned(lp.out, sv * es) && lp.out_pitch % sv == 0 && stride_ok(planes, lp.out_ps, sv) &&
-                 nEc % sv == 0 && aligned(lp.out_ll, sv * es) && lp.out_ll_pitch % sv == 0 &&
-                 stride_ok(planes, lp.out_ll_ps, sv);
-        // sample pairs: every row base (and plane stride) 8-byte aligned
-        lp.vec8 = aligned(lp.in, 2 * es) && lp.in_pitch % 2 == 0 && stride_ok(planes, lp.in_ps, 2) &&
-                  aligned(lp.out, 2 * es) && lp.out_pitch % 2 == 0 && stride_ok(planes, lp.out_ps, 2) &&
-                  aligned(lp.out_ll, 2 * es) && lp.out_ll_pitch % 2 == 0 && stride_ok(planes, lp.out_ll_ps, 2);
-        // image rows 16-byte aligned
-        const int v16 = (int)(16 / es);
-        lp.vec16 = aligned(lp.in, 16) && lp.in_pitch % v16 == 0 && stride_ok(planes, lp.in_ps, v16);
         const int rc = launch_planes(dwt2::kForward, wavelet, dtype, flags, lp, planes, es, s);
         if (rc) return rc;
         in = lp.out_ll;
@@ -422,19 +403,6 @@ int run_backward(dwt2::Direction dir, const void* src, void* dst, int32_t planes
         lp.out_pitch = l == 0 ? dp : ws_pitch(lp.w);
         lp.out_ps = l == 0 ? dps : buf_ps[(l - 1) % 2];
         plan_grid(config_of(flags, wavelet), &lp);
-        const int32_t nEc = (lp.w + 1) / 2;
-        const int sv = dwt2::subband_vec(dwt2::kConfigs[config_of(flags, wavelet)]);
-        lp.vec = aligned(lp.in, sv * es) && lp.in_pitch % sv == 0 && stride_ok(planes, lp.in_ps, sv) &&
-                 nEc % sv == 0 && aligned(lp.in_ll, sv * es) && lp.in_ll_pitch % sv == 0 &&
-                 stride_ok(planes, lp.in_ll_ps, sv) && aligned(lp.out, 4 * es) && lp.out_pitch % 4 == 0 &&
-                 stride_ok(planes, lp.out_ps, 4);
-        // sample pairs: every row base (and plane stride) 8-byte aligned
-        lp.vec8 = aligned(lp.in, 2 * es) && lp.in_pitch % 2 == 0 && stride_ok(planes, lp.in_ps, 2) &&
-                  aligned(lp.in_ll, 2 * es) && lp.in_ll_pitch % 2 == 0 && stride_ok(planes, lp.in_ll_ps, 2) &&
-                  aligned(lp.out, 2 * es) && lp.out_pitch % 2 == 0 && stride_ok(planes, lp.out_ps, 2);
-        // image rows 16-byte aligned
-        const int v16 = (int)(16 / es);
-        lp.vec16 = aligned(lp.out, 16) && lp.out_pitch % v16 == 0 && stride_ok(planes, lp.out_ps, v16);
         const int rc = launch_planes(dir, wavelet, dtype, flags, lp, planes, es, s);
         if (rc) return rc;
         ll = lp.out;

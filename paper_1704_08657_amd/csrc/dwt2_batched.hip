@@ -206,8 +206,6 @@ persist_plan_kernel(ImageSet S, int count, int levels, int core_cols, int core_r
     for (uint32_t j = tid; j < base; j += kPlanThreads) done[j] = 0;
 }
 
-__device__ __forceinline__ bool is_aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
-
 // ---- one launch per level --------------------------------------------------
 // Planner: per level an exclusive scan of the images' tile counts (one launch
 // of that level covers the tiles of all images) and each image's two LL
@@ -302,23 +300,9 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int l, unsig
         P.out_ll = l % 2 == 0 ? (void*)bufA : (void*)bufB;
         P.out_ll_pitch = ll_pitch((wl + 1) / 2);
     }
-    P.vec = is_aligned(P.in, 4 * es) && P.in_pitch % 4 == 0 && is_aligned(P.out, BPL * es) &&
-            P.out_pitch % BPL == 0 && ((wl + 1) / 2) % BPL == 0 && is_aligned(P.out_ll, BPL * es) &&
-            P.out_ll_pitch % BPL == 0;
-    P.vec8 = is_aligned(P.in, 2 * es) && P.in_pitch % 2 == 0 && is_aligned(P.out, 2 * es) &&
-             P.out_pitch % 2 == 0 && is_aligned(P.out_ll, 2 * es) && P.out_ll_pitch % 2 == 0;
-    P.vec16 = is_aligned(P.in, 16) && P.in_pitch % (int64_t)(16 / es) == 0;
     const int ty = tt / P.tiles_x;
     const int tx = tt - ty * P.tiles_x;
-    // images whose rows are only 8-byte aligned: semi-vector interior tiles
-    // (fused and split steps, as the level kernel)
-    if constexpr (SCH == kSchemeFused || SCH == kSchemeSplit) {
-        if (!P.vec && P.vec8) {
-            tile_body<kForward, kCdf97, T, SCH, NW, K, BPL, true>(P, tx, ty, lds, lane, wv);
-            return;
-        }
-    }
-    tile_body<kForward, kCdf97, T, SCH, NW, K, BPL, false>(P, tx, ty, lds, lane, wv);
+    tile_body<kForward, kCdf97, T, SCH, NW, K, BPL>(P, tx, ty, lds, lane, wv);
 }
 
 // ---- one persistent launch -------------------------------------------------
@@ -445,26 +429,11 @@ persist_fwd_kernel(ImageSet S, int count, int levels, BatchLayout BL, uint64_t w
             P.out_ll = bands + ll_band_offset(im.height, im.width, l, es);
             P.out_ll_pitch = ll_pitch((wl + 1) / 2);
         }
-        P.vec = is_aligned(P.in, 4 * es) && P.in_pitch % 4 == 0 && is_aligned(P.out, BPL * es) &&
-                P.out_pitch % BPL == 0 && ((wl + 1) / 2) % BPL == 0 && is_aligned(P.out_ll, BPL * es) &&
-                P.out_ll_pitch % BPL == 0;
-        P.vec8 = is_aligned(P.in, 2 * es) && P.in_pitch % 2 == 0 && is_aligned(P.out, 2 * es) &&
-                 P.out_pitch % 2 == 0 && is_aligned(P.out_ll, 2 * es) && P.out_ll_pitch % 2 == 0;
-        P.vec16 = is_aligned(P.in, 16) && P.in_pitch % (int64_t)(16 / es) == 0;
-        // images whose rows are only 8-byte aligned: semi-vector interior
-        // tiles (fused and split steps, as the level kernel)
-        bool semi = false;
-        if constexpr (SCH == kSchemeFused || SCH == kSchemeSplit) semi = !P.vec && P.vec8;
         // a level that a later one reads stores its LL band with agent-scope
         // stores (written through the L2, see coherent_store)
         const bool read_later = l + 1 < levels;
-        if (semi) {
-            if (read_later) tile_body<kForward, kCdf97, T, SCH, NW, K, BPL, true, false, true>(P, tcol, trow, lds, lane, wv);
-            else tile_body<kForward, kCdf97, T, SCH, NW, K, BPL, true>(P, tcol, trow, lds, lane, wv);
-        } else {
-            if (read_later) tile_body<kForward, kCdf97, T, SCH, NW, K, BPL, false, false, true>(P, tcol, trow, lds, lane, wv);
-            else tile_body<kForward, kCdf97, T, SCH, NW, K, BPL, false>(P, tcol, trow, lds, lane, wv);
-        }
+        if (read_later) tile_body<kForward, kCdf97, T, SCH, NW, K, BPL, false, true>(P, tcol, trow, lds, lane, wv);
+        else tile_body<kForward, kCdf97, T, SCH, NW, K, BPL>(P, tcol, trow, lds, lane, wv);
 
         // publish the tile: every wave waits until its stores have completed
         // (the LL band's agent-scope stores are then where every XCD reads

@@ -68,8 +68,6 @@ constexpr int kRemapRows = 2;
 // output block rows / columns of one tile (kAlgoTile, kAlgoLds)
 constexpr int core_rows(KernelConfig c) { return c.algo == kAlgoLds ? c.cy : c.waves * c.rows - 2 * kHalo; }
 constexpr int core_cols(KernelConfig c) { return c.algo == kAlgoLds ? c.cx : kLanes * c.bpl; }
-// samples per vector access of a subband row (alignment the `vec` path needs)
-constexpr int subband_vec(KernelConfig c) { return c.algo == kAlgoTile ? c.bpl : 2; }
 
 // One level of a transform.  Forward: `in` is the h x w image of this level,
 // `out` the origin of this level's region of the Mallat pyramid (details are
@@ -86,7 +84,6 @@ struct LevelParams {
     int64_t out_ll_pitch;
     int32_t h, w;
     int32_t tiles_x, tiles_y;
-    int32_t vec;       // 1: every row base is aligned for vector access
     int32_t seg_rows;  // kAlgoStream: block rows per segment
     // Plane batch: the launch covers `planes` planes; plane p's buffers
     // start p * (stride) elements after those of plane 0.  Set by the
@@ -94,14 +91,6 @@ struct LevelParams {
     // the streaming kernel takes one grid row per plane).
     int64_t in_ps, in_ll_ps, out_ps, out_ll_ps;
     int32_t planes;
-    // Without `vec`: every row base (and plane stride) is 8-byte aligned
-    // (even pitches), so interior tiles can use pairs of samples (the
-    // semi-vector interior path).
-    int32_t vec8;
-    // With `vec`: the image rows (forward input, inverse / adjoint output)
-    // start 16-byte aligned, so 16-bit samples of 4 blocks per lane move as
-    // one 16-byte access per row.
-    int32_t vec16;
     // CDF 9/7, a level whose output the call's next level reads (forward:
     // the LL band of every level but the last; inverse / adjoint: the image
     // of every level but the finest): interior tiles store it with ordinary

@@ -353,18 +353,6 @@ __device__ __forceinline__ void run_steps(Planes<RH, RW>& L, int tid) {
 // ---------------------------------------------------------------------------
 // global memory
 // ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void load_pair(const T* p, bool pair, float& a, float& b) {
-    if (pair) {
-        const Pack2<T> q = *reinterpret_cast<const Pack2<T>*>(p);
-        a = St<T>::load(q.v[0]);
-        b = St<T>::load(q.v[1]);
-    } else {
-        a = St<T>::load(p[0]);
-        b = St<T>::load(p[1]);
-    }
-}
-
 // Forward load: pixel rows 2 (rb0 - H) ... of the image into the planes of
 // buffer 0 (block (n, m) of the tile = image block (rb0 - H + n, cb0 - H + m));
 // outside the image the whole-point symmetric extension.
@@ -373,13 +361,15 @@ __device__ __forceinline__ void load_fwd(Planes<RH, RW>& L, const LevelParams& P
                                          int tid) {
     const T* in = static_cast<const T*>(P.in);
     const int r0 = 2 * (rb0 - H), c0 = 2 * (cb0 - H);
-    const bool pair = P.vec8 != 0;
     for (int idx = tid; idx < 2 * RH * RW; idx += kThreads) {
         const int pr = idx / RW, bc = idx - pr * RW;
         const int R = r0 + pr, C = c0 + 2 * bc;
         float a, b;
         if (inside) {
-            load_pair<T>(in + (int64_t)R * P.in_pitch + C, pair, a, b);
+            float v[2];
+            load_vec<T, 2>(in + (int64_t)R * P.in_pitch + C, v);
+            a = v[0];
+            b = v[1];
         } else {
             const T* row = in + (int64_t)reflect(R, P.h) * P.in_pitch;
             a = St<T>::load(row[reflect(C, P.w)]);
@@ -452,7 +442,6 @@ template <typename T, int H, int CX, int CY, int RH, int RW>
 __device__ __forceinline__ void store_inv(const float (&q)[4][RH][RW], const LevelParams& P, int rb0, int cb0,
                                           int tid) {
     T* img = static_cast<T*>(P.out);
-    const bool pair = P.vec8 != 0;
     for (int idx = tid; idx < 2 * CY * CX; idx += kThreads) {
         const int pr = idx / CX, m = idx - pr * CX;
         const int R = 2 * rb0 + pr, C = 2 * (cb0 + m);
@@ -461,8 +450,8 @@ __device__ __forceinline__ void store_inv(const float (&q)[4][RH][RW], const Lev
         const float a = q[k][H + (pr >> 1)][H + m], b = q[k + 1][H + (pr >> 1)][H + m];
         T* p = img + (int64_t)R * P.out_pitch + C;
         if (C + 1 < P.w) {
-            if (pair) nt_store2(p, St<T>::store(a), St<T>::store(b));
-            else { nt_store1(p, St<T>::store(a)); nt_store1(p + 1, St<T>::store(b)); }
+            const float v[2] = {a, b};
+            store_vec<T, 2>(p, v);
         } else {
             nt_store1(p, St<T>::store(a));
         }

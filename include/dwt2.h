@@ -91,8 +91,10 @@ typedef enum {
                                even += (9 (o[m-1] + o[m]) - (o[m-2] + o[m+1])) / 32,
                                LL * 2, HH * 1/2 (zeta = sqrt(2)); borders
                                reflect the pixel position of each sample.
-                               Forward / inverse on DWT2_ALGO_LDS kernel
-                               configurations only (the default for it).   */
+                               Forward / inverse: by default on a register
+                               tile kernel of its own; with a scheme flag or
+                               a named configuration on DWT2_ALGO_LDS kernel
+                               configurations (bit-identical results).     */
 } dwt2_wavelet;
 
 typedef enum {

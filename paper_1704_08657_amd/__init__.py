@@ -234,7 +234,8 @@ def config_supports(index: int, direction: str, wavelet: str, scheme: str = "fus
     """Whether kernel configuration `index` runs this case (the library
     rejects the others with DWT2_E_FLAGS): the LDS-plane configurations run
     the float wavelets forward and inverse with the fused, separable and
-    polyconvolution schemes, and are the only ones that run DD 13/7 and the
+    polyconvolution schemes, and are the only configurations that run DD 13/7
+    (which without one has a register tile kernel of its own) and the
     polyconvolution; the streaming ones run the fused and split schemes."""
     algo = dwt2_kernel_config(index)[1]
     if algo == DWT2_ALGO_LDS:
@@ -321,7 +322,7 @@ def fwd(x, wavelet: str = "cdf97", levels: int = 1, split: bool = False, out=Non
     `polyconv` (one polyconvolution step N_{P,U} per lifting pair, CDF 9/7,
     LDS-plane kernel); all compute the same values up to FP32 rounding.
     Wavelets: "cdf97", "cdf53" (reversible integer), "cdf53f" (real CDF
-    5/3), "dd137" (Deslauriers-Dubuc 13/7, LDS-plane kernel)."""
+    5/3), "dd137" (Deslauriers-Dubuc 13/7)."""
     return _transform(lib().dwt2_fwd_planes, "dwt2_fwd", x, wavelet, levels, split, out, config, separable,
                       factored, polyconv, persistent, workspace, fused)
 

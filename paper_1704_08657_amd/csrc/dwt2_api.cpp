@@ -306,7 +306,11 @@ int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, d
             q.out = lp.out ? (char*)lp.out + (size_t)p0 * (size_t)lp.out_ps * es : nullptr;
             q.out_ll = lp.out_ll ? (char*)lp.out_ll + (size_t)p0 * (size_t)lp.out_ll_ps * es : nullptr;
         }
-        const int rc = report(dwt2::launch_level(dir, to_wav(wavelet), to_dtype(dtype),
+        // DD 13/7 without a named configuration or scheme: the four-tap
+        // register tile kernel
+        const bool taps4 = wavelet == DWT2_DD137 && !(flags & ~DWT2_FLAG_FUSED);
+        const int rc = taps4 ? report(dwt2::launch_taps4(dir, to_dtype(dtype), q, n, s))
+                             : report(dwt2::launch_level(dir, to_wav(wavelet), to_dtype(dtype),
                                                  scheme_of(flags, dtype, wavelet, dir == dwt2::kAdjoint),
                                                  config_of(flags, wavelet), q, n, s));
         if (rc) return rc;

@@ -62,6 +62,9 @@ constexpr KernelConfig kConfigs[] = {
 constexpr int kNumConfigs = 10;
 constexpr int kDefaultConfig = 0;
 constexpr int kDefaultLdsConfig = 8;
+// The four-tap register tile kernel (DD 13/7): a halo of kHalo4 block rows
+// above and below a tile.
+constexpr int kHalo4 = 3;
 // Tile kernels deal work over the 8 XCDs in chunks of kRemapRows tile rows;
 // the grid is a multiple of 8 chunks.
 constexpr int kRemapRows = 2;
@@ -113,5 +116,8 @@ hipError_t launch_level(Direction dir, Wavelet wav, Dtype dt, Scheme scheme, int
 // of the float wavelets, fused / separable / polyconvolution schemes.
 hipError_t launch_lds(Direction dir, Wavelet wav, Dtype dt, Scheme scheme, int cfg, const LevelParams& p,
                       int planes, hipStream_t stream);
+// DD 13/7 with the fused steps, forward and inverse, on the four-tap register
+// tile kernel; sets the tile grid itself.  Bit-identical to the LDS-plane kernel.
+hipError_t launch_taps4(Direction dir, Dtype dt, const LevelParams& p, int planes, hipStream_t stream);
 
 }  // namespace dwt2

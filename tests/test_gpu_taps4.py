@@ -1,0 +1,55 @@
+"""DD 13/7 on the four-tap register tile kernel (calls that name no kernel
+configuration and no scheme): bit for bit the LDS-plane kernel's results, whose
+parity with the oracle tests/test_gpu_lds.py holds, at the ends of both
+kernels' tiles, for every storage type and direction; the smallest images
+against the oracle itself."""
+import numpy as np
+import pytest
+
+import workloads
+from oracle import lifting
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_1704_08657_amd as d  # noqa: E402
+
+TOL = 1e-5                     # FP32, of the largest coefficient (as the LDS-plane kernel's tests)
+LDS_CONFIG = 8
+
+
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda", 0)
+
+
+@pytest.mark.parametrize("tdt", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("h,w,levels", [(20, 240, 1), (21, 241, 1), (27, 247, 2), (58, 486, 1), (111, 495, 2),
+                                        (104, 480, 3), (200, 1000, 5), (2900, 2050, 2), (1, 1, 0)])
+def test_equals_lds_plane_kernel(tdt, h, w, levels):
+    # tiles are 240 pixels wide and 20 high, or 28 beyond 1024 tiles (2900 x 2050)
+    if levels == 0:            # one image with interior tiles, ragged ends, and every plane of a stack
+        n, h, w, levels = 3, 333, 1211, 4
+    else:
+        n = 1
+    x = torch.from_numpy(workloads.planes(n, h, w, seed=91)).to(dev()).to(tdt)
+    for direction in (d.fwd, d.inv):
+        print("taps4", tdt, (n, h, w), levels, direction.__name__, flush=True)
+        assert torch.equal(direction(x, "dd137", levels), direction(x, "dd137", levels, config=LDS_CONFIG))
+        assert torch.equal(direction(x, "dd137", levels, fused=True), direction(x, "dd137", levels))
+
+
+@pytest.mark.parametrize("h", [2, 3, 4, 6, 7, 8, 9])
+def test_small_images(h):
+    for w in (2, 3, 5, 7, 8, 11, 241):
+        x = workloads.uniform(h, w, seed=h * 300 + w)
+        lv = lifting.max_levels(h, w)
+        print("taps4 small", (h, w), lv, flush=True)
+        ref = lifting.fwd(x, "dd137", lv)
+        y = d.fwd(torch.from_numpy(x).to(dev()), "dd137", lv).cpu().numpy()
+        assert np.abs(y - ref).max() <= TOL * np.abs(ref).max(), w
+        c = ref.astype(np.float32)
+        want = lifting.inv(c, "dd137", lv)
+        r = d.inv(torch.from_numpy(c).to(dev()), "dd137", lv).cpu().numpy()
+        assert np.abs(r - want).max() <= TOL * np.abs(want).max(), w

@@ -211,7 +211,9 @@ int dwt2_workspace_bytes(int32_t height, int32_t width, int levels,
 /* Forward transform (Section "Proposed Schemes", non-separable lifting):
  * src = image (height x width, src_pitch), dst = Mallat pyramid
  * (height x width, dst_pitch).  Multi-level: levels >= 1, one launch per
- * level (DWT2_FLAG_PERSISTENT: one persistent launch for all levels). */
+ * level, or (calls with flags 0, where it is the faster way) per two levels,
+ * with the same results (DWT2_FLAG_PERSISTENT: one persistent launch for all
+ * levels). */
 int dwt2_fwd(const void* src, void* dst, int32_t height, int32_t width,
              int64_t src_pitch, int64_t dst_pitch, dwt2_dtype dtype,
              dwt2_wavelet wavelet, int levels, dwt2_boundary boundary,
@@ -248,8 +250,8 @@ int dwt2_adj(const void* src, void* dst, int32_t height, int32_t width,
 /* Plane batches (channels, batch items): `planes` images of the same shape
  * and pitch whose origins lie `src_plane_stride` / `dst_plane_stride`
  * elements apart, transformed as dwt2_fwd / dwt2_inv / dwt2_adj would
- * transform each one (bit-identical results), with one launch per level for
- * all planes.  planes >= 1 (else DWT2_E_COUNT); with planes > 1 each stride
+ * transform each one (bit-identical results), each launch covering all
+ * planes.  planes >= 1 (else DWT2_E_COUNT); with planes > 1 each stride
  * must cover a whole plane, (height - 1) * pitch + width elements (else
  * DWT2_E_PITCH); no plane of src may overlap any of dst or the workspace.
  * The workspace holds the intermediate LL bands of every plane:

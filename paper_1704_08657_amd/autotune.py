@@ -2,9 +2,11 @@
 
 Times every kernel configuration that the library offers for a case
 (direction, wavelet, storage type, image size class, level count) on the
-current GPU and records the fastest in a JSON cache.  The binding consults
-the cache when a call does not name a configuration; all configurations
-compute bit-identical results, so the choice affects speed only.
+current GPU, beside the library's own choice (which picks a kernel per level
+and may run two levels in one launch), and records a configuration that beats
+it in a JSON cache.  The binding consults the cache when a call does not name
+a configuration; all configurations compute bit-identical results, so the
+choice affects speed only.
 
     python -m paper_1704_08657_amd.autotune [--out FILE] [--quick]
 
@@ -74,23 +76,32 @@ def lookup(direction: str, wavelet: str, dtype: str, h: int, w: int, levels: int
 
 def tune_case(direction: str, wavelet: str, dtype: str, h: int, w: int, levels: int, run, configs=None,
               steps: int = 8, warm: int = 3):
-    """Time `run(config, i)` for every kernel configuration (or `configs`) on
-    the current GPU and stream, record the fastest (median of `steps`
-    launches) in the in-memory cache under this case's key, so calls that
+    """Time `run(config, i)` for every kernel configuration (or `configs`) and
+    for the library's own choice (None) on the current GPU and stream, record
+    the fastest in the in-memory cache under this case's key, so calls that
     name no configuration use it, and return (best, {config: ms})."""
     import torch
     import paper_1704_08657_amd as d
     if configs is None:
         configs = [c for c in range(d.DWT2_NUM_KERNEL_CONFIGS) if d.config_supports(c, direction, wavelet)]
+    # None must mean the library's choice here, not an earlier entry
+    _record(key(arch_name(), direction, wavelet, dtype, h, w, levels), None)
+    configs = [None, *configs]
     times = {c: _time(torch, lambda i, c=c: run(c, i), steps=steps, warm=warm) for c in configs}
     best = min(times, key=times.get)
-    cache = load_cache()
+    _record(key(arch_name(), direction, wavelet, dtype, h, w, levels), best)
+    return best, times
+
+
+def _record(k: str, config) -> None:
+    """Set (or with None drop) an entry of the in-memory cache."""
     global _cache
-    _cache = dict(cache)
-    _cache[key(arch_name(), direction, wavelet, dtype, h, w, levels)] = best
+    _cache = dict(load_cache())
+    _cache.pop(k, None)
+    if config is not None:
+        _cache[k] = config
     from . import _tuned               # the binding's memo of cache lookups
     _tuned.clear()
-    return best, times
 
 
 def _time(torch, fn, steps=20, warm=4):
@@ -144,7 +155,9 @@ def tune(sizes=(256, 1024, 4096, 8192), levels=(1, 5), quick=False, out=CACHE_PA
         fn = {"fwd": lambda x, y, c: d.fwd(x, wav, lv, out=y, config=c),
               "inv": lambda x, y, c: d.inv(x, wav, lv, out=y, config=c),
               "adj": lambda x, y, c: d.adj(x, lv, out=y, config=c)}[direction]
-        best, best_ms = None, float("inf")
+        k = key(arch, direction, wav, dt, n, n, lv)
+        _record(k, None)
+        best, best_ms = None, _time(torch, lambda i: fn(xs[i % nb], ys[i % nb], None), steps=8 if quick else 30)
         for c in range(nconf):
             # the LDS-plane configurations run what the register tile kernel
             # does not (and are never faster where both run)
@@ -153,8 +166,9 @@ def tune(sizes=(256, 1024, 4096, 8192), levels=(1, 5), quick=False, out=CACHE_PA
             ms = _time(torch, lambda i: fn(xs[i % nb], ys[i % nb], c), steps=8 if quick else 30)
             if ms < best_ms:
                 best, best_ms = c, ms
-        k = key(arch, direction, wav, dt, n, n, lv)
-        result[k] = best
+        result.pop(k, None)
+        if best is not None:           # the library's own choice needs no entry
+            result[k] = best
         log(f"{k}: config {best} ({best_ms * 1e3:.1f} us)")
     # batched: between the configurations the batched kernels support
     for dt in [t for t in ("f32", "bf16") if t in dtypes]:

@@ -65,9 +65,8 @@ void plan_levels(int32_t h, int32_t w, int levels, Plan* p) {
     }
 }
 
-// Two ping-pong buffers per plane for intermediate LL bands: buffer A holds
-// the LL of levels 1, 3, 5, ... (largest: level 1), buffer B of levels 2,
-// 4, ...  All planes' A buffers come first (plane stride a), then all B
+// Two ping-pong buffers per plane for intermediate LL bands: buffer A is large
+// enough for any (level 1's), buffer B for any but level 1's.  All planes' A buffers come first (plane stride a), then all B
 // buffers (plane stride b); a and b are multiples of kWsAlign bytes.
 struct WsLayout {
     size_t a, b;        // bytes of one plane's buffer A / B
@@ -293,9 +292,21 @@ void plan_grid(int cfg, dwt2::LevelParams* lp) {
     }
 }
 
+// Kernel configuration of one level: the one the call names, else the taller
+// tile (4 waves x 6 rows: 8 halo rows of 48 image rows instead of 8 of 32) for
+// levels of 2^25 samples and more, where the memory system is the limit
+// (8192^2 FP32 forward 94.8 us, 4 x 4: 95.6, inverse 96.1 / 97.9; 3 x 8192^2
+// BF16 148 / 158), and the shorter one below, where a tile's own time counts
+// more (2048^2 9.2 / 8.5; 1024^2 6.9 / 5.9).
+int level_config(unsigned flags, int wavelet, int32_t planes, int32_t h, int32_t w) {
+    const int cfg = config_of(flags, wavelet);
+    if (cfg != dwt2::kDefaultConfig || (flags & DWT2_FLAG_KERNEL_MASK)) return cfg;
+    return (int64_t)planes * h * w >= (1 << 25) ? dwt2::kLargeConfig : cfg;
+}
+
 // Launch one level for every plane, in grid chunks of at most
 // kMaxGridPlanes planes.
-int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, dwt2::LevelParams lp,
+int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, int cfg, dwt2::LevelParams lp,
                   int32_t planes, size_t es, hipStream_t s) {
     for (int32_t p0 = 0; p0 < planes; p0 += dwt2::kMaxGridPlanes) {
         const int32_t n = planes - p0 < dwt2::kMaxGridPlanes ? planes - p0 : dwt2::kMaxGridPlanes;
@@ -312,7 +323,7 @@ int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, d
         const int rc = taps4 ? report(dwt2::launch_taps4(dir, to_dtype(dtype), q, n, s))
                              : report(dwt2::launch_level(dir, to_wav(wavelet), to_dtype(dtype),
                                                  scheme_of(flags, dtype, wavelet, dir == dwt2::kAdjoint),
-                                                 config_of(flags, wavelet), q, n, s));
+                                                 cfg, q, n, s));
         if (rc) return rc;
     }
     return DWT2_OK;
@@ -329,6 +340,15 @@ int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, d
 // LL band the nontemporal path leaves in the Infinity Cache anyway).
 bool cached_output(int32_t planes, int32_t h, int32_t w, size_t es) {
     return (uint64_t)planes * (uint64_t)h * (uint64_t)w * es >= ((uint64_t)32 << 20);
+}
+
+// Levels the launch that starts at level l takes: two of a call that names no
+// scheme and no kernel configuration, where that is the faster way.
+int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int wavelet, unsigned flags,
+                     int32_t planes) {
+    const bool two = flags == 0 && wavelet != DWT2_DD137 && l + 1 < p.levels &&
+                     dwt2::pair_pays(dir, to_dtype(dtype), p.h[l], p.w[l], planes);
+    return two ? 2 : 1;
 }
 
 int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t dps, int32_t h, int32_t w,
@@ -352,7 +372,37 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
     const int64_t buf_ps[2] = {(int64_t)(L.a / es), (int64_t)(L.b / es)};
     const void* in = src;
     int64_t in_pitch = sp, in_ps = sps;
+    int cur = 1;                              // the buffer that holds `in` (none before the first level)
     for (int l = 0; l < levels; ++l) {
+        const int n = levels_in_launch(dwt2::kForward, p, l, dtype, wavelet, flags, planes);
+        const bool last = l + n == levels;
+        // the LL band that leaves this launch: dst, or the buffer the input is
+        // not in (A, which holds any band, before B, which holds all but the first)
+        cur ^= 1;
+        void* const out_ll = last ? dst : (void*)bufs[cur];
+        const int64_t out_ll_pitch = last ? dp : ws_pitch((p.w[l + n - 1] + 1) / 2);
+        const int64_t out_ll_ps = last ? dps : buf_ps[cur];
+        if (n == 2) {
+            dwt2::PairParams pp{};
+            pp.in = in;
+            pp.in_pitch = in_pitch;
+            pp.in_ps = in_ps;
+            pp.out = dst;
+            pp.out_pitch = dp;
+            pp.out_ps = dps;
+            pp.ll = out_ll;
+            pp.ll_pitch = out_ll_pitch;
+            pp.ll_ps = out_ll_ps;
+            pp.h = p.h[l];
+            pp.w = p.w[l];
+            const int rc = report(dwt2::launch_pair(dwt2::kForward, to_wav(wavelet), to_dtype(dtype), pp, planes, s));
+            if (rc) return rc;
+            in = out_ll;
+            in_pitch = out_ll_pitch;
+            in_ps = out_ll_ps;
+            ++l;
+            continue;
+        }
         dwt2::LevelParams lp{};
         lp.h = p.h[l];
         lp.w = p.w[l];
@@ -362,13 +412,13 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
         lp.out = dst;
         lp.out_pitch = dp;
         lp.out_ps = dps;
-        const bool last = l + 1 == levels;
         lp.ll_cached = !last && cached_output(planes, (lp.h + 1) / 2, (lp.w + 1) / 2, es) ? 1 : 0;
-        lp.out_ll = last ? dst : (void*)bufs[l % 2];
-        lp.out_ll_pitch = last ? dp : ws_pitch((lp.w + 1) / 2);
-        lp.out_ll_ps = last ? dps : buf_ps[l % 2];
-        plan_grid(config_of(flags, wavelet), &lp);
-        const int rc = launch_planes(dwt2::kForward, wavelet, dtype, flags, lp, planes, es, s);
+        lp.out_ll = out_ll;
+        lp.out_ll_pitch = out_ll_pitch;
+        lp.out_ll_ps = out_ll_ps;
+        const int cfg = level_config(flags, wavelet, planes, lp.h, lp.w);
+        plan_grid(cfg, &lp);
+        const int rc = launch_planes(dwt2::kForward, wavelet, dtype, flags, cfg, lp, planes, es, s);
         if (rc) return rc;
         in = lp.out_ll;
         in_pitch = lp.out_ll_pitch;
@@ -391,7 +441,37 @@ int run_backward(dwt2::Direction dir, const void* src, void* dst, int32_t planes
     const int64_t buf_ps[2] = {(int64_t)(L.a / es), (int64_t)(L.b / es)};
     const void* ll = src;
     int64_t ll_pitch = sp, ll_ps = sps;
-    for (int l = levels - 1; l >= 0; --l) {
+    // the launches, finest level first; their images, which the next launch
+    // reads as its LL band, alternate between the buffers so that the largest
+    // (the finest launch's input) lies in A
+    int first[32], count = 0;
+    for (int l = 0; l < levels; l += levels_in_launch(dir, p, l, dtype, wavelet, flags, planes)) first[count++] = l;
+    for (int j = count - 1; j >= 0; --j) {
+        const int l = first[j], n = (j + 1 < count ? first[j + 1] : levels) - l;
+        const int buf = (j - 1) & 1;
+        void* const out = l == 0 ? dst : (void*)bufs[buf];
+        const int64_t out_pitch = l == 0 ? dp : ws_pitch(p.w[l]);
+        const int64_t out_ps = l == 0 ? dps : buf_ps[buf];
+        if (n == 2) {
+            dwt2::PairParams pp{};
+            pp.in = src;
+            pp.in_pitch = sp;
+            pp.in_ps = sps;
+            pp.out = out;
+            pp.out_pitch = out_pitch;
+            pp.out_ps = out_ps;
+            pp.ll = const_cast<void*>(ll);         // read only
+            pp.ll_pitch = ll_pitch;
+            pp.ll_ps = ll_ps;
+            pp.h = p.h[l];
+            pp.w = p.w[l];
+            const int rc = report(dwt2::launch_pair(dir, to_wav(wavelet), to_dtype(dtype), pp, planes, s));
+            if (rc) return rc;
+            ll = out;
+            ll_pitch = out_pitch;
+            ll_ps = out_ps;
+            continue;
+        }
         dwt2::LevelParams lp{};
         lp.h = p.h[l];
         lp.w = p.w[l];
@@ -401,13 +481,14 @@ int run_backward(dwt2::Direction dir, const void* src, void* dst, int32_t planes
         lp.in_ll = ll;
         lp.in_ll_pitch = ll_pitch;
         lp.in_ll_ps = ll_ps;
-        // the image of level l is the LL of level l-1 (kept in buffer (l-1) % 2)
+        // the image of level l is the LL of level l-1
         lp.ll_cached = l > 0 && cached_output(planes, p.h[l], p.w[l], es) ? 1 : 0;
-        lp.out = l == 0 ? dst : (void*)bufs[(l - 1) % 2];
-        lp.out_pitch = l == 0 ? dp : ws_pitch(lp.w);
-        lp.out_ps = l == 0 ? dps : buf_ps[(l - 1) % 2];
-        plan_grid(config_of(flags, wavelet), &lp);
-        const int rc = launch_planes(dir, wavelet, dtype, flags, lp, planes, es, s);
+        lp.out = out;
+        lp.out_pitch = out_pitch;
+        lp.out_ps = out_ps;
+        const int cfg = level_config(flags, wavelet, planes, lp.h, lp.w);
+        plan_grid(cfg, &lp);
+        const int rc = launch_planes(dir, wavelet, dtype, flags, cfg, lp, planes, es, s);
         if (rc) return rc;
         ll = lp.out;
         ll_pitch = lp.out_pitch;

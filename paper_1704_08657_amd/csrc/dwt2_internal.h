@@ -61,6 +61,7 @@ constexpr KernelConfig kConfigs[] = {
     {kAlgoLds, 4, 0, 0, 0, 32, 32}};
 constexpr int kNumConfigs = 10;
 constexpr int kDefaultConfig = 0;
+constexpr int kLargeConfig = 3;       // levels of 2^25 samples and more
 constexpr int kDefaultLdsConfig = 8;
 // The four-tap register tile kernel (DD 13/7): a halo of kHalo4 block rows
 // above and below a tile.
@@ -102,6 +103,52 @@ struct LevelParams {
     // variant.
     int32_t ll_cached;
 };
+
+// Two consecutive levels in one launch.  Forward: `in` is the h x w image of
+// the first level, `out` the pyramid (the details of both levels go there), `ll`
+// receives the second level's LL band.  Inverse / adjoint: `in` is the pyramid,
+// `ll` the second level's LL band, `out` the h x w image.  *_ps: plane strides.
+struct PairParams {
+    const void* in;
+    int64_t in_pitch, in_ps;
+    void* out;
+    int64_t out_pitch, out_ps;
+    void* ll;
+    int64_t ll_pitch, ll_ps;
+    int32_t h, w;
+    int32_t tiles_x, tiles_y;     // set by the launcher, as is planes
+    int32_t planes;
+};
+
+// Its tiles: NW * K block rows of the first level with a halo of kHalo2 above
+// and below, 64 lanes of two block columns of which kEdge2 lanes on either side
+// are halo.
+constexpr int kHalo2 = 6;
+constexpr int kEdge2 = 4;
+constexpr int kPairCols = (kLanes - 2 * kEdge2) * 2;
+inline int64_t pair_tiles(int32_t h, int32_t w, int32_t planes, int rows) {
+    const int cy = rows - 2 * kHalo2;
+    return (int64_t)(((w + 1) / 2 + kPairCols - 1) / kPairCols) * (((h + 1) / 2 + cy - 1) / cy) * planes;
+}
+// Whether two levels in one launch beat one launch each (both sides measured
+// on MI355X, us; two launches first):
+//   * a level whose tiles all run at once: always (1024^2 FP32 11.7 / 7.2,
+//     inverse 11.6 / 8.0; 192 planes of 64^2 16.0 / 9.6);
+//   * larger ones, when 112 columns a tile do not cost half as many tiles
+//     again as the one-level kernel's 128 (8192^2 FP32 121 / 109, inverse
+//     127 / 103; 3469 x 5197 41 / 34; but 192 planes of 256^2, two tiles for
+//     one: 31.4 / 33.4, adjoint 40 / 55);
+//   * 16-bit storage, forward, up to 2^26 samples: beyond, the recomputed
+//     halo costs what the LL band saves (3 x 8192^2 BF16 188 / 193,
+//     3 x 4096^2 56 / 53, inverse 198 / 176).
+inline bool pair_pays(Direction dir, Dtype dt, int32_t h, int32_t w, int32_t planes) {
+    if (pair_tiles(h, w, planes, 32) <= 512) return true;
+    const int32_t nc = (w + 1) / 2;
+    if (2 * ((nc + kPairCols - 1) / kPairCols) >= 3 * ((nc + 2 * kLanes - 1) / (2 * kLanes))) return false;
+    return !(dir == kForward && (dt == kBF16 || dt == kF16) && (int64_t)h * w * planes > (1 << 26));
+}
+// Enqueue it with the wavelet's default scheme.
+hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t stream);
 
 // Enqueue one level for `planes` planes (1 <= planes <= kMaxGridPlanes).
 // Returns hipSuccess or the launch error.  `cfg` indexes kConfigs;

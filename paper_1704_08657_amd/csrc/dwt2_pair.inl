@@ -1,0 +1,573 @@
+// Two levels of the transform in one launch: device code (included by
+// dwt2_pair_*.hip and dwt2_batched.hip).
+#pragma once
+#include "dwt2_kernels.inl"
+
+namespace dwt2 {
+namespace kern {
+namespace pair {
+
+// What one launch per level costs beside the first level's traffic: the LL
+// band written and read again (a quarter of the level each way) and, for every
+// small level, a launch and one tile's time from load to store.  A tile here
+// runs both levels: a lane holds 2 x K blocks of the first level in VGPRs as
+// in the one-level tile kernel, so its LL samples are exactly the 1 x K/2 blocks
+// of the second level that the lane then holds, without moving a value.
+//
+// Forward: level 1 on the tile, its details stored, its LL samples (rounded
+// to the storage type, as a store would) taken as the blocks of level 2, level
+// 2 on them, its four bands stored.  Inverse and adjoint: the mirror image.
+//
+// The halo is that of both levels, 2 blocks of each: kHalo2 = 6 block rows of
+// level 1 above and below, and the columns of kEdge2 lanes on either side,
+// which load and compute but do not store: 3 would do, but 4 leave 112 columns,
+// whose subband segments (448 bytes of FP32) are whole 64-byte sectors (8192^2
+// FP32, two levels forward: 114 us with 4, 126 with 3; BF16 3 x 8192^2: 218, 263).  Halo values come from the
+// neighbouring lane or wave like any others, so a step has no halo operands:
+// horizontal neighbours are DPP shifts that fold into the adds, vertical ones
+// the lane's own rows or one LDS row per wave and step.
+//
+// Borders.  Level 1 runs on the symmetric extension of its input (the
+// adjoint: on zeros and its border weights).  The LL samples this gives outside
+// the image are not what level 2 extends them to when a side is even, so a
+// border tile passes its LL samples through LDS and each lane takes the
+// reflected ones.  Every value is formed by the same operations in the same
+// order as by the one-level kernels: the results are theirs bit for bit.
+
+template <typename V, int NW> struct PairLds {
+    Vec2<V> t[NW + 1][2][kLanes];     // top block rows (x0, x1) of every wave, for the wave above
+    Vec2<V> s[NW + 1][2][kLanes];     // bottom ones (x2, x3), for the wave below
+};
+// LL samples of a border tile.
+template <typename V, int ROWS> struct PairPlane { V p[ROWS][2 * kLanes]; };
+
+// lane i <- lane i + 1 / i - 1 (0 beyond the wave): whole-wave DPP shifts the
+// compiler folds into the instruction that uses them.
+__device__ __forceinline__ int right1(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, true); }
+__device__ __forceinline__ int left1(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, true); }
+__device__ __forceinline__ float right1(float v) { return __int_as_float(right1(__float_as_int(v))); }
+__device__ __forceinline__ float left1(float v) { return __int_as_float(left1(__float_as_int(v))); }
+
+constexpr bool horizontal_kind(int k) { return k == kSepH || k == kSepHInt || k == kSepHIntInv; }
+constexpr bool vertical_kind(int k) { return k == kSepV || k == kSepVInt || k == kSepVIntInv; }
+
+// Predict-shaped step: rows top to bottom, blocks left to right, so every
+// operand right of or below a block is still the value before the step.
+template <int KIND, bool EDGE, int NW, int BPL, int K, typename V>
+__device__ __forceinline__ void plus(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int lane, int wv, const Geo& g, float c) {
+    V dn[4 * BPL];
+#pragma unroll
+    for (int i = 0; i < 4 * BPL; ++i) dn[i] = V(0);
+    if constexpr (!horizontal_kind(KIND)) {
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) L.t[wv][b][lane] = Vec2<V>{a[0][4 * b], a[0][4 * b + 1]};
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) {
+            const Vec2<V> v = L.t[wv + 1][b][lane];
+            dn[4 * b] = v.a;
+            dn[4 * b + 1] = v.b;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        const V(&d)[4 * BPL] = r + 1 < K ? a[r + 1 < K ? r + 1 : r] : dn;
+        const V R0 = vertical_kind(KIND) ? V(0) : right1(a[r][0]);
+        const V R2 = vertical_kind(KIND) ? V(0) : right1(a[r][2]);
+        const V RD0 = vertical_kind(KIND) || horizontal_kind(KIND) ? V(0) : right1(d[0]);
+#pragma unroll
+        for (int b = 0; b < BPL; ++b)
+            plus_block<KIND, EDGE, EDGE>(a[r][4 * b], a[r][4 * b + 1], a[r][4 * b + 2], a[r][4 * b + 3],
+                                         b + 1 < BPL ? a[r][4 * ((b + 1) % BPL)] : R0,
+                                         b + 1 < BPL ? a[r][4 * ((b + 1) % BPL) + 2] : R2, d[4 * b], d[4 * b + 1],
+                                         b + 1 < BPL ? d[4 * ((b + 1) % BPL)] : RD0, g.gcL + b, g.gr0 + r, g, c);
+    }
+}
+
+// Update-shaped step: rows bottom to top, blocks right to left.
+template <int KIND, bool EDGE, int NW, int BPL, int K, typename V>
+__device__ __forceinline__ void minus(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int lane, int wv, const Geo& g, float c) {
+    V up[4 * BPL];
+#pragma unroll
+    for (int i = 0; i < 4 * BPL; ++i) up[i] = V(0);
+    if constexpr (!horizontal_kind(KIND)) {
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) L.s[wv + 1][b][lane] = Vec2<V>{a[K - 1][4 * b + 2], a[K - 1][4 * b + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) {
+            const Vec2<V> v = L.s[wv][b][lane];
+            up[4 * b + 2] = v.a;
+            up[4 * b + 3] = v.b;
+        }
+    }
+#pragma unroll
+    for (int r = K - 1; r >= 0; --r) {
+        const V(&u)[4 * BPL] = r > 0 ? a[r > 0 ? r - 1 : 0] : up;
+        const V L1 = vertical_kind(KIND) ? V(0) : left1(a[r][4 * BPL - 3]);
+        const V L3 = vertical_kind(KIND) ? V(0) : left1(a[r][4 * BPL - 1]);
+        const V LU3 = vertical_kind(KIND) || horizontal_kind(KIND) ? V(0) : left1(u[4 * BPL - 1]);
+#pragma unroll
+        for (int b = BPL - 1; b >= 0; --b)
+            minus_block<KIND, EDGE, EDGE>(a[r][4 * b], a[r][4 * b + 1], a[r][4 * b + 2], a[r][4 * b + 3],
+                                          b > 0 ? a[r][4 * ((b + BPL - 1) % BPL) + 1] : L1,
+                                          b > 0 ? a[r][4 * ((b + BPL - 1) % BPL) + 3] : L3, u[4 * b + 2], u[4 * b + 3],
+                                          b > 0 ? u[4 * ((b + BPL - 1) % BPL) + 3] : LU3, g.gcL + b, g.gr0 + r, g, c);
+    }
+}
+
+template <int BPL, int K, typename V>
+__device__ __forceinline__ void scale_bands(V (&a)[K][4 * BPL], float s0, float s3) {
+#pragma unroll
+    for (int r = 0; r < K; ++r)
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) {
+            a[r][4 * b] *= s0;
+            a[r][4 * b + 3] *= s3;
+        }
+}
+
+// The step program of one level (the same steps as the one-level kernel's
+// fused and factored schemes).  Predict- and update-shaped steps alternate
+// over both levels, and each shape has its own LDS rows, so the one barrier of
+// a step also orders the rows' reuse.
+template <int DIR, int WAV, int SCH, bool EDGE, int NW, int BPL, int K, typename V>
+__device__ __forceinline__ void steps(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int lane, int wv, const Geo& g) {
+    static_assert(SCH == kSchemeFused || SCH == kSchemeFactored, "default schemes");
+#define DWT2_P(KIND_, c_) plus<KIND_, EDGE, NW, BPL, K>(a, L, lane, wv, g, (c_));
+#define DWT2_M(KIND_, c_) minus<KIND_, EDGE, NW, BPL, K>(a, L, lane, wv, g, (c_));
+    if constexpr (WAV == kCdf53) {
+        static_assert(SCH == kSchemeFused, "the integer wavelet's default scheme");
+        if constexpr (DIR == kForward) { DWT2_P(kIntFwd, 0.f) DWT2_M(kIntFwd, 0.f) }
+        else { DWT2_M(kIntInv, 0.f) DWT2_P(kIntInv, 0.f) }
+    } else if constexpr (WAV == kCdf53Real) {
+        if constexpr (DIR == kForward) {
+            if constexpr (SCH == kSchemeFused) { DWT2_P(kFloat, kP53) DWT2_M(kFloat, kU53) }
+            else { DWT2_P(kSepH, kP53) DWT2_P(kSepV, kP53) DWT2_M(kSepH, kU53) DWT2_M(kSepV, kU53) }
+            scale_bands<BPL, K>(a, kZeta53Sq, kZeta53SqInv);
+        } else {
+            scale_bands<BPL, K>(a, kZeta53SqInv, kZeta53Sq);
+            if constexpr (SCH == kSchemeFused) { DWT2_M(kFloat, -kU53) DWT2_P(kFloat, -kP53) }
+            else { DWT2_M(kSepV, -kU53) DWT2_M(kSepH, -kU53) DWT2_P(kSepV, -kP53) DWT2_P(kSepH, -kP53) }
+        }
+    } else if constexpr (DIR == kForward) {
+        if constexpr (SCH == kSchemeFused) {
+            DWT2_P(kFloat, kAlpha) DWT2_M(kFloat, kBeta) DWT2_P(kFloat, kGamma) DWT2_M(kFloat, kDelta)
+        } else {
+            DWT2_P(kSepH, kAlpha) DWT2_P(kSepV, kAlpha) DWT2_M(kSepH, kBeta) DWT2_M(kSepV, kBeta)
+            DWT2_P(kSepH, kGamma) DWT2_P(kSepV, kGamma) DWT2_M(kSepH, kDelta) DWT2_M(kSepV, kDelta)
+        }
+        scale_bands<BPL, K>(a, kZeta2, kZetaM2);
+    } else if constexpr (DIR == kInverse) {
+        scale_bands<BPL, K>(a, kZetaM2, kZeta2);
+        if constexpr (SCH == kSchemeFused) {
+            DWT2_M(kFloat, -kDelta) DWT2_P(kFloat, -kGamma) DWT2_M(kFloat, -kBeta) DWT2_P(kFloat, -kAlpha)
+        } else {
+            DWT2_M(kSepV, -kDelta) DWT2_M(kSepH, -kDelta) DWT2_P(kSepV, -kGamma) DWT2_P(kSepH, -kGamma)
+            DWT2_M(kSepV, -kBeta) DWT2_M(kSepH, -kBeta) DWT2_P(kSepV, -kAlpha) DWT2_P(kSepH, -kAlpha)
+        }
+    } else {
+        scale_bands<BPL, K>(a, kZeta2, kZetaM2);
+        DWT2_P(kAdj, kDelta) DWT2_M(kAdj, kGamma) DWT2_P(kAdj, kBeta) DWT2_M(kAdj, kAlpha)
+    }
+#undef DWT2_P
+#undef DWT2_M
+}
+
+// The symmetric extension of N positions on either side (fold() takes -6 and
+// above; positions further out, which no stored output reads, keep their
+// parity and move there).
+template <int N>
+__device__ __forceinline__ void fold_both(int (&p)[N], int n) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = p[i] < -6 ? -6 + (p[i] & 1) : p[i];
+    fold(p, n);
+}
+
+// The image rows of a tile (forward): g.cb0 may be negative.
+template <typename T, int BPL, int K>
+__device__ __forceinline__ void load_image(typename St<T>::V (&a)[K][4 * BPL], const T* in, int64_t pitch, int h,
+                                           int w, const Geo& g, bool interior, int lane) {
+    using V = typename St<T>::V;
+    int rows[2 * K];
+#pragma unroll
+    for (int i = 0; i < 2 * K; ++i) rows[i] = 2 * g.gr0 + i;
+    if (!interior) fold_both(rows, h);
+    const int c0 = 2 * g.gcL;
+    if (interior || (c0 >= 0 && c0 + 2 * BPL <= w)) {
+        const T* const base = in + 2 * g.cb0;
+#pragma unroll
+        for (int i = 0; i < 2 * K; ++i) {
+            V v[2 * BPL];
+            load_vec<T, 2 * BPL>(lane_at(base + (int64_t)rows[i] * pitch, (uint32_t)lane * (2 * BPL * sizeof(T))), v);
+#pragma unroll
+            for (int s = 0; s < 2 * BPL; ++s) a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)] = v[s];
+        }
+    } else {
+        int cols[2 * BPL];
+#pragma unroll
+        for (int i = 0; i < 2 * BPL; ++i) cols[i] = c0 + i;
+        fold_both(cols, w);
+#pragma unroll
+        for (int i = 0; i < 2 * K; ++i)
+#pragma unroll
+            for (int s = 0; s < 2 * BPL; ++s)
+                a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)] = St<T>::load((in + (int64_t)rows[i] * pitch)[cols[s]]);
+    }
+}
+
+template <typename T, int N>
+__device__ __forceinline__ void load_band_row(typename St<T>::V (&v)[N], const T* p) {
+    if constexpr (N > 1) load_vec<T, N>(p, v);
+    else v[0] = St<T>::load(p[0]);
+}
+template <typename T, int N>
+__device__ __forceinline__ void store_band_row(T* p, const typename St<T>::V (&v)[N]) {
+    // a wave's row of single 16-bit samples is less than a line: an ordinary
+    // store, so that the caches gather the rows' neighbours (3 x 8192^2 BF16,
+    // two levels forward: 193 us, 218 nontemporal)
+    if constexpr (N > 1) store_vec<T, N>(p, v);
+    else if constexpr (sizeof(T) == 4) nt_store1<T>(p, St<T>::store(v[0]));
+    else p[0] = St<T>::store(v[0]);
+}
+
+// The bands K0 .. 3 of a tile of a pyramid level (h x w; inverse and adjoint).
+// ZERO: samples outside the level are 0 (adjoint).
+template <typename T, bool ZERO, int K0, int BPL, int K>
+__device__ __forceinline__ void load_bands(typename St<T>::V (&a)[K][4 * BPL], const T* ll, int64_t ll_pitch,
+                                           const T* det, int64_t pitch, int h, int w, const Geo& g, bool interior,
+                                           int lane) {
+    using V = typename St<T>::V;
+    int rows[2 * K];
+#pragma unroll
+    for (int i = 0; i < 2 * K; ++i) rows[i] = 2 * g.gr0 + i;
+    if (!ZERO && !interior) fold_both(rows, h);
+    const int c0 = 2 * g.gcL;
+    if (interior || (c0 >= 0 && c0 + 2 * BPL <= w)) {
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+#pragma unroll
+            for (int k = K0; k < 4; ++k) {
+                V v[BPL];
+                const int p = rows[2 * r + (k >> 1)];
+                const bool ok = !ZERO || interior || (p >= 0 && p < h);
+                load_band_row<T, BPL>(v, lane_at(subband_row(ll, ll_pitch, det, pitch, g, k, ok ? p >> 1 : 0) + g.cb0,
+                                                 (uint32_t)lane * (BPL * sizeof(T))));
+#pragma unroll
+                for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = ok ? v[b] : V(0);
+            }
+    } else {
+        int cols[2 * BPL];
+#pragma unroll
+        for (int i = 0; i < 2 * BPL; ++i) cols[i] = c0 + i;
+        if constexpr (!ZERO) fold_both(cols, w);
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+#pragma unroll
+            for (int k = K0; k < 4; ++k) {
+                const int p = rows[2 * r + (k >> 1)];
+                const bool ok = !ZERO || (p >= 0 && p < h);
+                const T* row = subband_row(ll, ll_pitch, det, pitch, g, k, ok ? p >> 1 : 0);
+#pragma unroll
+                for (int b = 0; b < BPL; ++b) {
+                    const int c = cols[2 * b + (k & 1)];
+                    V v = V(0);
+                    if (!ZERO || (ok && c >= 0 && c < w)) v = St<T>::load(row[c >> 1]);
+                    a[r][4 * b + k] = v;
+                }
+            }
+    }
+}
+
+// Bands K0 .. 3 of the tile's core to a pyramid level (forward).  H: halo
+// rows of the tile at this level (NW * K rows).
+template <typename T, bool BORDER, int K0, int H, int NW, int BPL, int K>
+__device__ __forceinline__ void store_bands(typename St<T>::V (&a)[K][4 * BPL], T* ll, int64_t ll_pitch, T* det,
+                                            int64_t pitch, const Geo& g, int lane, int wv) {
+    using V = typename St<T>::V;
+    constexpr bool kBySubband = !BORDER && sizeof(T) == 4;
+    T* row[4];
+#pragma unroll
+    for (int k = K0; k < 4; ++k) row[k] = subband_row(ll, ll_pitch, det, pitch, g, k, g.gr0) + g.cb0;
+#pragma unroll
+    for (int k0 = K0; k0 < (kBySubband ? 4 : K0 + 1); ++k0)
+#pragma unroll
+        for (int r = 0; r < K; ++r)
+#pragma unroll
+            for (int k = (kBySubband ? k0 : K0); k < (kBySubband ? k0 + 1 : 4); ++k) {
+                T* const p = lane_at(row[k], (uint32_t)lane * (BPL * sizeof(T)));
+                row[k] += k == 0 ? ll_pitch : pitch;
+                const int tr = wv * K + r;
+                if (tr < H || tr >= NW * K - H) continue;
+                if (BORDER && g.gr0 + r >= (k >= 2 ? g.nOr : g.nEr)) continue;
+                V v[BPL];
+#pragma unroll
+                for (int b = 0; b < BPL; ++b) v[b] = a[r][4 * b + k];
+                const int left = BORDER ? ((k & 1) ? g.nOc : g.nEc) - g.gcL : BPL;   // samples to the row's end
+                if (!BORDER || left >= BPL) {
+                    store_band_row<T, BPL>(p, v);
+                } else {
+#pragma unroll
+                    for (int b = 0; b + 1 < BPL; ++b)
+                        if (b < left) p[b] = St<T>::store(v[b]);
+                }
+            }
+}
+
+// The tile's core as image rows (inverse and adjoint).
+template <typename T, bool BORDER, int H, int NW, int BPL, int K>
+__device__ __forceinline__ void store_image(typename St<T>::V (&a)[K][4 * BPL], T* out, int64_t pitch, int h, int w,
+                                            const Geo& g, int lane, int wv) {
+    using V = typename St<T>::V;
+    T* row = out + (int64_t)(2 * g.gr0) * pitch + 2 * g.cb0;
+    const int left = w - 2 * g.gcL;
+#pragma unroll
+    for (int i = 0; i < 2 * K; ++i) {
+        T* const p = lane_at(row, (uint32_t)lane * (2 * BPL * sizeof(T)));
+        row += pitch;
+        const int tr = wv * K + (i >> 1);
+        if (tr < H || tr >= NW * K - H) continue;
+        if (BORDER && 2 * g.gr0 + i >= h) continue;
+        V v[2 * BPL];
+#pragma unroll
+        for (int s = 0; s < 2 * BPL; ++s) v[s] = a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)];
+        if (!BORDER || left >= 2 * BPL) {
+            store_vec<T, 2 * BPL>(p, v);
+        } else {
+#pragma unroll
+            for (int s = 0; s + 1 < 2 * BPL; ++s)
+                if (s < left) p[s] = St<T>::store(v[s]);
+        }
+    }
+}
+
+__device__ __forceinline__ int clamp_to(int x, int n) { return x < 0 ? 0 : x < n ? x : n - 1; }
+
+// What storing a value and loading it again gives.
+template <typename T>
+__device__ __forceinline__ typename St<T>::V stored(typename St<T>::V v) { return St<T>::load(St<T>::store(v)); }
+
+// Tile (tx, ty) of levels l and l + 1.
+template <int DIR, int WAV, typename T, int SCH, int NW, int K>
+__device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLds<typename St<T>::V, NW>& L,
+                                     PairPlane<typename St<T>::V, NW * K>& S, int lane, int wv) {
+    using V = typename St<T>::V;
+    static_assert(K % 2 == 0, "a wave's rows are whole blocks of the second level");
+    constexpr int R = NW * K, CY = R - 2 * kHalo2, K2 = K / 2;
+    Geo g, g2;
+    g.nEr = (P.h + 1) >> 1; g.nOr = P.h >> 1;
+    g.nEc = (P.w + 1) >> 1; g.nOc = P.w >> 1;
+    const int r0 = ty * CY - kHalo2;               // tile's first block row of level 1
+    g.cb0 = tx * kPairCols - 2 * kEdge2;
+    g.gcL = g.cb0 + 2 * lane;
+    g.gr0 = r0 + wv * K;
+    const int h2 = g.nEr, w2 = g.nEc;
+    g2.nEr = (h2 + 1) >> 1; g2.nOr = h2 >> 1;
+    g2.nEc = (w2 + 1) >> 1; g2.nOc = w2 >> 1;
+    g2.cb0 = g.cb0 >> 1;
+    g2.gcL = g2.cb0 + lane;
+    g2.gr0 = g.gr0 >> 1;
+    const bool interior = r0 >= 0 && g.cb0 >= 0 && r0 + R <= g.nOr && g.cb0 + 2 * kLanes <= g.nOc;
+    const bool core_lane = lane >= kEdge2 && lane < kLanes - kEdge2;
+    V a[K][8], b[K2][4];
+    if constexpr (DIR == kForward) {
+        load_image<T, 2, K>(a, static_cast<const T*>(P.in), P.in_pitch, P.h, P.w, g, interior, lane);
+        steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        T* const out = static_cast<T*>(P.out);
+        if (core_lane) {
+            if (interior) store_bands<T, false, 1, kHalo2, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
+            else store_bands<T, true, 1, kHalo2, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
+        }
+#pragma unroll
+        for (int r = 0; r < K2; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[r][k] = stored<T>(a[2 * r + (k >> 1)][4 * (k & 1)]);
+        if (!interior) {
+#pragma unroll
+            for (int r = 0; r < K2; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) S.p[wv * K + 2 * r + (k >> 1)][2 * lane + (k & 1)] = b[r][k];
+            __syncthreads();
+            int rows[K], cols[2];
+#pragma unroll
+            for (int i = 0; i < K; ++i) rows[i] = 2 * g2.gr0 + i;
+            cols[0] = 2 * g2.gcL;
+            cols[1] = 2 * g2.gcL + 1;
+            fold_both(rows, h2);
+            fold_both(cols, w2);
+#pragma unroll
+            for (int r = 0; r < K2; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    b[r][k] = S.p[clamp_to(rows[2 * r + (k >> 1)] - r0, R)][clamp_to(cols[k & 1] - g.cb0, 2 * kLanes)];
+        }
+        steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+        T* const ll = static_cast<T*>(P.ll);
+        if (core_lane) {
+            if (interior) store_bands<T, false, 0, kHalo2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
+            else store_bands<T, true, 0, kHalo2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
+        }
+    } else {
+        constexpr bool kZero = DIR == kAdjoint;
+        const T* const det = static_cast<const T*>(P.in);
+        load_bands<T, kZero, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2,
+                                       interior, lane);
+        load_bands<T, kZero, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        if constexpr (kZero) {
+            // the transposed border weights multiply rows beyond the tile by 0, which must stay finite
+            if (wv == NW - 1) L.t[NW][0][lane] = L.t[NW][1][lane] = Vec2<V>{V(0), V(0)};
+            if (wv == 0) L.s[0][0][lane] = L.s[0][1][lane] = Vec2<V>{V(0), V(0)};
+            if (interior) steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+            else steps<DIR, WAV, SCH, true, NW, 1, K2>(b, L, lane, wv, g2);
+        } else {
+            steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+        }
+#pragma unroll
+        for (int r = 0; r < K2; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a[2 * r + (k >> 1)][4 * (k & 1)] = stored<T>(b[r][k]);
+        if (!interior) {
+            if constexpr (kZero) {
+#pragma unroll
+                for (int r = 0; r < K; ++r)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const int gr = g.gr0 + r, gc = g.gcL + c;
+                        if (gr < 0 || gr >= h2 || gc < 0 || gc >= w2) a[r][4 * c] = V(0);
+                    }
+            } else {
+#pragma unroll
+                for (int r = 0; r < K; ++r)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) S.p[wv * K + r][2 * lane + c] = a[r][4 * c];
+                __syncthreads();
+                // LL sample of block (gr, gc): at its reflected pixel position
+                int rows[K], cols[2];
+#pragma unroll
+                for (int i = 0; i < K; ++i) rows[i] = 2 * (g.gr0 + i);
+                cols[0] = 2 * g.gcL;
+                cols[1] = 2 * g.gcL + 2;
+                fold_both(rows, P.h);
+                fold_both(cols, P.w);
+#pragma unroll
+                for (int r = 0; r < K; ++r)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        a[r][4 * c] = S.p[clamp_to((rows[r] >> 1) - r0, R)][clamp_to((cols[c] >> 1) - g.cb0, 2 * kLanes)];
+            }
+        }
+        if (kZero && !interior) steps<DIR, WAV, SCH, true, NW, 2, K>(a, L, lane, wv, g);
+        else steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        if (core_lane) {
+            T* const out = static_cast<T*>(P.out);
+            if (interior) store_image<T, false, kHalo2, NW, 2, K>(a, out, P.out_pitch, P.h, P.w, g, lane, wv);
+            else store_image<T, true, kHalo2, NW, 2, K>(a, out, P.out_pitch, P.h, P.w, g, lane, wv);
+        }
+    }
+}
+
+template <int DIR, int WAV, typename T, int SCH, int NW, int K>
+__global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
+    using V = typename St<T>::V;
+    __shared__ PairLds<V, NW> L;
+    __shared__ PairPlane<V, NW * K> S;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    // every kernel argument in one round trip, see fetch_params
+    asm volatile("" ::"s"(P.in), "s"(P.in_pitch), "s"(P.in_ps), "s"(P.out), "s"(P.out_pitch), "s"(P.out_ps), "s"(P.ll),
+                 "s"(P.ll_pitch), "s"(P.ll_ps), "s"(P.h), "s"(P.w), "s"(P.tiles_x), "s"(P.tiles_y), "s"(P.planes));
+    // XCD remap of the tile list (all planes), as in the one-level kernel
+    const int nt = P.tiles_x * P.tiles_y;
+    const int chunk = kRemapRows * P.tiles_x;
+    const int j = (int)(blockIdx.x >> 3);
+    const int n = ((j / chunk) * 8 + (int)(blockIdx.x & 7)) * chunk + j % chunk;
+    if (n >= nt * P.planes) return;               // uniform over the work-group
+    const int pl = n / nt;
+    const int t = n - pl * nt;
+    const int ty = t / P.tiles_x;
+    const int tx = t - ty * P.tiles_x;
+    PairParams Q = P;
+    Q.in = static_cast<const T*>(P.in) + (int64_t)pl * P.in_ps;
+    Q.out = static_cast<T*>(P.out) + (int64_t)pl * P.out_ps;
+    Q.ll = static_cast<T*>(P.ll) + (int64_t)pl * P.ll_ps;
+    tile<DIR, WAV, T, SCH, NW, K>(Q, tx, ty, L, S, lane, wv);
+}
+
+// ---- launch (host) ----------------------------------------------------------
+template <int DIR, int WAV, typename T, int SCH, int NW, int K>
+hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
+    constexpr int CY = NW * K - 2 * kHalo2;
+    p.tiles_x = ((p.w + 1) / 2 + kPairCols - 1) / kPairCols;
+    p.tiles_y = ((p.h + 1) / 2 + CY - 1) / CY;
+    // the tiles of all planes, rounded up to a multiple of 8 chunks; planes
+    // beyond what one grid holds go to further launches
+    const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
+    const int64_t chunk = (int64_t)kRemapRows * p.tiles_x;
+    const int64_t limit = 0x7fffffff - 8 * chunk;
+    if (nt < 1 || nt > limit) return hipErrorInvalidConfiguration;
+    const int64_t per = limit / nt;
+    for (int64_t p0 = 0; p0 < planes; p0 += per) {
+        PairParams q = p;
+        q.planes = (int32_t)(planes - p0 < per ? planes - p0 : per);
+        q.in = static_cast<const T*>(p.in) + p0 * p.in_ps;
+        q.out = static_cast<T*>(p.out) + p0 * p.out_ps;
+        q.ll = static_cast<T*>(p.ll) + p0 * p.ll_ps;
+        const int64_t grid = (nt * q.planes + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
+        hipLaunchKernelGGL((pair_kernel<DIR, WAV, T, SCH, NW, K>), dim3((unsigned)grid), dim3(NW * kLanes), 0, s, q);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Tile shape.  Few tiles, all on the chip at once (two work-groups of 8 waves
+// on each of 256 CUs): the shape that takes the least time from load to store,
+// 8 waves x 4 rows (1024^2 FP32 forward 7.2 us, 8 x 6: 9.1, 4 x 8: 8.5).
+// Otherwise 8 x 6, which recomputes 12 of 48 rows instead of 12 of 32 (3 x 1081
+// x 1921: 13.3 us, 16.0, 16.9; inverse 3 x 8192^2 FP16: 176, 194, 180).  Beyond
+// 2^25 4-byte samples the memory system is the limit, and smaller work-groups
+// overlap their loads, steps and stores better: forward 4 x 8, inverse 8 x 4
+// (8192^2 FP32: 109 us, 8 x 6 114; 103, 109).  The adjoint has two step
+// programs (border weights) and keeps 8 x 4, where both fit the registers
+// (8192^2: 124 us, 8 x 6 161).
+template <int DIR, int WAV, typename T, int SCH>
+hipError_t launch(const PairParams& p, int planes, hipStream_t s) {
+    if constexpr (DIR == kAdjoint) {
+        return launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
+    } else {
+        if (pair_tiles(p.h, p.w, planes, 8 * 4) <= 512) return launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
+        if (sizeof(T) == 4 && (int64_t)p.h * p.w * planes >= (1 << 25))
+            return DIR == kForward ? launch_shape<DIR, WAV, T, SCH, 4, 8>(p, planes, s)
+                                   : launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
+        return launch_shape<DIR, WAV, T, SCH, 8, 6>(p, planes, s);
+    }
+}
+
+// The default schemes: fused steps for 4-byte samples and for the adjoint,
+// factored ones for 16-bit storage.
+template <int DIR, int WAV, typename T>
+hipError_t launch_t(const PairParams& p, int planes, hipStream_t s) {
+    return launch<DIR, WAV, T, (sizeof(T) == 4 || DIR == kAdjoint) ? kSchemeFused : kSchemeFactored>(p, planes, s);
+}
+template <int DIR, int WAV>
+hipError_t launch_float(Dtype dt, const PairParams& p, int planes, hipStream_t s) {
+    switch (dt) {
+        case kF32: return launch_t<DIR, WAV, float>(p, planes, s);
+        case kBF16: return launch_t<DIR, WAV, __hip_bfloat16>(p, planes, s);
+        case kF16: return launch_t<DIR, WAV, __half>(p, planes, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+template <int DIR>
+hipError_t launch_dir(Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t s) {
+    if (wav == kCdf97) return launch_float<DIR, kCdf97>(dt, p, planes, s);
+    if constexpr (DIR != kAdjoint) {
+        if (wav == kCdf53) return launch_t<DIR, kCdf53, int32_t>(p, planes, s);
+        if (wav == kCdf53Real) return launch_float<DIR, kCdf53Real>(dt, p, planes, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+}  // namespace pair
+}  // namespace kern
+}  // namespace dwt2

@@ -291,8 +291,8 @@ int dwt2_workspace_bytes_batched(const dwt2_image* images, int count, dwt2_dtype
 /* Batched forward CDF 9/7 (Section "Proposed Schemes", non-separable lifting,
  * applied to each image as dwt2_fwd would): `count` independent images of any
  * (uneven) sizes, every one transformed to `levels` levels, on `stream`.  By
- * default a planner launch plus one launch per level, the launch of a level
- * covering the tiles of all images.  With DWT2_FLAG_PERSISTENT: a planner
+ * default a planner launch plus one launch per level, or (flags 0, where it is
+ * the faster way) per two levels, each covering the tiles of all images.  With DWT2_FLAG_PERSISTENT: a planner
  * launch plus one persistent launch for every level; its work-groups take
  * tiles (of every image) from work queues, level after level, and a tile of
  * level l >= 1 first waits until the tiles of level l - 1 whose LL rows it

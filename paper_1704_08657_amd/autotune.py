@@ -175,14 +175,17 @@ def tune(sizes=(256, 1024, 4096, 8192), levels=(1, 5), quick=False, out=CACHE_PA
         shapes = [(int(h), int(w)) for h, w in zip(*[iter(
             torch.randint(32, 2049, (64,), generator=torch.Generator().manual_seed(1)).mul(2).tolist())] * 2)]
         imgs = [torch.rand(s, device=dev).to(dts[dt]) for s in shapes]
+        k = f"{arch}|batched|cdf97|{dt}|any|5"
+        _record(k, None)
         best, best_ms = None, float("inf")
-        for c in [i for i in range(nconf) if d.dwt2_kernel_config(i)[1] == d.DWT2_ALGO_TILE]:
+        for c in [None] + [i for i in range(nconf) if d.dwt2_kernel_config(i)[1] == d.DWT2_ALGO_TILE]:
             call = d.BatchedForward(imgs, 5, config=c)
             ms = _time(torch, lambda i: call.run(), steps=5 if quick else 10, warm=2)
             if ms < best_ms:
                 best, best_ms = c, ms
-        k = f"{arch}|batched|cdf97|{dt}|any|5"
-        result[k] = best
+        result.pop(k, None)
+        if best is not None:
+            result[k] = best
         log(f"{k}: config {best} ({best_ms * 1e3:.1f} us)")
     with open(out, "w") as f:
         json.dump(result, f, indent=1, sort_keys=True)

@@ -351,6 +351,34 @@ int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int w
     return two ? 2 : 1;
 }
 
+// Two levels in one launch for a whole batch: the same choice as for a stack of
+// planes (pair_pays), on the sums over the images.
+struct BatchPairStats {
+    uint64_t tiles32, tiles48;    // tiles of 32 and of 48 block rows
+    uint64_t cols112, cols128;    // tiles across, two-level and one-level, weighted by the image's rows
+    uint64_t samples;
+};
+void add_pair_stats(int32_t h, int32_t w, int levels, BatchPairStats* st) {
+    for (int l = 0; l + 1 < levels; ++l) {
+        int32_t tx, ty;
+        dwt2::pair_tile_grid(h, w, 32, &tx, &ty);
+        st[l].tiles32 += (uint64_t)tx * (uint64_t)ty;
+        dwt2::pair_tile_grid(h, w, 48, &tx, &ty);
+        st[l].tiles48 += (uint64_t)tx * (uint64_t)ty;
+        st[l].cols112 += (uint64_t)tx * (uint64_t)h;
+        st[l].cols128 += (uint64_t)(((w + 1) / 2 + 2 * dwt2::kLanes - 1) / (2 * dwt2::kLanes)) * (uint64_t)h;
+        st[l].samples += (uint64_t)h * (uint64_t)w;
+        h = (h + 1) / 2;
+        w = (w + 1) / 2;
+    }
+}
+bool batch_pair_pays(int dtype, const BatchPairStats& st) {
+    if (st.tiles32 <= 512) return true;
+    if (st.tiles48 > 0x7fff0000ull) return false;
+    if (2 * st.cols112 >= 3 * st.cols128) return false;
+    return !(dtype != DWT2_F32 && st.samples > (1 << 26));
+}
+
 int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t dps, int32_t h, int32_t w,
                 int64_t sp, int64_t dp, int dtype, int wavelet, int levels, unsigned flags, void* ws,
                 hipStream_t s) {
@@ -684,11 +712,15 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
     }
     if (((flags & DWT2_FLAG_KERNEL_MASK) >> DWT2_FLAG_KERNEL_SHIFT) > (unsigned)dwt2::kNumConfigs)
         return DWT2_E_FLAGS;
-    const int cfg = config_of(flags, wavelet);
+    // without a named configuration: the taller tile, which measured fastest on
+    // batches of uneven images (64 of 32 ... 2048 pixels a side, 5 levels)
+    const int cfg = (flags & DWT2_FLAG_KERNEL_MASK) ? config_of(flags, wavelet) : dwt2::kLargeConfig;
     if (!dwt2::persist_config_supported(cfg)) return DWT2_E_FLAGS;
     const size_t es = elem_size(dtype);
     const dwt2::KernelConfig kc = dwt2::kConfigs[cfg];
     uint64_t tiles[32] = {0}, chunks = 0, all_tiles = 0;
+    BatchPairStats stats[32] = {};
+    const bool pairs = flags == 0;
     for (int i = 0; i < count; ++i) {
         const dwt2_image& im = host_images[i];
         if (!im.src || !im.dst) return DWT2_E_NULL;
@@ -700,6 +732,7 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
             return DWT2_E_ALIAS;
         for (int l = 0; l < levels; ++l)
             tiles[l] += dwt2::level_tile_count(im.height, im.width, l, dwt2::core_cols(kc), dwt2::core_rows(kc));
+        if (pairs) add_pair_stats(im.height, im.width, levels, stats);
         uint64_t c, t;
         image_work(im.height, im.width, levels, cfg, &c, &t);
         chunks += c;
@@ -727,10 +760,17 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
         return report(dwt2::launch_fwd_persistent(to_dtype(dtype), sch, cfg, S, count, levels, workspace, L,
                                                   all_tiles, (hipStream_t)stream));
     }
-    uint32_t tiles_per_level[32];
-    for (int l = 0; l < levels; ++l) tiles_per_level[l] = (uint32_t)tiles[l];
-    return report(dwt2::launch_fwd_batched_levels(to_dtype(dtype), sch, cfg, device_images, count, levels,
-                                                  workspace, tiles_per_level, (hipStream_t)stream));
+    dwt2::BatchLaunches B{};
+    uint32_t launch_tiles[32];
+    for (int l = 0; l < levels; ++B.n) {
+        const bool two = pairs && l + 1 < levels && batch_pair_pays(dtype, stats[l]);
+        B.first[B.n] = (int8_t)l;
+        B.pair_rows[B.n] = (int8_t)(!two ? 0 : stats[l].tiles32 <= 512 ? 32 : 48);
+        launch_tiles[B.n] = (uint32_t)(!two ? tiles[l] : stats[l].tiles32 <= 512 ? stats[l].tiles32 : stats[l].tiles48);
+        l += two ? 2 : 1;
+    }
+    return report(dwt2::launch_fwd_batched_levels(to_dtype(dtype), sch, cfg, B, device_images, count, levels,
+                                                  workspace, launch_tiles, (hipStream_t)stream));
 }
 
 int dwt2_workspace_status(const void* header) {

@@ -2,11 +2,11 @@
 // or a stack of equal planes (dwt2_fwd / dwt2_fwd_planes with
 // DWT2_FLAG_PERSISTENT), every level.
 //
-// One launch per level (the default of dwt2_fwd_batched): a planner kernel
-// lays out, from the device copy of the image descriptors, per level an
-// exclusive scan of the images' tile counts and every image's LL ping-pong
-// buffers; then one launch per level runs every image's tiles of that level.
-// Levels are ordered by the kernel boundaries of the stream alone.
+// One launch per level or per two levels (the default of dwt2_fwd_batched): a
+// planner kernel lays out, from the device copy of the image descriptors, per
+// launch an exclusive scan of the images' tile counts and every image's LL
+// ping-pong buffers; then each launch runs every image's tiles of its level or
+// levels.  Launches are ordered by the kernel boundaries of the stream alone.
 //
 // One persistent launch (DWT2_FLAG_PERSISTENT): a planner kernel (one work-group) builds the work tables of
 // dwt2_batch_plan.h from the image shapes and clears every counter; then one
@@ -42,6 +42,7 @@
 // of level l + 2 may run while a tile of level l + 1 still reads level l's
 // band.
 #include "dwt2_launch.inl"
+#include "dwt2_pair.inl"
 
 #include <stdlib.h>
 
@@ -206,26 +207,26 @@ persist_plan_kernel(ImageSet S, int count, int levels, int core_cols, int core_r
     for (uint32_t j = tid; j < base; j += kPlanThreads) done[j] = 0;
 }
 
-// ---- one launch per level --------------------------------------------------
-// Planner: per level an exclusive scan of the images' tile counts (one launch
-// of that level covers the tiles of all images) and each image's two LL
-// ping-pong buffers.
+// ---- one launch per level or two levels -------------------------------------
+// Planner: per launch an exclusive scan of the images' tile counts (a launch
+// covers the tiles of all images), and each image's two LL ping-pong buffers.
+// Work-group j scans for launch j, the last one the buffers: the scans are
+// latency alone (a read, two barriers per 1024 images), so they run side by side
+// (60 images, 5 levels: 4.7 us; one after the other in one work-group 7.5).
 __global__ void __launch_bounds__(kPlanThreads)
-level_plan_kernel(const dwt2_image* imgs, int count, int levels, int core_cols, int core_rows, int es,
+level_plan_kernel(const dwt2_image* imgs, int count, int levels, BatchLaunches B, int core_cols, int core_rows, int es,
                   unsigned char* ws) {
-    __shared__ uint32_t sh32[1][kPlanThreads / kLanes];
-    __shared__ uint64_t sh64[1][kPlanThreads / kLanes];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, j = blockIdx.x;
     const LevelBatchLayout L = level_batch_layout(count, levels);
-    uint32_t* tile_off = reinterpret_cast<uint32_t*>(ws + L.off_tile);
-    uint64_t* ll_off = reinterpret_cast<uint64_t*>(ws + L.off_ll_off);
-    for (int l = 0; l < levels; ++l) {
-        uint32_t* row = tile_off + (size_t)l * (count + 1);
+    if (j < B.n) {
+        __shared__ uint32_t sh32[1][kPlanThreads / kLanes];
+        uint32_t* row = reinterpret_cast<uint32_t*>(ws + L.off_tile) + (size_t)j * (count + 1);
+        const int l = B.first[j], rows = B.pair_rows[j];
         uint32_t carry = 0;
         for (int b = 0; b < count; b += kPlanThreads) {
             const int i = b + tid;
-            uint32_t v[1] = {i < count ? (uint32_t)level_tile_count(imgs[i].height, imgs[i].width, l, core_cols,
-                                                                    core_rows)
+            uint32_t v[1] = {i < count ? (uint32_t)launch_tile_count(imgs[i].height, imgs[i].width, l, rows, core_cols,
+                                                                     core_rows)
                                        : 0u};
             uint32_t t[1];
             block_scan<1>(v, t, sh32);
@@ -233,76 +234,123 @@ level_plan_kernel(const dwt2_image* imgs, int count, int levels, int core_cols, 
             carry += t[0];
         }
         if (tid == 0) row[count] = carry;
-    }
-    uint64_t carry64 = 0;
-    for (int b = 0; b < count; b += kPlanThreads) {
-        const int i = b + tid;
-        uint64_t v[1] = {i < count ? (uint64_t)pingpong_ll_bytes(imgs[i].height, imgs[i].width, levels, (size_t)es)
-                                   : 0ull};
-        uint64_t t[1];
-        block_scan<1>(v, t, sh64);
-        if (i < count) ll_off[i] = carry64 + v[0];
-        carry64 += t[0];
+    } else {
+        __shared__ uint64_t sh64[1][kPlanThreads / kLanes];
+        uint64_t* ll_off = reinterpret_cast<uint64_t*>(ws + L.off_ll_off);
+        uint64_t carry = 0;
+        for (int b = 0; b < count; b += kPlanThreads) {
+            const int i = b + tid;
+            uint64_t v[1] = {i < count ? (uint64_t)pingpong_ll_bytes(imgs[i].height, imgs[i].width, levels, (size_t)es)
+                                       : 0ull};
+            uint64_t t[1];
+            block_scan<1>(v, t, sh64);
+            if (i < count) ll_off[i] = carry + v[0];
+            carry += t[0];
+        }
     }
 }
 
-// Level l of every image.  The grid is a multiple of 8 chunks of
-// kLevelChunk tiles; work-groups are dealt round-robin over the 8 XCDs, so
-// each XCD is given runs of kLevelChunk consecutive tiles of the level
-// (row-major within an image, images in order) and the halo re-reads of
-// neighbouring tiles hit its L2.  Levels are ordered by the kernel
-// boundaries of the stream: no work-group waits for another.
+// The tile of this work-group in launch j (grid: a multiple of 8 chunks of
+// kLevelChunk tiles): its image and its index within the image.  Work-groups are
+// dealt round-robin over the 8 XCDs, so XCD x takes chunks x, x + 8, ... of
+// consecutive tiles (row-major within an image, images in order) and the halo
+// re-reads of neighbouring tiles hit its L2.  False past the last tile (uniform
+// over the work-group).
+__device__ __forceinline__ bool batched_tile(const unsigned char* ws, const LevelBatchLayout& L, int count, int j,
+                                             int* image, int* index) {
+    const uint32_t* off = reinterpret_cast<const uint32_t*>(ws + L.off_tile) + (size_t)j * (count + 1);
+    const uint32_t b = blockIdx.x >> 3;
+    const uint32_t t = ((b / kLevelChunk) * 8 + (blockIdx.x & 7)) * kLevelChunk + b % kLevelChunk;
+    if (t >= off[count]) return false;
+    // off[] is strictly increasing (every image has a tile)
+    *image = last_at_most(off, count, t);
+    *index = (int)(t - off[*image]);
+    return true;
+}
 
+// Input of launch j (level l of an image) and its LL output.
+struct BatchedBuffers {
+    const void* in;
+    int64_t in_pitch;
+    void* ll;
+    int64_t ll_pitch;
+};
+__device__ __forceinline__ BatchedBuffers batched_buffers(const dwt2_image& im, unsigned char* bufA, int levels, int j,
+                                                          bool last, int32_t wl, int32_t w_ll, size_t es) {
+    unsigned char* bufB = bufA + pingpong_b_offset(im.height, im.width, levels, es);
+    BatchedBuffers b;
+    b.in = j == 0 ? im.src : (const void*)(j % 2 == 1 ? bufA : bufB);
+    b.in_pitch = j == 0 ? im.src_pitch : ll_pitch(wl);
+    b.ll = last ? im.dst : (void*)(j % 2 == 0 ? bufA : bufB);
+    b.ll_pitch = last ? im.dst_pitch : ll_pitch(w_ll);
+    return b;
+}
+
+// Launch j: level l of every image.  Launches are ordered by the kernel
+// boundaries of the stream: no work-group waits for another.
 template <typename T, int SCH, int NW, int K, int BPL>
 __global__ void __launch_bounds__(NW * kLanes)
-batched_level_kernel(const dwt2_image* imgs, int count, int levels, int l, unsigned char* ws) {
+batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, unsigned char* ws) {
     using V = typename St<T>::V;
     constexpr int kCoreBY = NW * K - 2 * kHalo;
-    constexpr size_t es = sizeof(T);
     __shared__ TileLds<V, NW, BPL, K> lds;
     const int lane = threadIdx.x & (kLanes - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const LevelBatchLayout L = level_batch_layout(count, levels);
-    const uint32_t* off = reinterpret_cast<const uint32_t*>(ws + L.off_tile) + (size_t)l * (count + 1);
-    const uint64_t* ll_off = reinterpret_cast<const uint64_t*>(ws + L.off_ll_off);
-    unsigned char* ll_area = ws + L.off_ll;
-
-    // XCD x takes chunks x, x + 8, ... of kLevelChunk consecutive tiles
-    const uint32_t j = blockIdx.x >> 3;
-    const uint32_t t = ((j / kLevelChunk) * 8 + (blockIdx.x & 7)) * kLevelChunk + j % kLevelChunk;
-    if (t >= off[count]) return;                  // uniform over the work-group
-    // image of tile t: off[] is strictly increasing (every image has a tile)
-    const int i = last_at_most(off, count, t);
-    const int tt = (int)(t - off[i]);
+    int i, tt;
+    if (!batched_tile(ws, L, count, j, &i, &tt)) return;
     const dwt2_image im = imgs[i];
-
     LevelParams P{};
     int32_t hl, wl;
     level_size(im.height, im.width, l, &hl, &wl);
     P.h = hl;
     P.w = wl;
     level_tiles(hl, wl, Lay<BPL>::CORE_BX, kCoreBY, &P.tiles_x, &P.tiles_y);
-    unsigned char* bufA = ll_area + ll_off[i];
-    unsigned char* bufB = bufA + pingpong_b_offset(im.height, im.width, levels, es);
-    if (l == 0) {
-        P.in = im.src;
-        P.in_pitch = im.src_pitch;
-    } else {
-        P.in = (l - 1) % 2 == 0 ? (const void*)bufA : (const void*)bufB;
-        P.in_pitch = ll_pitch(wl);
-    }
+    const BatchedBuffers b = batched_buffers(im, ws + L.off_ll + reinterpret_cast<const uint64_t*>(ws + L.off_ll_off)[i],
+                                             levels, j, l + 1 == levels, wl, (wl + 1) / 2, sizeof(T));
+    P.in = b.in;
+    P.in_pitch = b.in_pitch;
     P.out = im.dst;
     P.out_pitch = im.dst_pitch;
-    if (l + 1 == levels) {
-        P.out_ll = im.dst;
-        P.out_ll_pitch = im.dst_pitch;
-    } else {
-        P.out_ll = l % 2 == 0 ? (void*)bufA : (void*)bufB;
-        P.out_ll_pitch = ll_pitch((wl + 1) / 2);
-    }
+    P.out_ll = b.ll;
+    P.out_ll_pitch = b.ll_pitch;
     const int ty = tt / P.tiles_x;
     const int tx = tt - ty * P.tiles_x;
     tile_body<kForward, kCdf97, T, SCH, NW, K, BPL>(P, tx, ty, lds, lane, wv);
+}
+
+// Launch j: levels l and l + 1 of every image.  60 uneven images of 64 ... 2048
+// pixels a side, FP32, 5 levels: 203 us a call in 3 launches, 240 in 5; 16 of
+// 64 ... 300: 31.5 us (88 with the earlier border tiles); 1024 of 256^2: 194.
+template <typename T, int SCH, int NW, int K>
+__global__ void __launch_bounds__(NW * kLanes)
+batched_pair_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, unsigned char* ws) {
+    using V = typename St<T>::V;
+    __shared__ pair::PairLds<V, NW> lds;
+    __shared__ pair::PairPlane<V, NW * K> plane;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    const LevelBatchLayout L = level_batch_layout(count, levels);
+    int i, tt;
+    if (!batched_tile(ws, L, count, j, &i, &tt)) return;
+    const dwt2_image im = imgs[i];
+    PairParams P{};
+    int32_t hl, wl;
+    level_size(im.height, im.width, l, &hl, &wl);
+    P.h = hl;
+    P.w = wl;
+    pair_tile_grid(hl, wl, NW * K, &P.tiles_x, &P.tiles_y);
+    const BatchedBuffers b = batched_buffers(im, ws + L.off_ll + reinterpret_cast<const uint64_t*>(ws + L.off_ll_off)[i],
+                                             levels, j, l + 2 == levels, wl, ((wl + 1) / 2 + 1) / 2, sizeof(T));
+    P.in = b.in;
+    P.in_pitch = b.in_pitch;
+    P.out = im.dst;
+    P.out_pitch = im.dst_pitch;
+    P.ll = b.ll;
+    P.ll_pitch = b.ll_pitch;
+    const int ty = tt / P.tiles_x;
+    const int tx = tt - ty * P.tiles_x;
+    pair::tile<kForward, kCdf97, T, SCH, NW, K>(P, tx, ty, lds, plane, lane, wv);
 }
 
 // ---- one persistent launch -------------------------------------------------
@@ -515,19 +563,30 @@ hipError_t launch_persist_shape(const ImageSet& S, int count, int levels, void* 
 }
 
 template <typename T, int SCH, int NW, int K, int BPL>
-hipError_t launch_levels_shape(const dwt2_image* dev_imgs, int count, int levels, void* ws,
-                               const uint32_t* tiles_per_level, hipStream_t s) {
+hipError_t launch_levels_shape(const BatchLaunches& B, const dwt2_image* dev_imgs, int count, int levels, void* ws,
+                               const uint32_t* tiles, hipStream_t s) {
     constexpr int kCoreBY = NW * K - 2 * kHalo;
+    constexpr int kPairScheme = sizeof(T) == 4 ? kSchemeFused : kSchemeFactored;   // the default of the storage type
     unsigned char* w = static_cast<unsigned char*>(ws);
-    hipLaunchKernelGGL(level_plan_kernel, dim3(1), dim3(kPlanThreads), 0, s, dev_imgs, count, levels,
+    hipLaunchKernelGGL(level_plan_kernel, dim3(B.n + 1), dim3(kPlanThreads), 0, s, dev_imgs, count, levels, B,
                        Lay<BPL>::CORE_BX, kCoreBY, (int)sizeof(T), w);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    for (int l = 0; l < levels; ++l) {
-        const uint32_t chunks = (tiles_per_level[l] + kLevelChunk - 1) / kLevelChunk;
-        const uint32_t grid = (chunks + 7u) / 8u * 8u * kLevelChunk;
-        hipLaunchKernelGGL((batched_level_kernel<T, SCH, NW, K, BPL>), dim3(grid), dim3(NW * kLanes), 0, s,
-                           dev_imgs, count, levels, l, w);
+    for (int j = 0; j < B.n; ++j) {
+        const uint32_t chunks = (tiles[j] + kLevelChunk - 1) / kLevelChunk;
+        const dim3 grid((chunks + 7u) / 8u * 8u * kLevelChunk);
+        const int l = B.first[j];
+        if (B.pair_rows[j] == 0)
+            hipLaunchKernelGGL((batched_level_kernel<T, SCH, NW, K, BPL>), grid, dim3(NW * kLanes), 0, s, dev_imgs,
+                               count, levels, j, l, w);
+        else if constexpr (SCH != kPairScheme)
+            return hipErrorInvalidValue;
+        else if (B.pair_rows[j] == 32)
+            hipLaunchKernelGGL((batched_pair_kernel<T, kPairScheme, 8, 4>), grid, dim3(8 * kLanes), 0, s, dev_imgs,
+                               count, levels, j, l, w);
+        else
+            hipLaunchKernelGGL((batched_pair_kernel<T, kPairScheme, 8, 6>), grid, dim3(8 * kLanes), 0, s, dev_imgs,
+                               count, levels, j, l, w);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -535,14 +594,14 @@ hipError_t launch_levels_shape(const dwt2_image* dev_imgs, int count, int levels
 }
 
 template <typename T, int SCH>
-hipError_t launch_levels_cfg(int cfg, const dwt2_image* d, int count, int levels, void* ws, const uint32_t* tpl,
-                             hipStream_t s) {
+hipError_t launch_levels_cfg(int cfg, const BatchLaunches& B, const dwt2_image* d, int count, int levels, void* ws,
+                             const uint32_t* tiles, hipStream_t s) {
     static_assert(kNumConfigs == 10, "dispatch table below lists every kernel configuration");
 #define DWT2_LCFG(i)                                                                                 \
     case i:                                                                                          \
         if constexpr (kConfigs[i].algo == kAlgoTile)                                                 \
             return launch_levels_shape<T, SCH, kConfigs[i].waves, kConfigs[i].rows, kConfigs[i].bpl>( \
-                d, count, levels, ws, tpl, s);                                                       \
+                B, d, count, levels, ws, tiles, s);                                                       \
         else                                                                                         \
             return hipErrorInvalidValue;
     switch (cfg) {
@@ -554,12 +613,12 @@ hipError_t launch_levels_cfg(int cfg, const dwt2_image* d, int count, int levels
 }
 
 template <typename T>
-hipError_t launch_levels_t(Scheme sch, int cfg, const dwt2_image* d, int count, int levels, void* ws,
-                           const uint32_t* tpl, hipStream_t s) {
+hipError_t launch_levels_t(Scheme sch, int cfg, const BatchLaunches& B, const dwt2_image* d, int count, int levels,
+                           void* ws, const uint32_t* tiles, hipStream_t s) {
     switch (sch) {
-        case kSchemeFused: return launch_levels_cfg<T, kSchemeFused>(cfg, d, count, levels, ws, tpl, s);
-        case kSchemeSplit: return launch_levels_cfg<T, kSchemeSplit>(cfg, d, count, levels, ws, tpl, s);
-        case kSchemeFactored: return launch_levels_cfg<T, kSchemeFactored>(cfg, d, count, levels, ws, tpl, s);
+        case kSchemeFused: return launch_levels_cfg<T, kSchemeFused>(cfg, B, d, count, levels, ws, tiles, s);
+        case kSchemeSplit: return launch_levels_cfg<T, kSchemeSplit>(cfg, B, d, count, levels, ws, tiles, s);
+        case kSchemeFactored: return launch_levels_cfg<T, kSchemeFactored>(cfg, B, d, count, levels, ws, tiles, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -600,13 +659,13 @@ hipError_t launch_persist_t(Scheme sch, int cfg, const ImageSet& S, int count, i
 
 bool persist_config_supported(int cfg) { return cfg >= 0 && cfg < kNumConfigs && kConfigs[cfg].algo == kAlgoTile; }
 
-hipError_t launch_fwd_batched_levels(Dtype dt, Scheme sch, int cfg, const dwt2_image* dev_imgs, int count,
-                                     int levels, void* ws, const uint32_t* tiles_per_level, hipStream_t s) {
+hipError_t launch_fwd_batched_levels(Dtype dt, Scheme sch, int cfg, const BatchLaunches& B,
+                                     const dwt2_image* dev_imgs, int count, int levels, void* ws,
+                                     const uint32_t* tiles, hipStream_t s) {
     switch (dt) {
-        case kF32: return kern::launch_levels_t<float>(sch, cfg, dev_imgs, count, levels, ws, tiles_per_level, s);
-        case kBF16:
-            return kern::launch_levels_t<__hip_bfloat16>(sch, cfg, dev_imgs, count, levels, ws, tiles_per_level, s);
-        case kF16: return kern::launch_levels_t<__half>(sch, cfg, dev_imgs, count, levels, ws, tiles_per_level, s);
+        case kF32: return kern::launch_levels_t<float>(sch, cfg, B, dev_imgs, count, levels, ws, tiles, s);
+        case kBF16: return kern::launch_levels_t<__hip_bfloat16>(sch, cfg, B, dev_imgs, count, levels, ws, tiles, s);
+        case kF16: return kern::launch_levels_t<__half>(sch, cfg, B, dev_imgs, count, levels, ws, tiles, s);
         default: return hipErrorInvalidValue;
     }
 }

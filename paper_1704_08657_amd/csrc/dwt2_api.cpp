@@ -373,8 +373,8 @@ void add_pair_stats(int32_t h, int32_t w, int levels, BatchPairStats* st) {
     }
 }
 bool batch_pair_pays(int dtype, const BatchPairStats& st) {
-    if (st.tiles32 <= 512) return true;
-    if (st.tiles48 > 0x7fff0000ull) return false;
+    if (st.tiles32 <= 640) return true;
+    if (st.tiles32 > 0x7fff0000ull) return false;
     if (2 * st.cols112 >= 3 * st.cols128) return false;
     return !(dtype != DWT2_F32 && st.samples > (1 << 26));
 }
@@ -765,8 +765,11 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
     for (int l = 0; l < levels; ++B.n) {
         const bool two = pairs && l + 1 < levels && batch_pair_pays(dtype, stats[l]);
         B.first[B.n] = (int8_t)l;
-        B.pair_rows[B.n] = (int8_t)(!two ? 0 : stats[l].tiles32 <= 512 ? 32 : 48);
-        launch_tiles[B.n] = (uint32_t)(!two ? tiles[l] : stats[l].tiles32 <= 512 ? stats[l].tiles32 : stats[l].tiles48);
+        const int rows = !two ? 0
+                              : dwt2::pair_rows(dwt2::kForward, es, (int64_t)stats[l].tiles32, (int64_t)stats[l].tiles48,
+                                                (int64_t)stats[l].samples);
+        B.pair_rows[B.n] = (int8_t)rows;
+        launch_tiles[B.n] = (uint32_t)(rows == 0 ? tiles[l] : rows == 32 ? stats[l].tiles32 : stats[l].tiles48);
         l += two ? 2 : 1;
     }
     return report(dwt2::launch_fwd_batched_levels(to_dtype(dtype), sch, cfg, B, device_images, count, levels,

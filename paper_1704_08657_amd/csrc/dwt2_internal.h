@@ -130,19 +130,36 @@ inline int64_t pair_tiles(int32_t h, int32_t w, int32_t planes, int rows) {
     const int cy = rows - 2 * kHalo2;
     return (int64_t)(((w + 1) / 2 + kPairCols - 1) / kPairCols) * (((h + 1) / 2 + cy - 1) / cy) * planes;
 }
+// Tile shape, in block rows of a tile (32: 8 waves x 4 rows, 48: 8 x 6).  Few tiles, all on the chip at once (up to 2.5 work-groups of 8
+// waves on each of 256 CUs): the shape that takes the least time from load to
+// store, 8 waves x 4 rows (1024^2 FP32 forward 7.3 us, 8 x 6: 9.2).  Beyond,
+// 8 x 6 recomputes 12 of 48 rows instead of 12 of 32, which counts where the
+// vector units are the limit: 16-bit storage (3 x 8192^2 FP16 inverse 179 us,
+// 8 x 4: 200) and one round of tiles (3 x 1081 x 1921 FP32 forward 13.2, 14.5);
+// 8 x 4 has 60 registers to 82 and more work-groups on a CU, which counts where
+// memory is: 4-byte samples forward (8192^2 106 us, 8 x 6: 115; 4096^2 28.3,
+// 29.1) and, inverse, from 2^25 samples (8192^2 103, 108; but 4096^2 27.3, 25.6).
+// The adjoint has two step programs (border weights) and keeps 8 x 4, where
+// both fit the registers (8192^2: 124 us, 8 x 6 161).
+inline int pair_rows(Direction dir, size_t es, int64_t tiles32, int64_t tiles48, int64_t samples) {
+    if (dir == kAdjoint || tiles32 <= 640) return 32;
+    if (es == 2) return 48;
+    if (dir == kForward) return tiles48 <= 512 ? 48 : 32;
+    return samples >= (1 << 25) ? 32 : 48;
+}
 // Whether two levels in one launch beat one launch each (both sides measured
 // on MI355X, us; two launches first):
 //   * a level whose tiles all run at once: always (1024^2 FP32 11.7 / 7.2,
 //     inverse 11.6 / 8.0; 192 planes of 64^2 16.0 / 9.6);
 //   * larger ones, when 112 columns a tile do not cost half as many tiles
-//     again as the one-level kernel's 128 (8192^2 FP32 121 / 109, inverse
-//     127 / 103; 3469 x 5197 41 / 34; but 192 planes of 256^2, two tiles for
-//     one: 31.4 / 33.4, adjoint 40 / 55);
+//     again as the one-level kernel's 128 (8192^2 FP32 121 / 106, inverse
+//     127 / 103; 3469 x 5197 41 / 33; but 192 planes of 256^2, two tiles for
+//     one: 31.4 / 34, adjoint 40 / 55);
 //   * 16-bit storage, forward, up to 2^26 samples: beyond, the recomputed
 //     halo costs what the LL band saves (3 x 8192^2 BF16 188 / 193,
 //     3 x 4096^2 56 / 53, inverse 198 / 176).
 inline bool pair_pays(Direction dir, Dtype dt, int32_t h, int32_t w, int32_t planes) {
-    if (pair_tiles(h, w, planes, 32) <= 512) return true;
+    if (pair_tiles(h, w, planes, 32) <= 640) return true;
     const int32_t nc = (w + 1) / 2;
     if (2 * ((nc + kPairCols - 1) / kPairCols) >= 3 * ((nc + 2 * kLanes - 1) / (2 * kLanes))) return false;
     return !(dir == kForward && (dt == kBF16 || dt == kF16) && (int64_t)h * w * planes > (1 << 26));

@@ -1038,6 +1038,13 @@ __device__ __forceinline__ Q* lane_at(Q* row, uint32_t off) {
     else return reinterpret_cast<Q*>(reinterpret_cast<char*>(row) + off);
 }
 
+// One sample of a uniform row, at a column c >= 0 of the lane's own (a row is at
+// most 2^30 samples, so its bytes fit the 32-bit offset).
+template <typename T>
+__device__ __forceinline__ typename St<T>::V load_at(const T* row, int c) {
+    return St<T>::load(*lane_at(row, (uint32_t)c * (uint32_t)sizeof(T)));
+}
+
 // Row `row` of subband k (0 LL, 1 HL, 2 LH, 3 HH) of a pyramid level.
 template <typename Q>
 __device__ __forceinline__ Q* subband_row(Q* ll, int64_t ll_pitch, Q* det, int64_t pitch, const Geo& g, int k,
@@ -1165,7 +1172,7 @@ __device__ __forceinline__ void load_tile_border(typename St<T>::V (&a)[K][Lay<B
 #pragma unroll
                 for (int s = 0; s < 2 * BPL; ++s)
                     a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)] =
-                        St<T>::load((in + (int64_t)rows[i] * P.in_pitch)[cols[s]]);
+                        load_at(in + (int64_t)rows[i] * P.in_pitch, cols[s]);
         }
         if (halo_lane) {
 #pragma unroll
@@ -1209,7 +1216,7 @@ __device__ __forceinline__ void load_tile_border(typename St<T>::V (&a)[K][Lay<B
                     for (int b = 0; b < BPL; ++b) {
                         const int c = cols[2 * b + (k & 1)];
                         V v = V(0);
-                        if (!kZero || (row_ok && c < P.w)) v = St<T>::load(row[c >> 1]);
+                        if (!kZero || (row_ok && c < P.w)) v = load_at(row, c >> 1);
                         a[r][4 * b + k] = v;
                     }
                 }

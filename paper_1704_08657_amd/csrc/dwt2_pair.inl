@@ -212,7 +212,7 @@ __device__ __forceinline__ void load_image(typename St<T>::V (&a)[K][4 * BPL], c
         for (int i = 0; i < 2 * K; ++i)
 #pragma unroll
             for (int s = 0; s < 2 * BPL; ++s)
-                a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)] = St<T>::load((in + (int64_t)rows[i] * pitch)[cols[s]]);
+                a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)] = load_at(in + (int64_t)rows[i] * pitch, cols[s]);
     }
 }
 
@@ -272,20 +272,23 @@ __device__ __forceinline__ void load_bands(typename St<T>::V (&a)[K][4 * BPL], c
                 for (int b = 0; b < BPL; ++b) {
                     const int c = cols[2 * b + (k & 1)];
                     V v = V(0);
-                    if (!ZERO || (ok && c >= 0 && c < w)) v = St<T>::load(row[c >> 1]);
+                    if (!ZERO || (ok && c >= 0 && c < w)) v = load_at(row, c >> 1);
                     a[r][4 * b + k] = v;
                 }
             }
     }
 }
 
-// Bands K0 .. 3 of the tile's core to a pyramid level (forward).  H: halo
+// Bands K0 .. 3 of the tile's core to a pyramid level (forward).  One body for
+// interior and border tiles: with a body each, the compiler gathered the
+// samples of every store ahead of the choice (33 more registers at K = 6, two
+// work-groups on a CU instead of three).  H: halo
 // rows of the tile at this level (NW * K rows).
-template <typename T, bool BORDER, int K0, int H, int NW, int BPL, int K>
+template <typename T, int K0, int H, int NW, int BPL, int K>
 __device__ __forceinline__ void store_bands(typename St<T>::V (&a)[K][4 * BPL], T* ll, int64_t ll_pitch, T* det,
                                             int64_t pitch, const Geo& g, int lane, int wv) {
     using V = typename St<T>::V;
-    constexpr bool kBySubband = !BORDER && sizeof(T) == 4;
+    constexpr bool kBySubband = sizeof(T) == 4;
     T* row[4];
 #pragma unroll
     for (int k = K0; k < 4; ++k) row[k] = subband_row(ll, ll_pitch, det, pitch, g, k, g.gr0) + g.cb0;
@@ -299,12 +302,12 @@ __device__ __forceinline__ void store_bands(typename St<T>::V (&a)[K][4 * BPL], 
                 row[k] += k == 0 ? ll_pitch : pitch;
                 const int tr = wv * K + r;
                 if (tr < H || tr >= NW * K - H) continue;
-                if (BORDER && g.gr0 + r >= (k >= 2 ? g.nOr : g.nEr)) continue;
+                if (g.gr0 + r >= (k >= 2 ? g.nOr : g.nEr)) continue;
                 V v[BPL];
 #pragma unroll
                 for (int b = 0; b < BPL; ++b) v[b] = a[r][4 * b + k];
-                const int left = BORDER ? ((k & 1) ? g.nOc : g.nEc) - g.gcL : BPL;   // samples to the row's end
-                if (!BORDER || left >= BPL) {
+                const int left = ((k & 1) ? g.nOc : g.nEc) - g.gcL;   // samples to the row's end
+                if (left >= BPL) {
                     store_band_row<T, BPL>(p, v);
                 } else {
 #pragma unroll
@@ -374,10 +377,7 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
         load_image<T, 2, K>(a, static_cast<const T*>(P.in), P.in_pitch, P.h, P.w, g, interior, lane);
         steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
         T* const out = static_cast<T*>(P.out);
-        if (core_lane) {
-            if (interior) store_bands<T, false, 1, kHalo2, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
-            else store_bands<T, true, 1, kHalo2, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
-        }
+        if (core_lane) store_bands<T, 1, kHalo2, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
 #pragma unroll
         for (int r = 0; r < K2; ++r)
 #pragma unroll
@@ -403,10 +403,7 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
         }
         steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
         T* const ll = static_cast<T*>(P.ll);
-        if (core_lane) {
-            if (interior) store_bands<T, false, 0, kHalo2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
-            else store_bands<T, true, 0, kHalo2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
-        }
+        if (core_lane) store_bands<T, 0, kHalo2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
     } else {
         constexpr bool kZero = DIR == kAdjoint;
         const T* const det = static_cast<const T*>(P.in);
@@ -520,27 +517,14 @@ hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
     return hipSuccess;
 }
 
-// Tile shape.  Few tiles, all on the chip at once (two work-groups of 8 waves
-// on each of 256 CUs): the shape that takes the least time from load to store,
-// 8 waves x 4 rows (1024^2 FP32 forward 7.2 us, 8 x 6: 9.1, 4 x 8: 8.5).
-// Otherwise 8 x 6, which recomputes 12 of 48 rows instead of 12 of 32 (3 x 1081
-// x 1921: 13.3 us, 16.0, 16.9; inverse 3 x 8192^2 FP16: 176, 194, 180).  Beyond
-// 2^25 4-byte samples the memory system is the limit, and smaller work-groups
-// overlap their loads, steps and stores better: forward 4 x 8, inverse 8 x 4
-// (8192^2 FP32: 109 us, 8 x 6 114; 103, 109).  The adjoint has two step
-// programs (border weights) and keeps 8 x 4, where both fit the registers
-// (8192^2: 124 us, 8 x 6 161).
 template <int DIR, int WAV, typename T, int SCH>
 hipError_t launch(const PairParams& p, int planes, hipStream_t s) {
-    if constexpr (DIR == kAdjoint) {
-        return launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
-    } else {
-        if (pair_tiles(p.h, p.w, planes, 8 * 4) <= 512) return launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
-        if (sizeof(T) == 4 && (int64_t)p.h * p.w * planes >= (1 << 25))
-            return DIR == kForward ? launch_shape<DIR, WAV, T, SCH, 4, 8>(p, planes, s)
-                                   : launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
-        return launch_shape<DIR, WAV, T, SCH, 8, 6>(p, planes, s);
+    if constexpr (DIR != kAdjoint) {
+        if (pair_rows((Direction)DIR, sizeof(T), pair_tiles(p.h, p.w, planes, 32), pair_tiles(p.h, p.w, planes, 48),
+                      (int64_t)p.h * p.w * planes) == 48)
+            return launch_shape<DIR, WAV, T, SCH, 8, 6>(p, planes, s);
     }
+    return launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
 }
 
 // The default schemes: fused steps for 4-byte samples and for the adjoint,

@@ -233,7 +233,7 @@ __device__ __forceinline__ void load(float (&a)[K][4 * BPL], const LevelParams& 
 #pragma unroll
                 for (int s = 0; s < 2 * BPL; ++s)
                     a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)] =
-                        St<T>::load((in + (int64_t)rows[i] * P.in_pitch)[cols[s]]);
+                        load_at(in + (int64_t)rows[i] * P.in_pitch, cols[s]);
         }
     } else {
         const T* ll = static_cast<const T*>(P.in_ll);
@@ -258,7 +258,7 @@ __device__ __forceinline__ void load(float (&a)[K][4 * BPL], const LevelParams& 
                 for (int k = 0; k < 4; ++k) {
                     const T* row = subband_row(ll, P.in_ll_pitch, det, P.in_pitch, g, k, rows[2 * r + (k >> 1)] >> 1);
 #pragma unroll
-                    for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = St<T>::load(row[cols[2 * b + (k & 1)] >> 1]);
+                    for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = load_at(row, cols[2 * b + (k & 1)] >> 1);
                 }
         }
 #pragma unroll

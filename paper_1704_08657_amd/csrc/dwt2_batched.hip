@@ -250,25 +250,41 @@ level_plan_kernel(const dwt2_image* imgs, int count, int levels, BatchLaunches B
     }
 }
 
-// The tile of this work-group in launch j (grid: a multiple of 8 chunks of
-// kLevelChunk tiles): its image and its index within the image.  Work-groups are
-// dealt round-robin over the 8 XCDs, so XCD x takes chunks x, x + 8, ... of
-// consecutive tiles (row-major within an image, images in order) and the halo
-// re-reads of neighbouring tiles hit its L2.  False past the last tile (uniform
-// over the work-group).
+// The tile of this work-group in launch j of `total` tiles (grid: a multiple of
+// 8 chunks of kLevelChunk tiles): its image and its index within the image.
+// Work-groups are dealt round-robin over the 8 XCDs, so XCD x takes chunks x,
+// x + 8, ... of consecutive tiles (row-major within an image, images in order)
+// and the halo re-reads of neighbouring tiles hit its L2.  False past the last
+// tile (uniform over the work-group).
+// Every work-group waits for this before its first load, so the memory round
+// trips count: the total comes with the launch, and up to 64 images one read
+// (a lane each) finds both the image and its first tile.
 __device__ __forceinline__ bool batched_tile(const unsigned char* ws, const LevelBatchLayout& L, int count, int j,
-                                             int* image, int* index) {
-    const uint32_t* off = reinterpret_cast<const uint32_t*>(ws + L.off_tile) + (size_t)j * (count + 1);
+                                             uint32_t total, int* image, int* index) {
     const uint32_t b = blockIdx.x >> 3;
     const uint32_t t = ((b / kLevelChunk) * 8 + (blockIdx.x & 7)) * kLevelChunk + b % kLevelChunk;
-    if (t >= off[count]) return false;
+    if (t >= total) return false;
     // off[] is strictly increasing (every image has a tile)
-    *image = last_at_most(off, count, t);
-    *index = (int)(t - off[*image]);
+    const uint32_t* off = reinterpret_cast<const uint32_t*>(ws + L.off_tile) + (size_t)j * (count + 1);
+    int i;
+    uint32_t first;
+    if (count <= kLanes) {
+        const int lane = threadIdx.x & (kLanes - 1);
+        const uint32_t v = off[lane < count ? lane : count - 1];
+        i = 63 - __builtin_clzll(__ballot(lane < count && v <= t));
+        first = (uint32_t)__builtin_amdgcn_readlane((int)v, i);
+    } else {
+        i = last_at_most(off, count, t);
+        first = off[i];
+    }
+    // uniform: keep it, and everything derived from it, in SGPRs
+    *image = __builtin_amdgcn_readfirstlane(i);
+    *index = __builtin_amdgcn_readfirstlane((int)(t - first));
     return true;
 }
 
-// Input of launch j (level l of an image) and its LL output.
+// Input of launch j (level l of an image) and its LL output.  bufA: the image's
+// first LL buffer; the second is needed from the second launch on.
 struct BatchedBuffers {
     const void* in;
     int64_t in_pitch;
@@ -277,12 +293,17 @@ struct BatchedBuffers {
 };
 __device__ __forceinline__ BatchedBuffers batched_buffers(const dwt2_image& im, unsigned char* bufA, int levels, int j,
                                                           bool last, int32_t wl, int32_t w_ll, size_t es) {
-    unsigned char* bufB = bufA + pingpong_b_offset(im.height, im.width, levels, es);
     BatchedBuffers b;
-    b.in = j == 0 ? im.src : (const void*)(j % 2 == 1 ? bufA : bufB);
-    b.in_pitch = j == 0 ? im.src_pitch : ll_pitch(wl);
-    b.ll = last ? im.dst : (void*)(j % 2 == 0 ? bufA : bufB);
+    b.ll = last ? im.dst : (void*)bufA;
     b.ll_pitch = last ? im.dst_pitch : ll_pitch(w_ll);
+    b.in = im.src;
+    b.in_pitch = im.src_pitch;
+    if (j > 0) {
+        unsigned char* bufB = bufA + pingpong_b_offset(im.height, im.width, levels, es);
+        b.in = j % 2 == 1 ? bufA : bufB;
+        b.in_pitch = ll_pitch(wl);
+        if (!last && j % 2 == 1) b.ll = bufB;
+    }
     return b;
 }
 
@@ -290,7 +311,7 @@ __device__ __forceinline__ BatchedBuffers batched_buffers(const dwt2_image& im, 
 // boundaries of the stream: no work-group waits for another.
 template <typename T, int SCH, int NW, int K, int BPL>
 __global__ void __launch_bounds__(NW * kLanes)
-batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, unsigned char* ws) {
+batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, unsigned char* ws) {
     using V = typename St<T>::V;
     constexpr int kCoreBY = NW * K - 2 * kHalo;
     __shared__ TileLds<V, NW, BPL, K> lds;
@@ -298,7 +319,7 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const LevelBatchLayout L = level_batch_layout(count, levels);
     int i, tt;
-    if (!batched_tile(ws, L, count, j, &i, &tt)) return;
+    if (!batched_tile(ws, L, count, j, total, &i, &tt)) return;
     const dwt2_image im = imgs[i];
     LevelParams P{};
     int32_t hl, wl;
@@ -324,7 +345,7 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
 // 64 ... 300: 31.5 us (88 with the earlier border tiles); 1024 of 256^2: 194.
 template <typename T, int SCH, int NW, int K>
 __global__ void __launch_bounds__(NW * kLanes)
-batched_pair_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, unsigned char* ws) {
+batched_pair_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, unsigned char* ws) {
     using V = typename St<T>::V;
     __shared__ pair::PairLds<V, NW> lds;
     __shared__ pair::PairPlane<V, NW * K> plane;
@@ -332,7 +353,7 @@ batched_pair_kernel(const dwt2_image* imgs, int count, int levels, int j, int l,
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const LevelBatchLayout L = level_batch_layout(count, levels);
     int i, tt;
-    if (!batched_tile(ws, L, count, j, &i, &tt)) return;
+    if (!batched_tile(ws, L, count, j, total, &i, &tt)) return;
     const dwt2_image im = imgs[i];
     PairParams P{};
     int32_t hl, wl;
@@ -578,15 +599,15 @@ hipError_t launch_levels_shape(const BatchLaunches& B, const dwt2_image* dev_img
         const int l = B.first[j];
         if (B.pair_rows[j] == 0)
             hipLaunchKernelGGL((batched_level_kernel<T, SCH, NW, K, BPL>), grid, dim3(NW * kLanes), 0, s, dev_imgs,
-                               count, levels, j, l, w);
+                               count, levels, j, l, tiles[j], w);
         else if constexpr (SCH != kPairScheme)
             return hipErrorInvalidValue;
         else if (B.pair_rows[j] == 32)
             hipLaunchKernelGGL((batched_pair_kernel<T, kPairScheme, 8, 4>), grid, dim3(8 * kLanes), 0, s, dev_imgs,
-                               count, levels, j, l, w);
+                               count, levels, j, l, tiles[j], w);
         else
             hipLaunchKernelGGL((batched_pair_kernel<T, kPairScheme, 8, 6>), grid, dim3(8 * kLanes), 0, s, dev_imgs,
-                               count, levels, j, l, w);
+                               count, levels, j, l, tiles[j], w);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

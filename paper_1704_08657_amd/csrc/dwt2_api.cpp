@@ -329,41 +329,47 @@ int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, i
     return DWT2_OK;
 }
 
-// Forward: level l reads the LL of level l-1 (src for l = 0) and writes its
-// details into dst at the level's region origin (dst itself: every level's
-// region starts at (0, 0)), its LL into the workspace or, for the last level,
-// into dst.
 // Whether a level stores the output the next level of the call reads with
-// ordinary stores (LevelParams::ll_cached): measured on MI355X, it pays for
-// outputs of 32 MiB and more (an 8192^2 FP32 level's LL band: +4% on two
-// levels, forward and inverse) and costs 2% on smaller ones (4096^2, whose
-// LL band the nontemporal path leaves in the Infinity Cache anyway).
-bool cached_output(int32_t planes, int32_t h, int32_t w, size_t es) {
-    return (uint64_t)planes * (uint64_t)h * (uint64_t)w * es >= ((uint64_t)32 << 20);
+// ordinary stores (LevelParams::ll_cached).  It pays from 32 MiB (5 inverse
+// levels of 8192^2 FP32: 147.6 us, 151.3 without; smaller outputs stay in the
+// Infinity Cache either way) to 128 MiB (16384^2, 2 levels inverse, 256 MiB: 489
+// us, 478 without).  A forward LL band of 4-byte samples does not gain
+// (5 levels of 8192^2 154.3 with, 151.5 without; 3 planes, 3 levels, 379 and
+// 359), one of 16-bit samples does (3 x 8192^2 BF16, 5 levels, 202 and 208).
+bool cached_output(dwt2::Direction dir, int32_t planes, int32_t h, int32_t w, size_t es) {
+    const uint64_t n = (uint64_t)planes * (uint64_t)h * (uint64_t)w * es;
+    return (dir != dwt2::kForward || es == 2) && n >= ((uint64_t)32 << 20) && n <= ((uint64_t)128 << 20);
 }
 
-// Levels the launch that starts at level l takes: two of a call that names no
-// scheme and no kernel configuration, where that is the faster way.
+// Levels the launch that starts at level l takes, in a call that names no
+// scheme and no kernel configuration: the last three, forward or inverse, while
+// their tiles all run at once (two work-groups on each of 256 CUs: 192 x 256 FP32
+// 10.3 us for 13.8 in two launches; past it the recomputed halo, three quarters
+// of a tile, costs more: 2048^2, 704 tiles, 19.8 for 17.4), else two where that
+// is the faster way.
 int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int wavelet, unsigned flags,
                      int32_t planes) {
-    const bool two = flags == 0 && wavelet != DWT2_DD137 && l + 1 < p.levels &&
-                     dwt2::pair_pays(dir, to_dtype(dtype), p.h[l], p.w[l], planes);
-    return two ? 2 : 1;
+    if (flags != 0 || wavelet == DWT2_DD137 || l + 1 >= p.levels) return 1;
+    if (dir != dwt2::kAdjoint && l + 3 == p.levels && dwt2::triple_tiles(p.h[l], p.w[l], planes) <= 512) return 3;
+    return dwt2::pair_pays(dir, to_dtype(dtype), p.h[l], p.w[l], planes) ? 2 : 1;
 }
 
-// Two levels in one launch for a whole batch: the same choice as for a stack of
-// planes (pair_pays), on the sums over the images.
+// Two or three levels in one launch for a whole batch: the same choice as for a
+// stack of planes (levels_in_launch), on the sums over the images.
 struct BatchPairStats {
-    uint64_t tiles32, tiles48;    // tiles of 32 and of 48 block rows
+    uint64_t tiles32, tiles48;    // two-level tiles of 32 and of 48 block rows
+    uint64_t tiles3;              // three-level tiles
     uint64_t cols112, cols128;    // tiles across, two-level and one-level, weighted by the image's rows
     uint64_t samples;
 };
 void add_pair_stats(int32_t h, int32_t w, int levels, BatchPairStats* st) {
     for (int l = 0; l + 1 < levels; ++l) {
         int32_t tx, ty;
-        dwt2::pair_tile_grid(h, w, 32, &tx, &ty);
+        dwt2::multi_tile_grid(h, w, 3, 0, &tx, &ty);
+        st[l].tiles3 += (uint64_t)tx * (uint64_t)ty;
+        dwt2::multi_tile_grid(h, w, 2, 32, &tx, &ty);
         st[l].tiles32 += (uint64_t)tx * (uint64_t)ty;
-        dwt2::pair_tile_grid(h, w, 48, &tx, &ty);
+        dwt2::multi_tile_grid(h, w, 2, 48, &tx, &ty);
         st[l].tiles48 += (uint64_t)tx * (uint64_t)ty;
         st[l].cols112 += (uint64_t)tx * (uint64_t)h;
         st[l].cols128 += (uint64_t)(((w + 1) / 2 + 2 * dwt2::kLanes - 1) / (2 * dwt2::kLanes)) * (uint64_t)h;
@@ -379,6 +385,10 @@ bool batch_pair_pays(int dtype, const BatchPairStats& st) {
     return !(dtype != DWT2_F32 && st.samples > (1 << 26));
 }
 
+// Forward: level l reads the LL of level l-1 (src for l = 0) and writes its
+// details into dst at the level's region origin (dst itself: every level's
+// region starts at (0, 0)), its LL into the workspace or, for the last level,
+// into dst.
 int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t dps, int32_t h, int32_t w,
                 int64_t sp, int64_t dp, int dtype, int wavelet, int levels, unsigned flags, void* ws,
                 hipStream_t s) {
@@ -410,7 +420,7 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
         void* const out_ll = last ? dst : (void*)bufs[cur];
         const int64_t out_ll_pitch = last ? dp : ws_pitch((p.w[l + n - 1] + 1) / 2);
         const int64_t out_ll_ps = last ? dps : buf_ps[cur];
-        if (n == 2) {
+        if (n > 1) {
             dwt2::PairParams pp{};
             pp.in = in;
             pp.in_pitch = in_pitch;
@@ -423,12 +433,12 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
             pp.ll_ps = out_ll_ps;
             pp.h = p.h[l];
             pp.w = p.w[l];
-            const int rc = report(dwt2::launch_pair(dwt2::kForward, to_wav(wavelet), to_dtype(dtype), pp, planes, s));
+            const int rc = report(dwt2::launch_pair(dwt2::kForward, to_wav(wavelet), to_dtype(dtype), n, pp, planes, s));
             if (rc) return rc;
             in = out_ll;
             in_pitch = out_ll_pitch;
             in_ps = out_ll_ps;
-            ++l;
+            l += n - 1;
             continue;
         }
         dwt2::LevelParams lp{};
@@ -440,7 +450,7 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
         lp.out = dst;
         lp.out_pitch = dp;
         lp.out_ps = dps;
-        lp.ll_cached = !last && cached_output(planes, (lp.h + 1) / 2, (lp.w + 1) / 2, es) ? 1 : 0;
+        lp.ll_cached = !last && cached_output(dwt2::kForward, planes, (lp.h + 1) / 2, (lp.w + 1) / 2, es) ? 1 : 0;
         lp.out_ll = out_ll;
         lp.out_ll_pitch = out_ll_pitch;
         lp.out_ll_ps = out_ll_ps;
@@ -480,7 +490,7 @@ int run_backward(dwt2::Direction dir, const void* src, void* dst, int32_t planes
         void* const out = l == 0 ? dst : (void*)bufs[buf];
         const int64_t out_pitch = l == 0 ? dp : ws_pitch(p.w[l]);
         const int64_t out_ps = l == 0 ? dps : buf_ps[buf];
-        if (n == 2) {
+        if (n > 1) {
             dwt2::PairParams pp{};
             pp.in = src;
             pp.in_pitch = sp;
@@ -493,7 +503,7 @@ int run_backward(dwt2::Direction dir, const void* src, void* dst, int32_t planes
             pp.ll_ps = ll_ps;
             pp.h = p.h[l];
             pp.w = p.w[l];
-            const int rc = report(dwt2::launch_pair(dir, to_wav(wavelet), to_dtype(dtype), pp, planes, s));
+            const int rc = report(dwt2::launch_pair(dir, to_wav(wavelet), to_dtype(dtype), n, pp, planes, s));
             if (rc) return rc;
             ll = out;
             ll_pitch = out_pitch;
@@ -510,7 +520,7 @@ int run_backward(dwt2::Direction dir, const void* src, void* dst, int32_t planes
         lp.in_ll_pitch = ll_pitch;
         lp.in_ll_ps = ll_ps;
         // the image of level l is the LL of level l-1
-        lp.ll_cached = l > 0 && cached_output(planes, p.h[l], p.w[l], es) ? 1 : 0;
+        lp.ll_cached = l > 0 && cached_output(dir, planes, p.h[l], p.w[l], es) ? 1 : 0;
         lp.out = out;
         lp.out_pitch = out_pitch;
         lp.out_ps = out_ps;
@@ -763,14 +773,17 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
     dwt2::BatchLaunches B{};
     uint32_t launch_tiles[32];
     for (int l = 0; l < levels; ++B.n) {
-        const bool two = pairs && l + 1 < levels && batch_pair_pays(dtype, stats[l]);
+        const BatchPairStats& st = stats[l];
+        const int n = !pairs || l + 1 >= levels ? 1
+                      : l + 3 == levels && st.tiles3 <= 512 ? 3
+                      : batch_pair_pays(dtype, st) ? 2 : 1;
+        const int rows = n != 2 ? 0 : dwt2::pair_rows(dwt2::kForward, es, (int64_t)st.tiles32, (int64_t)st.tiles48,
+                                                      (int64_t)st.samples);
         B.first[B.n] = (int8_t)l;
-        const int rows = !two ? 0
-                              : dwt2::pair_rows(dwt2::kForward, es, (int64_t)stats[l].tiles32, (int64_t)stats[l].tiles48,
-                                                (int64_t)stats[l].samples);
-        B.pair_rows[B.n] = (int8_t)rows;
-        launch_tiles[B.n] = (uint32_t)(rows == 0 ? tiles[l] : rows == 32 ? stats[l].tiles32 : stats[l].tiles48);
-        l += two ? 2 : 1;
+        B.levels[B.n] = (int8_t)n;
+        B.rows[B.n] = (int8_t)rows;
+        launch_tiles[B.n] = (uint32_t)(n == 1 ? tiles[l] : n == 3 ? st.tiles3 : rows == 32 ? st.tiles32 : st.tiles48);
+        l += n;
     }
     return report(dwt2::launch_fwd_batched_levels(to_dtype(dtype), sch, cfg, B, device_images, count, levels,
                                                   workspace, launch_tiles, (hipStream_t)stream));

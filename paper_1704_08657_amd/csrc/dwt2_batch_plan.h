@@ -149,33 +149,33 @@ __host__ __device__ inline size_t image_ll_bytes(int32_t h, int32_t w, int level
 // ---- one launch per level (the default path of dwt2_fwd_batched) ----------
 // Workspace, from its start:
 //   uint32 tile_off[levels][count + 1]   first tile of image i within the
-//                                        launch l (of level l, or of two
+//                                        launch l (of one, two or three
 //                                        levels); [l][count] = its tiles
 //   uint64 ll_off[count]                 byte offset of image i's LL buffers
 //                                        in the LL area
 //   LL area                              per image: buffer A (LL of levels
 //                                        1, 3, ...), buffer B (levels 2, 4, ...)
-// The launches: launch j takes level first[j], or, with pair_rows[j] > 0, levels
-// first[j] and first[j] + 1 in tiles of pair_rows[j] block rows (halo included).
-// tile_off's row j then holds the tiles of launch j.  The LL band that leaves
-// launch j (but the last) lies in buffer A for even j, B for odd j: A holds any
-// of the image's bands, B any but the first level's.
+// The launches: launch j takes levels[j] levels (1, 2 or 3) from level first[j]
+// on; two in tiles of rows[j] block rows (halo included).  tile_off's row j
+// then holds the tiles of launch j.  The LL band that leaves launch j (but the
+// last) lies in buffer A for even j, B for odd j: A holds any of the image's
+// bands, B any but the first level's.
 struct BatchLaunches {
     int32_t n;
-    int8_t first[32];
-    int8_t pair_rows[32];
+    int8_t first[32], levels[32], rows[32];
 };
-__host__ __device__ inline void pair_tile_grid(int32_t hl, int32_t wl, int rows, int32_t* tx, int32_t* ty) {
-    const int32_t nEr = (hl + 1) / 2, nEc = (wl + 1) / 2, core = rows - 2 * kHalo2;
-    *tx = (nEc + kPairCols - 1) / kPairCols;
-    *ty = (nEr + core - 1) / core;
+__host__ __device__ inline void multi_tile_grid(int32_t hl, int32_t wl, int levels, int rows, int32_t* tx, int32_t* ty) {
+    const int32_t nEr = (hl + 1) / 2, nEc = (wl + 1) / 2;
+    const int32_t cx = levels == 3 ? kTripleCols : kPairCols, cy = levels == 3 ? kTripleRows : rows - 2 * kHalo2;
+    *tx = (nEc + cx - 1) / cx;
+    *ty = (nEr + cy - 1) / cy;
 }
-__host__ __device__ inline uint64_t launch_tile_count(int32_t h, int32_t w, int l, int pair_rows, int core_cols,
+__host__ __device__ inline uint64_t launch_tile_count(int32_t h, int32_t w, int l, int levels, int rows, int core_cols,
                                                       int core_rows) {
-    if (pair_rows == 0) return level_tile_count(h, w, l, core_cols, core_rows);
+    if (levels == 1) return level_tile_count(h, w, l, core_cols, core_rows);
     int32_t hl, wl, tx, ty;
     level_size(h, w, l, &hl, &wl);
-    pair_tile_grid(hl, wl, pair_rows, &tx, &ty);
+    multi_tile_grid(hl, wl, levels, rows, &tx, &ty);
     return (uint64_t)tx * (uint64_t)ty;
 }
 // The batched level kernel deals its grid over the 8 XCDs in chunks of this
@@ -259,8 +259,8 @@ constexpr int kWaitLimitMs = 200;
 
 // Planner plus the launches of B: one level each on a tile kernel configuration
 // (persist_config_supported), CDF 9/7 forward, fused, split or factored steps,
-// float storage, or two levels each (the default scheme of the storage type,
-// pair_rows 32 or 48); `tiles[j]` (host array) is the number of tiles of launch
+// float storage, or two (rows 32 or 48) or three levels each (the default scheme
+// of the storage type); `tiles[j]` (host array) is the number of tiles of launch
 // j summed over the images and sizes its grid.
 hipError_t launch_fwd_batched_levels(Dtype dt, Scheme sch, int cfg, const BatchLaunches& B,
                                      const dwt2_image* dev_imgs, int count, int levels, void* ws,

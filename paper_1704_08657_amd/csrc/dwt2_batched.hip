@@ -2,7 +2,7 @@
 // or a stack of equal planes (dwt2_fwd / dwt2_fwd_planes with
 // DWT2_FLAG_PERSISTENT), every level.
 //
-// One launch per level or per two levels (the default of dwt2_fwd_batched): a
+// One launch per level, two or three (the default of dwt2_fwd_batched): a
 // planner kernel lays out, from the device copy of the image descriptors, per
 // launch an exclusive scan of the images' tile counts and every image's LL
 // ping-pong buffers; then each launch runs every image's tiles of its level or
@@ -207,7 +207,7 @@ persist_plan_kernel(ImageSet S, int count, int levels, int core_cols, int core_r
     for (uint32_t j = tid; j < base; j += kPlanThreads) done[j] = 0;
 }
 
-// ---- one launch per level or two levels -------------------------------------
+// ---- one launch per level, two or three -------------------------------------
 // Planner: per launch an exclusive scan of the images' tile counts (a launch
 // covers the tiles of all images), and each image's two LL ping-pong buffers.
 // Work-group j scans for launch j, the last one the buffers: the scans are
@@ -221,12 +221,12 @@ level_plan_kernel(const dwt2_image* imgs, int count, int levels, BatchLaunches B
     if (j < B.n) {
         __shared__ uint32_t sh32[1][kPlanThreads / kLanes];
         uint32_t* row = reinterpret_cast<uint32_t*>(ws + L.off_tile) + (size_t)j * (count + 1);
-        const int l = B.first[j], rows = B.pair_rows[j];
+        const int l = B.first[j], n = B.levels[j], rows = B.rows[j];
         uint32_t carry = 0;
         for (int b = 0; b < count; b += kPlanThreads) {
             const int i = b + tid;
-            uint32_t v[1] = {i < count ? (uint32_t)launch_tile_count(imgs[i].height, imgs[i].width, l, rows, core_cols,
-                                                                     core_rows)
+            uint32_t v[1] = {i < count ? (uint32_t)launch_tile_count(imgs[i].height, imgs[i].width, l, n, rows,
+                                                                     core_cols, core_rows)
                                        : 0u};
             uint32_t t[1];
             block_scan<1>(v, t, sh32);
@@ -340,12 +340,13 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
     tile_body<kForward, kCdf97, T, SCH, NW, K, BPL>(P, tx, ty, lds, lane, wv);
 }
 
-// Launch j: levels l and l + 1 of every image.  60 uneven images of 64 ... 2048
-// pixels a side, FP32, 5 levels: 203 us a call in 3 launches, 240 in 5; 16 of
-// 64 ... 300: 31.5 us (88 with the earlier border tiles); 1024 of 256^2: 194.
-template <typename T, int SCH, int NW, int K>
+// Launch j: levels l and l + 1, or l to l + 2, of every image.  60 uneven images
+// of 64 ... 2048 pixels a side, FP32, 5 levels: 240 us a call with a launch for
+// each level, 193 in three (2, 2, 1 levels); 16 of 64 ... 300: 25.6 us in two (88
+// with a launch for each level and the earlier border tiles).
+template <typename T, int SCH, int NW, int K, int LEVELS>
 __global__ void __launch_bounds__(NW * kLanes)
-batched_pair_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, unsigned char* ws) {
+batched_multi_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, unsigned char* ws) {
     using V = typename St<T>::V;
     __shared__ pair::PairLds<V, NW> lds;
     __shared__ pair::PairPlane<V, NW * K> plane;
@@ -356,13 +357,14 @@ batched_pair_kernel(const dwt2_image* imgs, int count, int levels, int j, int l,
     if (!batched_tile(ws, L, count, j, total, &i, &tt)) return;
     const dwt2_image im = imgs[i];
     PairParams P{};
-    int32_t hl, wl;
+    int32_t hl, wl, hx, wx;
     level_size(im.height, im.width, l, &hl, &wl);
+    level_size(hl, wl, LEVELS, &hx, &wx);          // the LL band that leaves the launch
     P.h = hl;
     P.w = wl;
-    pair_tile_grid(hl, wl, NW * K, &P.tiles_x, &P.tiles_y);
+    multi_tile_grid(hl, wl, LEVELS, NW * K, &P.tiles_x, &P.tiles_y);
     const BatchedBuffers b = batched_buffers(im, ws + L.off_ll + reinterpret_cast<const uint64_t*>(ws + L.off_ll_off)[i],
-                                             levels, j, l + 2 == levels, wl, ((wl + 1) / 2 + 1) / 2, sizeof(T));
+                                             levels, j, l + LEVELS == levels, wl, wx, sizeof(T));
     P.in = b.in;
     P.in_pitch = b.in_pitch;
     P.out = im.dst;
@@ -371,7 +373,8 @@ batched_pair_kernel(const dwt2_image* imgs, int count, int levels, int j, int l,
     P.ll_pitch = b.ll_pitch;
     const int ty = tt / P.tiles_x;
     const int tx = tt - ty * P.tiles_x;
-    pair::tile<kForward, kCdf97, T, SCH, NW, K>(P, tx, ty, lds, plane, lane, wv);
+    if constexpr (LEVELS == 3) pair::tile3<kForward, kCdf97, T, SCH>(P, tx, ty, lds, plane, lane, wv);
+    else pair::tile<kForward, kCdf97, T, SCH, NW, K>(P, tx, ty, lds, plane, lane, wv);
 }
 
 // ---- one persistent launch -------------------------------------------------
@@ -587,7 +590,7 @@ template <typename T, int SCH, int NW, int K, int BPL>
 hipError_t launch_levels_shape(const BatchLaunches& B, const dwt2_image* dev_imgs, int count, int levels, void* ws,
                                const uint32_t* tiles, hipStream_t s) {
     constexpr int kCoreBY = NW * K - 2 * kHalo;
-    constexpr int kPairScheme = sizeof(T) == 4 ? kSchemeFused : kSchemeFactored;   // the default of the storage type
+    constexpr int kMultiScheme = sizeof(T) == 4 ? kSchemeFused : kSchemeFactored;   // the default of the storage type
     unsigned char* w = static_cast<unsigned char*>(ws);
     hipLaunchKernelGGL(level_plan_kernel, dim3(B.n + 1), dim3(kPlanThreads), 0, s, dev_imgs, count, levels, B,
                        Lay<BPL>::CORE_BX, kCoreBY, (int)sizeof(T), w);
@@ -597,17 +600,21 @@ hipError_t launch_levels_shape(const BatchLaunches& B, const dwt2_image* dev_img
         const uint32_t chunks = (tiles[j] + kLevelChunk - 1) / kLevelChunk;
         const dim3 grid((chunks + 7u) / 8u * 8u * kLevelChunk);
         const int l = B.first[j];
-        if (B.pair_rows[j] == 0)
+#define DWT2_MULTI(NW_, K_, LEVELS_)                                                                        \
+    hipLaunchKernelGGL((batched_multi_kernel<T, kMultiScheme, NW_, K_, LEVELS_>), grid, dim3((NW_) * kLanes), 0, s, \
+                       dev_imgs, count, levels, j, l, tiles[j], w)
+        if (B.levels[j] == 1)
             hipLaunchKernelGGL((batched_level_kernel<T, SCH, NW, K, BPL>), grid, dim3(NW * kLanes), 0, s, dev_imgs,
                                count, levels, j, l, tiles[j], w);
-        else if constexpr (SCH != kPairScheme)
+        else if constexpr (SCH != kMultiScheme)
             return hipErrorInvalidValue;
-        else if (B.pair_rows[j] == 32)
-            hipLaunchKernelGGL((batched_pair_kernel<T, kPairScheme, 8, 4>), grid, dim3(8 * kLanes), 0, s, dev_imgs,
-                               count, levels, j, l, tiles[j], w);
+        else if (B.levels[j] == 3)
+            DWT2_MULTI(kTripleWaves, kTripleK, 3);
+        else if (B.rows[j] == 32)
+            DWT2_MULTI(8, 4, 2);
         else
-            hipLaunchKernelGGL((batched_pair_kernel<T, kPairScheme, 8, 6>), grid, dim3(8 * kLanes), 0, s, dev_imgs,
-                               count, levels, j, l, tiles[j], w);
+            DWT2_MULTI(8, 6, 2);
+#undef DWT2_MULTI
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -23,16 +23,17 @@ hipError_t launch_level(Direction dir, Wavelet wav, Dtype dt, Scheme sch, int cf
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_pair_fwd(Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t s);
-hipError_t launch_pair_inv(Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t s);
-hipError_t launch_pair_adj(Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t s);
+hipError_t launch_pair_fwd(Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes, hipStream_t s);
+hipError_t launch_pair_inv(Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes, hipStream_t s);
+hipError_t launch_pair_adj(Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes, hipStream_t s);
 
-hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t stream) {
+hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes,
+                       hipStream_t stream) {
     if (planes <= 0) return hipSuccess;
     switch (dir) {
-        case kForward: return launch_pair_fwd(wav, dt, p, planes, stream);
-        case kInverse: return launch_pair_inv(wav, dt, p, planes, stream);
-        case kAdjoint: return launch_pair_adj(wav, dt, p, planes, stream);
+        case kForward: return launch_pair_fwd(wav, dt, levels, p, planes, stream);
+        case kInverse: return launch_pair_inv(wav, dt, levels, p, planes, stream);
+        case kAdjoint: return launch_pair_adj(wav, dt, levels, p, planes, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -104,10 +104,10 @@ struct LevelParams {
     int32_t ll_cached;
 };
 
-// Two consecutive levels in one launch.  Forward: `in` is the h x w image of
-// the first level, `out` the pyramid (the details of both levels go there), `ll`
-// receives the second level's LL band.  Inverse / adjoint: `in` is the pyramid,
-// `ll` the second level's LL band, `out` the h x w image.  *_ps: plane strides.
+// Two or three consecutive levels in one launch.  Forward: `in` is the h x w
+// image of the first level, `out` the pyramid (the details of every level go
+// there), `ll` receives the last level's LL band.  Inverse / adjoint: `in` is the
+// pyramid, `ll` the last level's LL band, `out` the h x w image.  *_ps: plane strides.
 struct PairParams {
     const void* in;
     int64_t in_pitch, in_ps;
@@ -164,8 +164,19 @@ inline bool pair_pays(Direction dir, Dtype dt, int32_t h, int32_t w, int32_t pla
     if (2 * ((nc + kPairCols - 1) / kPairCols) >= 3 * ((nc + 2 * kLanes - 1) / (2 * kLanes))) return false;
     return !(dir == kForward && (dt == kBF16 || dt == kF16) && (int64_t)h * w * planes > (1 << 26));
 }
-// Enqueue it with the wavelet's default scheme.
-hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t stream);
+// Three levels (forward and inverse): tiles of 8 waves x 6 block rows with a halo
+// of kHalo3 blocks on every side.
+constexpr int kHalo3 = 16;
+constexpr int kTripleWaves = 8, kTripleK = 6;
+constexpr int kTripleRows = kTripleWaves * kTripleK - 2 * kHalo3;
+constexpr int kTripleCols = 2 * kLanes - 2 * kHalo3;
+inline int64_t triple_tiles(int32_t h, int32_t w, int32_t planes) {
+    return (int64_t)(((w + 1) / 2 + kTripleCols - 1) / kTripleCols) *
+           (((h + 1) / 2 + kTripleRows - 1) / kTripleRows) * planes;
+}
+// Enqueue `levels` (2 or 3) levels with the wavelet's default scheme.
+hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes,
+                       hipStream_t stream);
 
 // Enqueue one level for `planes` planes (1 <= planes <= kMaxGridPlanes).
 // Returns hipSuccess or the launch error.  `cfg` indexes kConfigs;

@@ -33,11 +33,11 @@ hipError_t launch_grid(const LevelParams& p, int planes, hipStream_t s) {
     return hipSuccess;
 }
 
-// A CDF 9/7 level whose output the next level of the call reads stores it
+// A CDF 9/7 level whose output the next level of the call reads may store it
 // with ordinary stores in its interior tiles (ll_cached).
 template <int DIR, int WAV, typename T, int SCH, int NW, int K, int BPL>
 hipError_t launch_shape(const LevelParams& p, int planes, hipStream_t s) {
-    if constexpr (WAV == kCdf97) {
+    if constexpr (WAV == kCdf97 && (DIR != kForward || sizeof(T) == 2)) {
         if (p.ll_cached) return launch_grid<DIR, WAV, T, SCH, NW, K, BPL, true>(p, planes, s);
     }
     return launch_grid<DIR, WAV, T, SCH, NW, K, BPL>(p, planes, s);

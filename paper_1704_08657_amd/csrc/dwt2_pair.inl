@@ -1,4 +1,4 @@
-// Two levels of the transform in one launch: device code (included by
+// Two or three levels of the transform in one launch: device code (included by
 // dwt2_pair_*.hip and dwt2_batched.hip).
 #pragma once
 #include "dwt2_kernels.inl"
@@ -317,6 +317,25 @@ __device__ __forceinline__ void store_bands(typename St<T>::V (&a)[K][4 * BPL], 
             }
 }
 
+// The same for the third level: ROWS block rows from the tile's first wave on, K
+// a wave, so the last waves may hold none.
+template <typename T, int H, int ROWS, int K>
+__device__ __forceinline__ void store_bands3(typename St<T>::V (&a)[K][4], T* ll, int64_t ll_pitch, T* det,
+                                             int64_t pitch, const Geo& g, int lane, int wv) {
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        const int tr = wv * K + r;
+        if (tr < H || tr >= ROWS - H) continue;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (g.gr0 + r >= (k >= 2 ? g.nOr : g.nEr) || g.gcL >= ((k & 1) ? g.nOc : g.nEc)) continue;
+            const typename St<T>::V v[1] = {a[r][k]};
+            store_band_row<T, 1>(lane_at(subband_row(ll, ll_pitch, det, pitch, g, k, g.gr0 + r) + g.cb0,
+                                         (uint32_t)lane * (uint32_t)sizeof(T)), v);
+        }
+    }
+}
+
 // The tile's core as image rows (inverse and adjoint).
 template <typename T, bool BORDER, int H, int NW, int BPL, int K>
 __device__ __forceinline__ void store_image(typename St<T>::V (&a)[K][4 * BPL], T* out, int64_t pitch, int h, int w,
@@ -463,7 +482,152 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
     }
 }
 
-template <int DIR, int WAV, typename T, int SCH, int NW, int K>
+// ---- three levels in one launch ---------------------------------------------
+// For the last three levels of small images, where a launch costs more than the
+// work: 192 x 256, 3 levels, took a two-level launch of 7.3 us and a one-level
+// launch of 6.  Levels l and l + 1 as above; level l + 2 takes its samples from
+// LDS, a block a lane (32 blocks across) and kRows3 block rows a wave, with the
+// symmetric extension applied in the read.  The halo is that of three levels, 14
+// block rows and columns of level 1, rounded up to whole blocks of level 3.
+constexpr int kRows3 = 2;
+
+// Tile (tx, ty) of levels l, l + 1 and l + 2 (forward and inverse): 8 waves x 6
+// rows, of which kTripleRows rows and kTripleCols block columns are stored.
+template <int DIR, int WAV, typename T, int SCH>
+__device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairLds<typename St<T>::V, kTripleWaves>& L,
+                                      PairPlane<typename St<T>::V, kTripleWaves * kTripleK>& S, int lane, int wv) {
+    using V = typename St<T>::V;
+    constexpr int NW = kTripleWaves, K = kTripleK, K2 = K / 2, R = NW * K, R2 = R / 2;
+    static_assert(NW * kRows3 >= R / 4, "level 3's block rows");
+    Geo g, g2, g3;
+    const int h2 = (P.h + 1) >> 1, w2 = (P.w + 1) >> 1, h3 = (h2 + 1) >> 1, w3 = (w2 + 1) >> 1;
+    g.nEr = h2; g.nOr = P.h >> 1; g.nEc = w2; g.nOc = P.w >> 1;
+    g2.nEr = h3; g2.nOr = h2 >> 1; g2.nEc = w3; g2.nOc = w2 >> 1;
+    g3.nEr = (h3 + 1) >> 1; g3.nOr = h3 >> 1; g3.nEc = (w3 + 1) >> 1; g3.nOc = w3 >> 1;
+    const int r0 = ty * kTripleRows - kHalo3, c0 = tx * kTripleCols - kHalo3;   // multiples of 4
+    g.cb0 = c0;
+    g.gcL = c0 + 2 * lane;
+    g.gr0 = r0 + wv * K;
+    g2.cb0 = c0 / 2;
+    g2.gcL = g2.cb0 + lane;
+    g2.gr0 = g.gr0 / 2;
+    g3.cb0 = c0 / 4;
+    g3.gcL = g3.cb0 + lane;
+    g3.gr0 = r0 / 4 + wv * kRows3;
+    const bool interior = r0 >= 0 && c0 >= 0 && r0 + R <= g.nOr && c0 + 2 * kLanes <= g.nOc;
+    constexpr int kEl = kHalo3 / 2;                // halo lanes of levels 1 and 2; half as many at level 3
+    const bool core_lane = lane >= kEl && lane < kLanes - kEl;
+    const bool core_lane3 = lane >= kEl / 2 && lane < kLanes / 2 - kEl / 2;
+    V a[K][8], b[K2][4], c[kRows3][4];
+    // LL samples of level 1 for level 2 (forward) or back (inverse), see tile()
+    auto plane1 = [&](int row, int col) -> V& { return S.p[clamp_to(row - r0, R)][clamp_to(col - c0, 2 * kLanes)]; };
+    // those of level 2 for level 3: R2 rows of 64, in the same LDS rows
+    auto plane2 = [&](int row, int col) -> V& { return S.p[clamp_to(row - r0 / 2, R2)][clamp_to(col - c0 / 2, kLanes)]; };
+    if constexpr (DIR == kForward) {
+        load_image<T, 2, K>(a, static_cast<const T*>(P.in), P.in_pitch, P.h, P.w, g, interior, lane);
+        steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        T* const out = static_cast<T*>(P.out);
+        if (core_lane) store_bands<T, 1, kHalo3, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
+#pragma unroll
+        for (int r = 0; r < K2; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[r][k] = stored<T>(a[2 * r + (k >> 1)][4 * (k & 1)]);
+        if (!interior) {
+#pragma unroll
+            for (int r = 0; r < K2; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) S.p[wv * K + 2 * r + (k >> 1)][2 * lane + (k & 1)] = b[r][k];
+            __syncthreads();
+            int rows[K], cols[2];
+#pragma unroll
+            for (int i = 0; i < K; ++i) rows[i] = 2 * g2.gr0 + i;
+            cols[0] = 2 * g2.gcL;
+            cols[1] = 2 * g2.gcL + 1;
+            fold_both(rows, h2);
+            fold_both(cols, w2);
+#pragma unroll
+            for (int r = 0; r < K2; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) b[r][k] = plane1(rows[2 * r + (k >> 1)], cols[k & 1]);
+        }
+        steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+        if (core_lane) store_bands<T, 1, kHalo3 / 2, NW, 1, K2>(b, out, 0, out, P.out_pitch, g2, lane, wv);
+        // the reads of plane 1 precede the barriers of level 2's steps
+#pragma unroll
+        for (int r = 0; r < K2; ++r) S.p[wv * K2 + r][lane] = stored<T>(b[r][0]);
+        __syncthreads();
+        int rows[2 * kRows3], cols[2];
+#pragma unroll
+        for (int i = 0; i < 2 * kRows3; ++i) rows[i] = 2 * g3.gr0 + i;
+        cols[0] = 2 * g3.gcL;
+        cols[1] = 2 * g3.gcL + 1;
+        fold_both(rows, h3);
+        fold_both(cols, w3);
+#pragma unroll
+        for (int r = 0; r < kRows3; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) c[r][k] = plane2(rows[2 * r + (k >> 1)], cols[k & 1]);
+        steps<DIR, WAV, SCH, false, NW, 1, kRows3>(c, L, lane, wv, g3);
+        if (core_lane3)
+            store_bands3<T, kHalo3 / 4, R / 4, kRows3>(c, static_cast<T*>(P.ll), P.ll_pitch, out, P.out_pitch, g3, lane,
+                                                       wv);
+    } else {
+        static_assert(DIR == kInverse, "the adjoint takes at most two levels a launch");
+        const T* const det = static_cast<const T*>(P.in);
+        load_bands<T, false, 0, 1, kRows3>(c, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h3, w3, g3, false,
+                                           lane);
+        load_bands<T, false, 1, 1, K2>(b, det, P.in_pitch, det, P.in_pitch, h2, w2, g2, interior, lane);
+        load_bands<T, false, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        steps<DIR, WAV, SCH, false, NW, 1, kRows3>(c, L, lane, wv, g3);
+        if (lane < kLanes / 2) {
+#pragma unroll
+            for (int r = 0; r < kRows3; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int row = 2 * (wv * kRows3 + r) + (k >> 1);
+                    if (row < R2) S.p[row][2 * lane + (k & 1)] = stored<T>(c[r][k]);
+                }
+        }
+        __syncthreads();
+        {
+            // LL sample of block (gr, gc): at its reflected pixel position
+            int rows[K2], cols[1] = {2 * g2.gcL};
+#pragma unroll
+            for (int i = 0; i < K2; ++i) rows[i] = 2 * (g2.gr0 + i);
+            fold_both(rows, h2);
+            fold_both(cols, w2);
+#pragma unroll
+            for (int r = 0; r < K2; ++r) b[r][0] = plane2(rows[r] >> 1, cols[0] >> 1);
+        }
+        steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+#pragma unroll
+        for (int r = 0; r < K2; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a[2 * r + (k >> 1)][4 * (k & 1)] = stored<T>(b[r][k]);
+        if (!interior) {
+            // the reads of plane 2 precede the barriers of level 2's steps
+#pragma unroll
+            for (int r = 0; r < K; ++r)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) S.p[wv * K + r][2 * lane + q] = a[r][4 * q];
+            __syncthreads();
+            int rows[K], cols[2] = {2 * g.gcL, 2 * g.gcL + 2};
+#pragma unroll
+            for (int i = 0; i < K; ++i) rows[i] = 2 * (g.gr0 + i);
+            fold_both(rows, P.h);
+            fold_both(cols, P.w);
+#pragma unroll
+            for (int r = 0; r < K; ++r)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) a[r][4 * q] = plane1(rows[r] >> 1, cols[q] >> 1);
+        }
+        steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        if (core_lane)
+            store_image<T, true, kHalo3, NW, 2, K>(a, static_cast<T*>(P.out), P.out_pitch, P.h, P.w, g, lane, wv);
+    }
+}
+
+template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
 __global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
     using V = typename St<T>::V;
     __shared__ PairLds<V, NW> L;
@@ -487,14 +651,16 @@ __global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
     Q.in = static_cast<const T*>(P.in) + (int64_t)pl * P.in_ps;
     Q.out = static_cast<T*>(P.out) + (int64_t)pl * P.out_ps;
     Q.ll = static_cast<T*>(P.ll) + (int64_t)pl * P.ll_ps;
-    tile<DIR, WAV, T, SCH, NW, K>(Q, tx, ty, L, S, lane, wv);
+    if constexpr (LEVELS == 3) tile3<DIR, WAV, T, SCH>(Q, tx, ty, L, S, lane, wv);
+    else tile<DIR, WAV, T, SCH, NW, K>(Q, tx, ty, L, S, lane, wv);
 }
 
 // ---- launch (host) ----------------------------------------------------------
-template <int DIR, int WAV, typename T, int SCH, int NW, int K>
+template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
 hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
-    constexpr int CY = NW * K - 2 * kHalo2;
-    p.tiles_x = ((p.w + 1) / 2 + kPairCols - 1) / kPairCols;
+    constexpr int CX = LEVELS == 3 ? kTripleCols : kPairCols;
+    constexpr int CY = LEVELS == 3 ? kTripleRows : NW * K - 2 * kHalo2;
+    p.tiles_x = ((p.w + 1) / 2 + CX - 1) / CX;
     p.tiles_y = ((p.h + 1) / 2 + CY - 1) / CY;
     // the tiles of all planes, rounded up to a multiple of 8 chunks; planes
     // beyond what one grid holds go to further launches
@@ -510,7 +676,7 @@ hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
         q.out = static_cast<T*>(p.out) + p0 * p.out_ps;
         q.ll = static_cast<T*>(p.ll) + p0 * p.ll_ps;
         const int64_t grid = (nt * q.planes + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
-        hipLaunchKernelGGL((pair_kernel<DIR, WAV, T, SCH, NW, K>), dim3((unsigned)grid), dim3(NW * kLanes), 0, s, q);
+        hipLaunchKernelGGL((pair_kernel<DIR, WAV, T, SCH, NW, K, LEVELS>), dim3((unsigned)grid), dim3(NW * kLanes), 0, s, q);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -518,8 +684,9 @@ hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
 }
 
 template <int DIR, int WAV, typename T, int SCH>
-hipError_t launch(const PairParams& p, int planes, hipStream_t s) {
+hipError_t launch(int levels, const PairParams& p, int planes, hipStream_t s) {
     if constexpr (DIR != kAdjoint) {
+        if (levels == 3) return launch_shape<DIR, WAV, T, SCH, kTripleWaves, kTripleK, 3>(p, planes, s);
         if (pair_rows((Direction)DIR, sizeof(T), pair_tiles(p.h, p.w, planes, 32), pair_tiles(p.h, p.w, planes, 48),
                       (int64_t)p.h * p.w * planes) == 48)
             return launch_shape<DIR, WAV, T, SCH, 8, 6>(p, planes, s);
@@ -530,24 +697,25 @@ hipError_t launch(const PairParams& p, int planes, hipStream_t s) {
 // The default schemes: fused steps for 4-byte samples and for the adjoint,
 // factored ones for 16-bit storage.
 template <int DIR, int WAV, typename T>
-hipError_t launch_t(const PairParams& p, int planes, hipStream_t s) {
-    return launch<DIR, WAV, T, (sizeof(T) == 4 || DIR == kAdjoint) ? kSchemeFused : kSchemeFactored>(p, planes, s);
+hipError_t launch_t(int levels, const PairParams& p, int planes, hipStream_t s) {
+    return launch<DIR, WAV, T, (sizeof(T) == 4 || DIR == kAdjoint) ? kSchemeFused : kSchemeFactored>(levels, p, planes, s);
 }
 template <int DIR, int WAV>
-hipError_t launch_float(Dtype dt, const PairParams& p, int planes, hipStream_t s) {
+hipError_t launch_float(Dtype dt, int levels, const PairParams& p, int planes, hipStream_t s) {
     switch (dt) {
-        case kF32: return launch_t<DIR, WAV, float>(p, planes, s);
-        case kBF16: return launch_t<DIR, WAV, __hip_bfloat16>(p, planes, s);
-        case kF16: return launch_t<DIR, WAV, __half>(p, planes, s);
+        case kF32: return launch_t<DIR, WAV, float>(levels, p, planes, s);
+        case kBF16: return launch_t<DIR, WAV, __hip_bfloat16>(levels, p, planes, s);
+        case kF16: return launch_t<DIR, WAV, __half>(levels, p, planes, s);
         default: return hipErrorInvalidValue;
     }
 }
 template <int DIR>
-hipError_t launch_dir(Wavelet wav, Dtype dt, const PairParams& p, int planes, hipStream_t s) {
-    if (wav == kCdf97) return launch_float<DIR, kCdf97>(dt, p, planes, s);
+hipError_t launch_dir(Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes, hipStream_t s) {
+    if (levels != 2 && (levels != 3 || DIR == kAdjoint)) return hipErrorInvalidValue;
+    if (wav == kCdf97) return launch_float<DIR, kCdf97>(dt, levels, p, planes, s);
     if constexpr (DIR != kAdjoint) {
-        if (wav == kCdf53) return launch_t<DIR, kCdf53, int32_t>(p, planes, s);
-        if (wav == kCdf53Real) return launch_float<DIR, kCdf53Real>(dt, p, planes, s);
+        if (wav == kCdf53) return launch_t<DIR, kCdf53, int32_t>(levels, p, planes, s);
+        if (wav == kCdf53Real) return launch_float<DIR, kCdf53Real>(dt, levels, p, planes, s);
     }
     return hipErrorInvalidValue;
 }

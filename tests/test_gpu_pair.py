@@ -1,9 +1,9 @@
-"""Two levels in one launch (calls that name no scheme and no kernel
-configuration) against one launch per level (configuration 0): bit for bit the
-same, for every wavelet, storage type and direction, at the ends of its tiles
-(224 pixels wide, 40 / 72 / 40 high for the small / middle / largest levels), on
-the smallest images, over odd pitches and plane strides, and with an odd and an
-even number of levels."""
+"""Two levels in one launch, and the last three of small images (calls that name
+no scheme and no kernel configuration), against one launch per level
+(configuration 0): bit for bit the same, for every wavelet, storage type and
+direction, at the ends of their tiles (224 pixels wide, 40 or 72 high; three
+levels 192 wide, 32 high), on the smallest images, over odd pitches and plane
+strides, and with an odd and an even number of levels."""
 import pytest
 
 import workloads
@@ -41,7 +41,8 @@ def check(x, wavelet, levels):
 @pytest.mark.parametrize("wavelet,tdt", TYPES)
 def test_tile_ends(wavelet, tdt):
     for n, h, w, levels in ((1, 39, 223, 2), (1, 40, 224, 3), (2, 41, 225, 2), (1, 44, 226, 4), (1, 81, 449, 2),
-                            (3, 83, 460, 5), (1, 120, 672, 3), (1, 200, 1000, 4)):
+                            (3, 83, 460, 5), (1, 120, 672, 3), (1, 200, 1000, 4), (1, 31, 191, 3), (2, 32, 192, 3),
+                            (1, 33, 193, 3), (1, 64, 384, 3), (3, 66, 387, 3), (40, 96, 200, 3)):
         check(image(n, h, w, tdt, 101), wavelet, levels)
 
 
@@ -60,9 +61,10 @@ def test_larger_levels(wavelet, tdt, n, h, w, levels):
 
 
 @pytest.mark.parametrize("wavelet,tdt", TYPES[:4])
-def test_strides(wavelet, tdt):
+@pytest.mark.parametrize("levels", [3, 4])
+def test_strides(wavelet, tdt, levels):
     """Raw calls with offset buffers, odd pitches and gaps between planes."""
-    n, h, w, levels = 3, 85, 451, 4
+    n, h, w = 3, 85, 451
     x = image(n, h, w, tdt, 104)
     dt = d.dtype_code(x)
     ws = d.workspace(h, w, levels, dt, dev(), n)

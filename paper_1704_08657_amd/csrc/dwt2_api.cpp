@@ -350,7 +350,7 @@ bool cached_output(dwt2::Direction dir, int32_t planes, int32_t h, int32_t w, si
 int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int wavelet, unsigned flags,
                      int32_t planes) {
     if (flags != 0 || wavelet == DWT2_DD137 || l + 1 >= p.levels) return 1;
-    if (dir != dwt2::kAdjoint && l + 3 == p.levels && dwt2::triple_tiles(p.h[l], p.w[l], planes) <= 512) return 3;
+    if (l + 3 == p.levels && dwt2::triple_tiles(p.h[l], p.w[l], planes) <= 512) return 3;
     return dwt2::pair_pays(dir, to_dtype(dtype), p.h[l], p.w[l], planes) ? 2 : 1;
 }
 

@@ -138,11 +138,10 @@ inline int64_t pair_tiles(int32_t h, int32_t w, int32_t planes, int rows) {
 // 8 x 4: 200) and one round of tiles (3 x 1081 x 1921 FP32 forward 13.2, 14.5);
 // 8 x 4 has 60 registers to 82 and more work-groups on a CU, which counts where
 // memory is: 4-byte samples forward (8192^2 106 us, 8 x 6: 115; 4096^2 28.3,
-// 29.1) and, inverse, from 2^25 samples (8192^2 103, 108; but 4096^2 27.3, 25.6).
-// The adjoint has two step programs (border weights) and keeps 8 x 4, where
-// both fit the registers (8192^2: 124 us, 8 x 6 161).
+// 29.1) and, inverse and adjoint, from 2^25 samples (inverse 8192^2 103, 108; but
+// 4096^2 27.3, 25.6).
 inline int pair_rows(Direction dir, size_t es, int64_t tiles32, int64_t tiles48, int64_t samples) {
-    if (dir == kAdjoint || tiles32 <= 640) return 32;
+    if (tiles32 <= 640) return 32;
     if (es == 2) return 48;
     if (dir == kForward) return tiles48 <= 512 ? 48 : 32;
     return samples >= (1 << 25) ? 32 : 48;
@@ -154,7 +153,7 @@ inline int pair_rows(Direction dir, size_t es, int64_t tiles32, int64_t tiles48,
 //   * larger ones, when 112 columns a tile do not cost half as many tiles
 //     again as the one-level kernel's 128 (8192^2 FP32 121 / 106, inverse
 //     127 / 103; 3469 x 5197 41 / 33; but 192 planes of 256^2, two tiles for
-//     one: 31.4 / 34, adjoint 40 / 55);
+//     one: 31.4 / 34);
 //   * 16-bit storage, forward, up to 2^26 samples: beyond, the recomputed
 //     halo costs what the LL band saves (3 x 8192^2 BF16 188 / 193,
 //     3 x 4096^2 56 / 53, inverse 198 / 176).
@@ -164,7 +163,7 @@ inline bool pair_pays(Direction dir, Dtype dt, int32_t h, int32_t w, int32_t pla
     if (2 * ((nc + kPairCols - 1) / kPairCols) >= 3 * ((nc + 2 * kLanes - 1) / (2 * kLanes))) return false;
     return !(dir == kForward && (dt == kBF16 || dt == kF16) && (int64_t)h * w * planes > (1 << 26));
 }
-// Three levels (forward and inverse): tiles of 8 waves x 6 block rows with a halo
+// Three levels: tiles of 8 waves x 6 block rows with a halo
 // of kHalo3 blocks on every side.
 constexpr int kHalo3 = 16;
 constexpr int kTripleWaves = 8, kTripleK = 6;

@@ -29,8 +29,8 @@
 //     per subband row, both coalesced across the wave;
 //   * tiles touching the image border load the whole-point symmetric
 //     extension of the image and then run the same unclamped steps (each
-//     step keeps the extension symmetric); the adjoint's border tiles apply
-//     the transposed border weights instead; interior tiles take a
+//     step keeps the extension symmetric); the adjoint's border tiles hold the
+//     end samples of each axis doubled; interior tiles take a
 //     branch-free vector path;
 //   * the step program is chosen at compile time: the fused steps, the fused
 //     steps with the split, the separable steps (the comparison scheme) or
@@ -443,22 +443,22 @@ __device__ __forceinline__ void gather_minus(const V (&cur)[Lay<BPL>::BX], const
 
 // Apply a step to blocks 0 .. N-1 of v (v[4 b + k] = x_k of block b) whose
 // bit is set in MASK; gc[b]: block column, gr: block row.
-template <int KIND, int MASK, bool EX, bool EY, int N, typename V>
+template <int KIND, int MASK, int N, typename V>
 __device__ __forceinline__ void apply_plus(V (&v)[4 * N], const PlusOps<V, N>& o, const int (&gc)[N], int gr,
                                            const Geo& g, float c) {
 #pragma unroll
     for (int b = 0; b < N; ++b)
         if ((MASK >> b) & 1)
-            plus_block<KIND, EX, EY>(v[4 * b], v[4 * b + 1], v[4 * b + 2], v[4 * b + 3], o.x0R[b], o.x2R[b],
+            plus_block<KIND, false, false>(v[4 * b], v[4 * b + 1], v[4 * b + 2], v[4 * b + 3], o.x0R[b], o.x2R[b],
                                      o.x0D[b], o.x1D[b], o.x0DR[b], gc[b], gr, g, c);
 }
-template <int KIND, int MASK, bool EX, bool EY, int N, typename V>
+template <int KIND, int MASK, int N, typename V>
 __device__ __forceinline__ void apply_minus(V (&v)[4 * N], const MinusOps<V, N>& o, const int (&gc)[N], int gr,
                                             const Geo& g, float c) {
 #pragma unroll
     for (int b = 0; b < N; ++b)
         if ((MASK >> b) & 1)
-            minus_block<KIND, EX, EY>(v[4 * b], v[4 * b + 1], v[4 * b + 2], v[4 * b + 3], o.x1l[b], o.x3l[b],
+            minus_block<KIND, false, false>(v[4 * b], v[4 * b + 1], v[4 * b + 2], v[4 * b + 3], o.x1l[b], o.x3l[b],
                                       o.x2u[b], o.x3u[b], o.x3ul[b], gc[b], gr, g, c);
 }
 
@@ -544,7 +544,7 @@ __device__ __forceinline__ void publish_minus(const V (&a)[K][Lay<BPL>::BX], con
 // Predict-shaped step over the tile (after the barrier).  Core rows top to
 // bottom, so row r+1 is still unmodified when row r reads it; the halo lanes
 // read only values taken before the step.
-template <int KIND, int EMASK, bool EDGE, int NW, int BPL, int K, typename V>
+template <int KIND, int EMASK, int NW, int BPL, int K, typename V>
 __device__ __forceinline__ void plus_step(V (&a)[K][Lay<BPL>::BX], V (&e)[8], TileLds<V, NW, BPL, K>& L, int lane,
                                           int wv, const Geo& g, const TileGeo<BPL>& tg, float c) {
     using Ly = Lay<BPL>;
@@ -586,13 +586,13 @@ __device__ __forceinline__ void plus_step(V (&a)[K][Lay<BPL>::BX], V (&e)[8], Ti
         PlusOps<V, BPL> o;
         if (r + 1 < K) gather_plus<BPL>(a[r], a[r + 1 < K ? r + 1 : r], R0[r], R2[r], R0[r + 1], o);
         else gather_plus<BPL>(a[r], dn, R0[r], R2[r], R0[r + 1], o);
-        apply_plus<KIND, (1 << BPL) - 1, EDGE, EDGE>(a[r], o, tg.gc, g.gr0 + r, g, c);
+        apply_plus<KIND, (1 << BPL) - 1>(a[r], o, tg.gc, g.gr0 + r, g, c);
     }
-    apply_plus<KIND, EMASK, EDGE, EDGE>(e, h, tg.ge, tg.gre, g, c);
+    apply_plus<KIND, EMASK>(e, h, tg.ge, tg.gre, g, c);
 }
 
 // Update-shaped step over the tile (after the barrier): core rows bottom to top.
-template <int KIND, int EMASK, bool EDGE, int NW, int BPL, int K, typename V>
+template <int KIND, int EMASK, int NW, int BPL, int K, typename V>
 __device__ __forceinline__ void minus_step(V (&a)[K][Lay<BPL>::BX], V (&e)[8], TileLds<V, NW, BPL, K>& L, int lane,
                                            int wv, const Geo& g, const TileGeo<BPL>& tg, float c) {
     using Ly = Lay<BPL>;
@@ -634,9 +634,9 @@ __device__ __forceinline__ void minus_step(V (&a)[K][Lay<BPL>::BX], V (&e)[8], T
         MinusOps<V, BPL> o;
         if (r > 0) gather_minus<BPL>(a[r], a[r > 0 ? r - 1 : 0], L1[r], L3[r + 1], L3[r], o);
         else gather_minus<BPL>(a[r], up, L1[r], L3[r + 1], L3[r], o);
-        apply_minus<KIND, (1 << BPL) - 1, EDGE, EDGE>(a[r], o, tg.gc, g.gr0 + r, g, c);
+        apply_minus<KIND, (1 << BPL) - 1>(a[r], o, tg.gc, g.gr0 + r, g, c);
     }
-    apply_minus<KIND, EMASK, EDGE, EDGE>(e, h, tg.ge, tg.gre, g, c);
+    apply_minus<KIND, EMASK>(e, h, tg.ge, tg.gre, g, c);
 }
 
 // Constant parts of the split (no neighbour access): separable lifting with
@@ -707,35 +707,23 @@ __device__ __forceinline__ void sync_horizontal() {
 // the fused steps (4 barriers for CDF 9/7, 2 for 5/3), the fused steps with
 // the split, the separable steps (8 and 4 barriers), or the fused steps
 // evaluated as their horizontal and vertical factors (4 and 2 barriers).
-template <int DIR, int WAV, bool EDGE, int SCH, int NW, int BPL, int K, typename V>
+template <int DIR, int WAV, int SCH, int NW, int BPL, int K, typename V>
 __device__ __forceinline__ void run(V (&a)[K][Lay<BPL>::BX], V (&e)[8], TileLds<V, NW, BPL, K>& L, int lane, int wv,
                                     const Geo& g, const TileGeo<BPL>& tg) {
-    // the slots no wave publishes to hold zeros (the transposed border
-    // weights multiply values beyond the tile by 0, which must stay finite)
-    if (wv == NW - 1) {
-#pragma unroll
-        for (int q = 0; q < Lay<BPL>::NG; ++q) L.t[NW][q][lane] = Vec4<V>{V(0), V(0), V(0), V(0)};
-        if (lane < 2) L.et[NW][lane] = Vec4<V>{V(0), V(0), V(0), V(0)};
-    }
-    if (wv == 0) {
-#pragma unroll
-        for (int q = 0; q < Lay<BPL>::NG; ++q) L.s[0][q][lane] = Vec4<V>{V(0), V(0), V(0), V(0)};
-        if (lane < 2) L.es[0][lane] = Vec4<V>{V(0), V(0), V(0), V(0)};
-    }
 #define DWT2_PLUS(KIND_, M_, c_) publish_plus<NW, BPL, K>(a, e, L, lane, wv); __syncthreads(); \
-    plus_step<KIND_, M_, EDGE, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
+    plus_step<KIND_, M_, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
 #define DWT2_MINUS(KIND_, M_, c_) publish_minus<NW, BPL, K>(a, e, L, lane, wv); __syncthreads(); \
-    minus_step<KIND_, M_, EDGE, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
+    minus_step<KIND_, M_, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
     // separable steps publish only what their axis reads: exchange columns
     // (horizontal) or edge rows (vertical)
 #define DWT2_PH(KIND_, M_, c_) publish_plus<NW, BPL, K, true, false>(a, e, L, lane, wv); sync_horizontal<SCH>(); \
-    plus_step<KIND_, M_, EDGE, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
+    plus_step<KIND_, M_, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
 #define DWT2_PV(KIND_, M_, c_) publish_plus<NW, BPL, K, false, true>(a, e, L, lane, wv); __syncthreads(); \
-    plus_step<KIND_, M_, EDGE, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
+    plus_step<KIND_, M_, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
 #define DWT2_MH(KIND_, M_, c_) publish_minus<NW, BPL, K, true, false>(a, e, L, lane, wv); sync_horizontal<SCH>(); \
-    minus_step<KIND_, M_, EDGE, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
+    minus_step<KIND_, M_, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
 #define DWT2_MV(KIND_, M_, c_) publish_minus<NW, BPL, K, false, true>(a, e, L, lane, wv); __syncthreads(); \
-    minus_step<KIND_, M_, EDGE, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
+    minus_step<KIND_, M_, NW, BPL, K>(a, e, L, lane, wv, g, tg, (c_));
     // halo masks (first halo block = 1, second = 2) per step, from the column ranges each stage
     // must cover: predict/update/predict/update -> 3, 3, 2, 0;
     // update/predict/update/predict -> 3, 3, 1, 0; predict/update -> 2, 0;
@@ -834,12 +822,13 @@ __device__ __forceinline__ void run(V (&a)[K][Lay<BPL>::BX], V (&e)[8], TileLds<
         }
     } else {
         // W^T = T_1^T S_1^T T_2^T S_2^T Z: transposed steps in reverse order;
-        // the transpose of an update is predict-shaped and vice versa.
+        // the transpose of an update is predict-shaped and vice versa.  The
+        // transposed border weights: scale_edges().
         scale(a, e, kZeta2, kZetaM2);
-        DWT2_PLUS(kAdj, 3, kDelta)
-        DWT2_MINUS(kAdj, 3, kGamma)
-        DWT2_PLUS(kAdj, 2, kBeta)
-        DWT2_MINUS(kAdj, 0, kAlpha)
+        DWT2_PLUS(kFloat, 3, kDelta)
+        DWT2_MINUS(kFloat, 3, kGamma)
+        DWT2_PLUS(kFloat, 2, kBeta)
+        DWT2_MINUS(kFloat, 0, kAlpha)
     }
 #undef DWT2_PLUS
 #undef DWT2_MINUS
@@ -1030,6 +1019,57 @@ __device__ __forceinline__ void fold(int (&p)[N], int n) {
     } while (--times > 0);
 }
 
+// The adjoint's border weights.  The transpose of a lifting step with the
+// whole-point extension weights the end samples: x[0] of a component that starts
+// the signal takes its one neighbour once, where the extension would take it
+// twice, and the sample that ends the signal counts twice in its neighbour.  Both
+// are the plain step on the extension if the first and the last sample of the
+// signal are held doubled: W^T = D^-1 S D with S the steps on the symmetric
+// extension and D = 2 at the two ends of each axis (4 in the corners).  So a
+// border tile doubles those samples after its load (f = 2), runs the same steps
+// as an interior tile and halves them before its store (f = 1/2); both are exact,
+// and every value is the weighted step's, bit for bit (up to overflow and
+// subnormal numbers at the ends).  A border step program with the weights cost a
+// dozen operations more a block and step and twice the code: 192 planes of 256^2
+// FP32, 3 levels, took 46.8 us, now 39.2; 8192^2, 2 levels, 112.7, now 101.6 (BF16
+// 102, now 73).
+// rows, cols: the (folded) positions of a's samples; components K0 .. K1 - 1.
+template <int K0, int K1, int BPL, int K, typename V>
+__device__ __forceinline__ void scale_edges(V (&a)[K][4 * BPL], const int (&rows)[2 * K], const int (&cols)[2 * BPL],
+                                            int h, int w, float f) {
+#pragma unroll
+    for (int b = 0; b < BPL; ++b)
+#pragma unroll
+        for (int k = K0; k < K1; ++k) {
+            const int c = cols[2 * b + (k & 1)];
+            const float s = c == 0 || c == w - 1 ? f : 1.f;
+#pragma unroll
+            for (int r = 0; r < K; ++r) a[r][4 * b + k] *= s;
+        }
+#pragma unroll
+    for (int r = 0; r < K; ++r)
+#pragma unroll
+        for (int i = K0 >> 1; i <= (K1 - 1) >> 1; ++i) {
+            const int p = rows[2 * r + i];
+            if (p != 0 && p != h - 1) continue;
+#pragma unroll
+            for (int b = 0; b < BPL; ++b)
+#pragma unroll
+                for (int k = K0; k < K1; ++k)
+                    if ((k >> 1) == i) a[r][4 * b + k] *= f;
+        }
+}
+// The same at the positions of the lane's blocks as they are (not folded).
+template <int K0, int K1, int BPL, int K, typename V>
+__device__ __forceinline__ void scale_edges(V (&a)[K][4 * BPL], const Geo& g, int h, int w, float f) {
+    int rows[2 * K], cols[2 * BPL];
+#pragma unroll
+    for (int i = 0; i < 2 * K; ++i) rows[i] = 2 * g.gr0 + i;
+#pragma unroll
+    for (int i = 0; i < 2 * BPL; ++i) cols[i] = 2 * g.gcL + i;
+    scale_edges<K0, K1, BPL>(a, rows, cols, h, w, f);
+}
+
 // The lane's sample `off` bytes into a uniform row: the row pointer stays in
 // SGPRs and the lane's offset, the same for every row, in one VGPR.
 template <typename Q>
@@ -1123,8 +1163,7 @@ __device__ __forceinline__ void load_tile(typename St<T>::V (&a)[K][Lay<BPL>::BX
 // clamps.  Each step keeps the extension symmetric, and every sum a step
 // forms pairs the same two values as the clamped step at the same place, so
 // every coefficient equals the clamped computation bit for bit.  The
-// adjoint's border weights are not a symmetric extension: its samples outside
-// the image are 0.
+// adjoint takes the inverse's extension, of samples scale_edges() has doubled.
 // A wave's rows are uniform, so their extension costs scalar instructions
 // only, and every lane whose columns lie inside the image loads vectors; a
 // lane at or past the right end loads single samples.  Small levels consist
@@ -1137,7 +1176,6 @@ __device__ __forceinline__ void load_tile_border(typename St<T>::V (&a)[K][Lay<B
                                                  const LevelParams& P, const Geo& g, const TileGeo<BPL>& tg,
                                                  int lane) {
     using V = typename St<T>::V;
-    constexpr bool kZero = DIR == kAdjoint;
     const bool halo_lane = lane < 32 && tg.re < K;
     int rows[2 * K], cols[2 * BPL], hr[2], hc[4];
 #pragma unroll
@@ -1148,11 +1186,9 @@ __device__ __forceinline__ void load_tile_border(typename St<T>::V (&a)[K][Lay<B
     for (int i = 0; i < 2; ++i) hr[i] = 2 * tg.gre + i;
 #pragma unroll
     for (int i = 0; i < 4; ++i) hc[i] = 2 * tg.ge[0] + i;
-    if constexpr (!kZero) {
-        fold(rows, P.h);
-        fold(hr, P.h);
-        fold(hc, P.w);
-    }
+    fold(rows, P.h);
+    fold(hr, P.h);
+    fold(hc, P.w);
     if constexpr (DIR == kForward) {
         const T* in = static_cast<const T*>(P.in);
         const bool full = cols[2 * BPL - 1] < P.w;
@@ -1192,49 +1228,35 @@ __device__ __forceinline__ void load_tile_border(typename St<T>::V (&a)[K][Lay<B
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     V v[BPL];
-                    const int p = rows[2 * r + (k >> 1)];
-                    if (kZero && (p < 0 || p >= P.h)) {
-#pragma unroll
-                        for (int b = 0; b < BPL; ++b) v[b] = V(0);
-                    } else {
-                        load_vec<T, BPL>(lane_at(subband_row(ll, P.in_ll_pitch, det, P.in_pitch, g, k, p >> 1) + g.cb0,
-                                                 (uint32_t)lane * (BPL * sizeof(T))), v);
-                    }
+                    load_vec<T, BPL>(lane_at(subband_row(ll, P.in_ll_pitch, det, P.in_pitch, g, k,
+                                                         rows[2 * r + (k >> 1)] >> 1) + g.cb0,
+                                             (uint32_t)lane * (BPL * sizeof(T))), v);
 #pragma unroll
                     for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = v[b];
                 }
         } else {
-            if constexpr (!kZero) fold(cols, P.w);
+            fold(cols, P.w);
 #pragma unroll
             for (int r = 0; r < K; ++r)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const int p = rows[2 * r + (k >> 1)];
-                    const bool row_ok = !kZero || (p >= 0 && p < P.h);
-                    const T* row = subband_row(ll, P.in_ll_pitch, det, P.in_pitch, g, k, row_ok ? p >> 1 : 0);
+                    const T* row = subband_row(ll, P.in_ll_pitch, det, P.in_pitch, g, k, rows[2 * r + (k >> 1)] >> 1);
 #pragma unroll
-                    for (int b = 0; b < BPL; ++b) {
-                        const int c = cols[2 * b + (k & 1)];
-                        V v = V(0);
-                        if (!kZero || (row_ok && c < P.w)) v = load_at(row, c >> 1);
-                        a[r][4 * b + k] = v;
-                    }
+                    for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = load_at(row, cols[2 * b + (k & 1)] >> 1);
                 }
         }
         if (halo_lane) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int p = hr[k >> 1];
-                const bool row_ok = !kZero || (p >= 0 && p < P.h);
-                const T* row = subband_row(ll, P.in_ll_pitch, det, P.in_pitch, g, k, row_ok ? p >> 1 : 0);
+                const T* row = subband_row(ll, P.in_ll_pitch, det, P.in_pitch, g, k, hr[k >> 1] >> 1);
 #pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const int c = hc[2 * b + (k & 1)];
-                    V v = V(0);
-                    if (!kZero || (row_ok && c >= 0 && c < P.w)) v = St<T>::load(row[c >> 1]);
-                    e[4 * b + k] = v;
-                }
+                for (int b = 0; b < 2; ++b) e[4 * b + k] = St<T>::load(row[hc[2 * b + (k & 1)] >> 1]);
             }
+        }
+        if constexpr (DIR == kAdjoint) {
+            scale_edges<0, 4, BPL>(a, rows, cols, P.h, P.w, 2.f);
+            V(&h)[1][8] = reinterpret_cast<V(&)[1][8]>(e);
+            scale_edges<0, 4, 2>(h, hr, hc, P.h, P.w, 2.f);
         }
     }
 }
@@ -1346,24 +1368,26 @@ __device__ __forceinline__ void tile_body(const LevelParams& P, int tx, int ty,
     V e[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) e[q] = V(0);
-    if constexpr (DIR == kAdjoint || SCH == kSchemeSplit) {
-        // border tiles run another step program: the adjoint's with the
-        // transposed border weights, the split's without the split
+    if constexpr (SCH == kSchemeSplit) {
+        // border tiles run another step program, without the split
         if (interior) {
             load_tile<DIR, T, BPL>(a, e, P, g, tg, lane);
-            run<DIR, WAV, false, SCH, NW, BPL>(a, e, lds, lane, wv, g, tg);
+            run<DIR, WAV, SCH, NW, BPL>(a, e, lds, lane, wv, g, tg);
             store_tile<DIR, T, false, NW, BPL, K, LLC, LLX>(a, P, g, lane, wv);
         } else {
             load_tile_border<DIR, T, BPL>(a, e, P, g, tg, lane);
-            run<DIR, WAV, DIR == kAdjoint, kSchemeFused, NW, BPL>(a, e, lds, lane, wv, g, tg);
+            run<DIR, WAV, kSchemeFused, NW, BPL>(a, e, lds, lane, wv, g, tg);
             store_tile<DIR, T, true, NW, BPL, K, false, LLX>(a, P, g, lane, wv);
         }
     } else {
         if (interior) load_tile<DIR, T, BPL>(a, e, P, g, tg, lane);
         else load_tile_border<DIR, T, BPL>(a, e, P, g, tg, lane);
-        run<DIR, WAV, false, SCH, NW, BPL>(a, e, lds, lane, wv, g, tg);
+        run<DIR, WAV, SCH, NW, BPL>(a, e, lds, lane, wv, g, tg);
         if (interior) store_tile<DIR, T, false, NW, BPL, K, LLC, LLX>(a, P, g, lane, wv);
-        else store_tile<DIR, T, true, NW, BPL, K, false, LLX>(a, P, g, lane, wv);
+        else {
+            if constexpr (DIR == kAdjoint) scale_edges<0, 4, BPL>(a, g, P.h, P.w, 0.5f);
+            store_tile<DIR, T, true, NW, BPL, K, false, LLX>(a, P, g, lane, wv);
+        }
     }
 }
 

@@ -27,8 +27,7 @@ namespace pair {
 // horizontal neighbours are DPP shifts that fold into the adds, vertical ones
 // the lane's own rows or one LDS row per wave and step.
 //
-// Borders.  Level 1 runs on the symmetric extension of its input (the
-// adjoint: on zeros and its border weights).  The LL samples this gives outside
+// Borders.  Level 1 runs on the symmetric extension of its input.  The LL samples this gives outside
 // the image are not what level 2 extends them to when a side is even, so a
 // border tile passes its LL samples through LDS and each lane takes the
 // reflected ones.  Every value is formed by the same operations in the same
@@ -53,7 +52,7 @@ constexpr bool vertical_kind(int k) { return k == kSepV || k == kSepVInt || k ==
 
 // Predict-shaped step: rows top to bottom, blocks left to right, so every
 // operand right of or below a block is still the value before the step.
-template <int KIND, bool EDGE, int NW, int BPL, int K, typename V>
+template <int KIND, int NW, int BPL, int K, typename V>
 __device__ __forceinline__ void plus(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int lane, int wv, const Geo& g, float c) {
     V dn[4 * BPL];
 #pragma unroll
@@ -77,7 +76,7 @@ __device__ __forceinline__ void plus(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int 
         const V RD0 = vertical_kind(KIND) || horizontal_kind(KIND) ? V(0) : right1(d[0]);
 #pragma unroll
         for (int b = 0; b < BPL; ++b)
-            plus_block<KIND, EDGE, EDGE>(a[r][4 * b], a[r][4 * b + 1], a[r][4 * b + 2], a[r][4 * b + 3],
+            plus_block<KIND, false, false>(a[r][4 * b], a[r][4 * b + 1], a[r][4 * b + 2], a[r][4 * b + 3],
                                          b + 1 < BPL ? a[r][4 * ((b + 1) % BPL)] : R0,
                                          b + 1 < BPL ? a[r][4 * ((b + 1) % BPL) + 2] : R2, d[4 * b], d[4 * b + 1],
                                          b + 1 < BPL ? d[4 * ((b + 1) % BPL)] : RD0, g.gcL + b, g.gr0 + r, g, c);
@@ -85,7 +84,7 @@ __device__ __forceinline__ void plus(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int 
 }
 
 // Update-shaped step: rows bottom to top, blocks right to left.
-template <int KIND, bool EDGE, int NW, int BPL, int K, typename V>
+template <int KIND, int NW, int BPL, int K, typename V>
 __device__ __forceinline__ void minus(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int lane, int wv, const Geo& g, float c) {
     V up[4 * BPL];
 #pragma unroll
@@ -109,7 +108,7 @@ __device__ __forceinline__ void minus(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int
         const V LU3 = vertical_kind(KIND) || horizontal_kind(KIND) ? V(0) : left1(u[4 * BPL - 1]);
 #pragma unroll
         for (int b = BPL - 1; b >= 0; --b)
-            minus_block<KIND, EDGE, EDGE>(a[r][4 * b], a[r][4 * b + 1], a[r][4 * b + 2], a[r][4 * b + 3],
+            minus_block<KIND, false, false>(a[r][4 * b], a[r][4 * b + 1], a[r][4 * b + 2], a[r][4 * b + 3],
                                           b > 0 ? a[r][4 * ((b + BPL - 1) % BPL) + 1] : L1,
                                           b > 0 ? a[r][4 * ((b + BPL - 1) % BPL) + 3] : L3, u[4 * b + 2], u[4 * b + 3],
                                           b > 0 ? u[4 * ((b + BPL - 1) % BPL) + 3] : LU3, g.gcL + b, g.gr0 + r, g, c);
@@ -131,11 +130,11 @@ __device__ __forceinline__ void scale_bands(V (&a)[K][4 * BPL], float s0, float 
 // fused and factored schemes).  Predict- and update-shaped steps alternate
 // over both levels, and each shape has its own LDS rows, so the one barrier of
 // a step also orders the rows' reuse.
-template <int DIR, int WAV, int SCH, bool EDGE, int NW, int BPL, int K, typename V>
+template <int DIR, int WAV, int SCH, int NW, int BPL, int K, typename V>
 __device__ __forceinline__ void steps(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int lane, int wv, const Geo& g) {
     static_assert(SCH == kSchemeFused || SCH == kSchemeFactored, "default schemes");
-#define DWT2_P(KIND_, c_) plus<KIND_, EDGE, NW, BPL, K>(a, L, lane, wv, g, (c_));
-#define DWT2_M(KIND_, c_) minus<KIND_, EDGE, NW, BPL, K>(a, L, lane, wv, g, (c_));
+#define DWT2_P(KIND_, c_) plus<KIND_, NW, BPL, K>(a, L, lane, wv, g, (c_));
+#define DWT2_M(KIND_, c_) minus<KIND_, NW, BPL, K>(a, L, lane, wv, g, (c_));
     if constexpr (WAV == kCdf53) {
         static_assert(SCH == kSchemeFused, "the integer wavelet's default scheme");
         if constexpr (DIR == kForward) { DWT2_P(kIntFwd, 0.f) DWT2_M(kIntFwd, 0.f) }
@@ -168,7 +167,7 @@ __device__ __forceinline__ void steps(V (&a)[K][4 * BPL], PairLds<V, NW>& L, int
         }
     } else {
         scale_bands<BPL, K>(a, kZeta2, kZetaM2);
-        DWT2_P(kAdj, kDelta) DWT2_M(kAdj, kGamma) DWT2_P(kAdj, kBeta) DWT2_M(kAdj, kAlpha)
+        DWT2_P(kFloat, kDelta) DWT2_M(kFloat, kGamma) DWT2_P(kFloat, kBeta) DWT2_M(kFloat, kAlpha)
     }
 #undef DWT2_P
 #undef DWT2_M
@@ -232,8 +231,8 @@ __device__ __forceinline__ void store_band_row(T* p, const typename St<T>::V (&v
 }
 
 // The bands K0 .. 3 of a tile of a pyramid level (h x w; inverse and adjoint).
-// ZERO: samples outside the level are 0 (adjoint).
-template <typename T, bool ZERO, int K0, int BPL, int K>
+// ADJ: the adjoint's, the end samples of each axis doubled in a border tile.
+template <typename T, bool ADJ, int K0, int BPL, int K>
 __device__ __forceinline__ void load_bands(typename St<T>::V (&a)[K][4 * BPL], const T* ll, int64_t ll_pitch,
                                            const T* det, int64_t pitch, int h, int w, const Geo& g, bool interior,
                                            int lane) {
@@ -241,41 +240,35 @@ __device__ __forceinline__ void load_bands(typename St<T>::V (&a)[K][4 * BPL], c
     int rows[2 * K];
 #pragma unroll
     for (int i = 0; i < 2 * K; ++i) rows[i] = 2 * g.gr0 + i;
-    if (!ZERO && !interior) fold_both(rows, h);
-    const int c0 = 2 * g.gcL;
-    if (interior || (c0 >= 0 && c0 + 2 * BPL <= w)) {
+    if (!interior) fold_both(rows, h);
+    int cols[2 * BPL];
+#pragma unroll
+    for (int i = 0; i < 2 * BPL; ++i) cols[i] = 2 * g.gcL + i;
+    if (interior || (cols[0] >= 0 && cols[2 * BPL - 1] < w)) {
 #pragma unroll
         for (int r = 0; r < K; ++r)
 #pragma unroll
             for (int k = K0; k < 4; ++k) {
                 V v[BPL];
-                const int p = rows[2 * r + (k >> 1)];
-                const bool ok = !ZERO || interior || (p >= 0 && p < h);
-                load_band_row<T, BPL>(v, lane_at(subband_row(ll, ll_pitch, det, pitch, g, k, ok ? p >> 1 : 0) + g.cb0,
+                load_band_row<T, BPL>(v, lane_at(subband_row(ll, ll_pitch, det, pitch, g, k,
+                                                             rows[2 * r + (k >> 1)] >> 1) + g.cb0,
                                                  (uint32_t)lane * (BPL * sizeof(T))));
 #pragma unroll
-                for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = ok ? v[b] : V(0);
+                for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = v[b];
             }
     } else {
-        int cols[2 * BPL];
-#pragma unroll
-        for (int i = 0; i < 2 * BPL; ++i) cols[i] = c0 + i;
-        if constexpr (!ZERO) fold_both(cols, w);
+        fold_both(cols, w);
 #pragma unroll
         for (int r = 0; r < K; ++r)
 #pragma unroll
             for (int k = K0; k < 4; ++k) {
-                const int p = rows[2 * r + (k >> 1)];
-                const bool ok = !ZERO || (p >= 0 && p < h);
-                const T* row = subband_row(ll, ll_pitch, det, pitch, g, k, ok ? p >> 1 : 0);
+                const T* row = subband_row(ll, ll_pitch, det, pitch, g, k, rows[2 * r + (k >> 1)] >> 1);
 #pragma unroll
-                for (int b = 0; b < BPL; ++b) {
-                    const int c = cols[2 * b + (k & 1)];
-                    V v = V(0);
-                    if (!ZERO || (ok && c >= 0 && c < w)) v = load_at(row, c >> 1);
-                    a[r][4 * b + k] = v;
-                }
+                for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = load_at(row, cols[2 * b + (k & 1)] >> 1);
             }
+    }
+    if constexpr (ADJ) {
+        if (!interior) scale_edges<K0, 4, BPL>(a, rows, cols, h, w, 2.f);
     }
 }
 
@@ -365,6 +358,30 @@ __device__ __forceinline__ void store_image(typename St<T>::V (&a)[K][4 * BPL], 
 
 __device__ __forceinline__ int clamp_to(int x, int n) { return x < 0 ? 0 : x < n ? x : n - 1; }
 
+// LL samples of a border tile's blocks (inverse and adjoint): each at its
+// reflected pixel position of the h x w level, `ll(row, col)` being the block's;
+// the adjoint's doubled at the ends of an axis (adj: 2, see scale_edges()).
+template <int BPL, int K, bool ADJ, typename V, typename F>
+__device__ __forceinline__ void reflect_ll(V (&a)[K][4 * BPL], const Geo& g, int h, int w, float adj, const F& ll) {
+    int rows[K], cols[BPL];
+#pragma unroll
+    for (int i = 0; i < K; ++i) rows[i] = 2 * (g.gr0 + i);
+#pragma unroll
+    for (int i = 0; i < BPL; ++i) cols[i] = 2 * (g.gcL + i);
+    fold_both(rows, h);
+    fold_both(cols, w);
+#pragma unroll
+    for (int r = 0; r < K; ++r)
+#pragma unroll
+        for (int b = 0; b < BPL; ++b) {
+            a[r][4 * b] = ll(rows[r] >> 1, cols[b] >> 1);
+            if constexpr (ADJ) {
+                a[r][4 * b] *= rows[r] == 0 || rows[r] == h - 1 ? adj : 1.f;
+                a[r][4 * b] *= cols[b] == 0 || cols[b] == w - 1 ? adj : 1.f;
+            }
+        }
+}
+
 // What storing a value and loading it again gives.
 template <typename T>
 __device__ __forceinline__ typename St<T>::V stored(typename St<T>::V v) { return St<T>::load(St<T>::store(v)); }
@@ -394,7 +411,7 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
     V a[K][8], b[K2][4];
     if constexpr (DIR == kForward) {
         load_image<T, 2, K>(a, static_cast<const T*>(P.in), P.in_pitch, P.h, P.w, g, interior, lane);
-        steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        steps<DIR, WAV, SCH, NW, 2, K>(a, L, lane, wv, g);
         T* const out = static_cast<T*>(P.out);
         if (core_lane) store_bands<T, 1, kHalo2, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
 #pragma unroll
@@ -420,60 +437,37 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
                 for (int k = 0; k < 4; ++k)
                     b[r][k] = S.p[clamp_to(rows[2 * r + (k >> 1)] - r0, R)][clamp_to(cols[k & 1] - g.cb0, 2 * kLanes)];
         }
-        steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+        steps<DIR, WAV, SCH, NW, 1, K2>(b, L, lane, wv, g2);
         T* const ll = static_cast<T*>(P.ll);
         if (core_lane) store_bands<T, 0, kHalo2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
     } else {
-        constexpr bool kZero = DIR == kAdjoint;
+        constexpr bool kAdj = DIR == kAdjoint;
         const T* const det = static_cast<const T*>(P.in);
-        load_bands<T, kZero, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2,
-                                       interior, lane);
-        load_bands<T, kZero, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
-        if constexpr (kZero) {
-            // the transposed border weights multiply rows beyond the tile by 0, which must stay finite
-            if (wv == NW - 1) L.t[NW][0][lane] = L.t[NW][1][lane] = Vec2<V>{V(0), V(0)};
-            if (wv == 0) L.s[0][0][lane] = L.s[0][1][lane] = Vec2<V>{V(0), V(0)};
-            if (interior) steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
-            else steps<DIR, WAV, SCH, true, NW, 1, K2>(b, L, lane, wv, g2);
-        } else {
-            steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+        load_bands<T, kAdj, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2, interior,
+                                      lane);
+        load_bands<T, kAdj, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        steps<DIR, WAV, SCH, NW, 1, K2>(b, L, lane, wv, g2);
+        if constexpr (kAdj) {
+            if (!interior) scale_edges<0, 4, 1>(b, g2, h2, w2, 0.5f);
         }
 #pragma unroll
         for (int r = 0; r < K2; ++r)
 #pragma unroll
             for (int k = 0; k < 4; ++k) a[2 * r + (k >> 1)][4 * (k & 1)] = stored<T>(b[r][k]);
         if (!interior) {
-            if constexpr (kZero) {
 #pragma unroll
-                for (int r = 0; r < K; ++r)
+            for (int r = 0; r < K; ++r)
 #pragma unroll
-                    for (int c = 0; c < 2; ++c) {
-                        const int gr = g.gr0 + r, gc = g.gcL + c;
-                        if (gr < 0 || gr >= h2 || gc < 0 || gc >= w2) a[r][4 * c] = V(0);
-                    }
-            } else {
-#pragma unroll
-                for (int r = 0; r < K; ++r)
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) S.p[wv * K + r][2 * lane + c] = a[r][4 * c];
-                __syncthreads();
-                // LL sample of block (gr, gc): at its reflected pixel position
-                int rows[K], cols[2];
-#pragma unroll
-                for (int i = 0; i < K; ++i) rows[i] = 2 * (g.gr0 + i);
-                cols[0] = 2 * g.gcL;
-                cols[1] = 2 * g.gcL + 2;
-                fold_both(rows, P.h);
-                fold_both(cols, P.w);
-#pragma unroll
-                for (int r = 0; r < K; ++r)
-#pragma unroll
-                    for (int c = 0; c < 2; ++c)
-                        a[r][4 * c] = S.p[clamp_to((rows[r] >> 1) - r0, R)][clamp_to((cols[c] >> 1) - g.cb0, 2 * kLanes)];
-            }
+                for (int c = 0; c < 2; ++c) S.p[wv * K + r][2 * lane + c] = a[r][4 * c];
+            __syncthreads();
+            reflect_ll<2, K, kAdj>(a, g, P.h, P.w, 2.f, [&](int row, int col) -> V {
+                return S.p[clamp_to(row - r0, R)][clamp_to(col - g.cb0, 2 * kLanes)];
+            });
         }
-        if (kZero && !interior) steps<DIR, WAV, SCH, true, NW, 2, K>(a, L, lane, wv, g);
-        else steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        steps<DIR, WAV, SCH, NW, 2, K>(a, L, lane, wv, g);
+        if constexpr (kAdj) {
+            if (!interior) scale_edges<0, 4, 2>(a, g, P.h, P.w, 0.5f);
+        }
         if (core_lane) {
             T* const out = static_cast<T*>(P.out);
             if (interior) store_image<T, false, kHalo2, NW, 2, K>(a, out, P.out_pitch, P.h, P.w, g, lane, wv);
@@ -491,7 +485,7 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
 // block rows and columns of level 1, rounded up to whole blocks of level 3.
 constexpr int kRows3 = 2;
 
-// Tile (tx, ty) of levels l, l + 1 and l + 2 (forward and inverse): 8 waves x 6
+// Tile (tx, ty) of levels l, l + 1 and l + 2: 8 waves x 6
 // rows, of which kTripleRows rows and kTripleCols block columns are stored.
 template <int DIR, int WAV, typename T, int SCH>
 __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairLds<typename St<T>::V, kTripleWaves>& L,
@@ -525,7 +519,7 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
     auto plane2 = [&](int row, int col) -> V& { return S.p[clamp_to(row - r0 / 2, R2)][clamp_to(col - c0 / 2, kLanes)]; };
     if constexpr (DIR == kForward) {
         load_image<T, 2, K>(a, static_cast<const T*>(P.in), P.in_pitch, P.h, P.w, g, interior, lane);
-        steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        steps<DIR, WAV, SCH, NW, 2, K>(a, L, lane, wv, g);
         T* const out = static_cast<T*>(P.out);
         if (core_lane) store_bands<T, 1, kHalo3, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
 #pragma unroll
@@ -550,7 +544,7 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
 #pragma unroll
                 for (int k = 0; k < 4; ++k) b[r][k] = plane1(rows[2 * r + (k >> 1)], cols[k & 1]);
         }
-        steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
+        steps<DIR, WAV, SCH, NW, 1, K2>(b, L, lane, wv, g2);
         if (core_lane) store_bands<T, 1, kHalo3 / 2, NW, 1, K2>(b, out, 0, out, P.out_pitch, g2, lane, wv);
         // the reads of plane 1 precede the barriers of level 2's steps
 #pragma unroll
@@ -567,18 +561,19 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
         for (int r = 0; r < kRows3; ++r)
 #pragma unroll
             for (int k = 0; k < 4; ++k) c[r][k] = plane2(rows[2 * r + (k >> 1)], cols[k & 1]);
-        steps<DIR, WAV, SCH, false, NW, 1, kRows3>(c, L, lane, wv, g3);
+        steps<DIR, WAV, SCH, NW, 1, kRows3>(c, L, lane, wv, g3);
         if (core_lane3)
             store_bands3<T, kHalo3 / 4, R / 4, kRows3>(c, static_cast<T*>(P.ll), P.ll_pitch, out, P.out_pitch, g3, lane,
                                                        wv);
     } else {
-        static_assert(DIR == kInverse, "the adjoint takes at most two levels a launch");
+        constexpr bool kAdj = DIR == kAdjoint;
         const T* const det = static_cast<const T*>(P.in);
-        load_bands<T, false, 0, 1, kRows3>(c, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h3, w3, g3, false,
-                                           lane);
-        load_bands<T, false, 1, 1, K2>(b, det, P.in_pitch, det, P.in_pitch, h2, w2, g2, interior, lane);
-        load_bands<T, false, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
-        steps<DIR, WAV, SCH, false, NW, 1, kRows3>(c, L, lane, wv, g3);
+        load_bands<T, kAdj, 0, 1, kRows3>(c, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h3, w3, g3, false,
+                                          lane);
+        load_bands<T, kAdj, 1, 1, K2>(b, det, P.in_pitch, det, P.in_pitch, h2, w2, g2, interior, lane);
+        load_bands<T, kAdj, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        steps<DIR, WAV, SCH, NW, 1, kRows3>(c, L, lane, wv, g3);
+        if constexpr (kAdj) scale_edges<0, 4, 1>(c, g3, h3, w3, 0.5f);
         if (lane < kLanes / 2) {
 #pragma unroll
             for (int r = 0; r < kRows3; ++r)
@@ -589,17 +584,12 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
                 }
         }
         __syncthreads();
-        {
-            // LL sample of block (gr, gc): at its reflected pixel position
-            int rows[K2], cols[1] = {2 * g2.gcL};
-#pragma unroll
-            for (int i = 0; i < K2; ++i) rows[i] = 2 * (g2.gr0 + i);
-            fold_both(rows, h2);
-            fold_both(cols, w2);
-#pragma unroll
-            for (int r = 0; r < K2; ++r) b[r][0] = plane2(rows[r] >> 1, cols[0] >> 1);
+        // an interior tile's level 2 is free of border weights, as its loads are
+        reflect_ll<1, K2, kAdj>(b, g2, h2, w2, interior ? 1.f : 2.f, plane2);
+        steps<DIR, WAV, SCH, NW, 1, K2>(b, L, lane, wv, g2);
+        if constexpr (kAdj) {
+            if (!interior) scale_edges<0, 4, 1>(b, g2, h2, w2, 0.5f);
         }
-        steps<DIR, WAV, SCH, false, NW, 1, K2>(b, L, lane, wv, g2);
 #pragma unroll
         for (int r = 0; r < K2; ++r)
 #pragma unroll
@@ -611,17 +601,12 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
 #pragma unroll
                 for (int q = 0; q < 2; ++q) S.p[wv * K + r][2 * lane + q] = a[r][4 * q];
             __syncthreads();
-            int rows[K], cols[2] = {2 * g.gcL, 2 * g.gcL + 2};
-#pragma unroll
-            for (int i = 0; i < K; ++i) rows[i] = 2 * (g.gr0 + i);
-            fold_both(rows, P.h);
-            fold_both(cols, P.w);
-#pragma unroll
-            for (int r = 0; r < K; ++r)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) a[r][4 * q] = plane1(rows[r] >> 1, cols[q] >> 1);
+            reflect_ll<2, K, kAdj>(a, g, P.h, P.w, 2.f, plane1);
         }
-        steps<DIR, WAV, SCH, false, NW, 2, K>(a, L, lane, wv, g);
+        steps<DIR, WAV, SCH, NW, 2, K>(a, L, lane, wv, g);
+        if constexpr (kAdj) {
+            if (!interior) scale_edges<0, 4, 2>(a, g, P.h, P.w, 0.5f);
+        }
         if (core_lane)
             store_image<T, true, kHalo3, NW, 2, K>(a, static_cast<T*>(P.out), P.out_pitch, P.h, P.w, g, lane, wv);
     }
@@ -685,12 +670,10 @@ hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
 
 template <int DIR, int WAV, typename T, int SCH>
 hipError_t launch(int levels, const PairParams& p, int planes, hipStream_t s) {
-    if constexpr (DIR != kAdjoint) {
-        if (levels == 3) return launch_shape<DIR, WAV, T, SCH, kTripleWaves, kTripleK, 3>(p, planes, s);
-        if (pair_rows((Direction)DIR, sizeof(T), pair_tiles(p.h, p.w, planes, 32), pair_tiles(p.h, p.w, planes, 48),
-                      (int64_t)p.h * p.w * planes) == 48)
-            return launch_shape<DIR, WAV, T, SCH, 8, 6>(p, planes, s);
-    }
+    if (levels == 3) return launch_shape<DIR, WAV, T, SCH, kTripleWaves, kTripleK, 3>(p, planes, s);
+    if (pair_rows((Direction)DIR, sizeof(T), pair_tiles(p.h, p.w, planes, 32), pair_tiles(p.h, p.w, planes, 48),
+                  (int64_t)p.h * p.w * planes) == 48)
+        return launch_shape<DIR, WAV, T, SCH, 8, 6>(p, planes, s);
     return launch_shape<DIR, WAV, T, SCH, 8, 4>(p, planes, s);
 }
 
@@ -711,7 +694,7 @@ hipError_t launch_float(Dtype dt, int levels, const PairParams& p, int planes, h
 }
 template <int DIR>
 hipError_t launch_dir(Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes, hipStream_t s) {
-    if (levels != 2 && (levels != 3 || DIR == kAdjoint)) return hipErrorInvalidValue;
+    if (levels != 2 && levels != 3) return hipErrorInvalidValue;
     if (wav == kCdf97) return launch_float<DIR, kCdf97>(dt, levels, p, planes, s);
     if constexpr (DIR != kAdjoint) {
         if (wav == kCdf53) return launch_t<DIR, kCdf53, int32_t>(levels, p, planes, s);

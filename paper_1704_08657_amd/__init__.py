@@ -174,12 +174,17 @@ def _check(x):
         raise ValueError("the last dimension must be contiguous")
 
 
+_raw_stream = None
+
+
 def _stream_ptr(x):
-    torch = _torch()
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)   # the current stream's handle, without a Stream object
-    if raw is not None:
-        return ctypes.c_void_p(raw(x.device.index))
-    return ctypes.c_void_p(torch.cuda.current_stream(x.device).cuda_stream)
+    """The current stream's handle, without a Stream object where torch offers that."""
+    global _raw_stream
+    if _raw_stream is None:
+        torch = _torch()
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+    return _raw_stream(x.get_device())
 
 
 def workspace(h: int, w: int, levels: int, dtype, device, planes: int = 1):
@@ -270,41 +275,42 @@ def _transform(fn, name, x, wavelet, levels, split, out, config=None, separable=
             raise ValueError("out must match the input's shape, dtype and device")
         if not out.is_contiguous():
             raise ValueError("out must be contiguous")
-    result = out
-    H, W = x.shape[-2], x.shape[-1]
-    if x.dim() == 2:                      # one plane: no reshaped views (per-call host time)
-        x2, planes = x, 1
-    else:
-        x2, out = x.reshape(-1, H, W), out.reshape(-1, H, W)
-        planes = x2.shape[0]
-    dt = dtype_code(x2)
-    stream = _stream_ptr(x2)
+    # both tensors are contiguous: planes of H rows of W samples, no reshaped
+    # views and strides to ask for (per-call host time)
+    shape = x.shape
+    H, W = shape[-2], shape[-1]
+    planes = 1
+    for n in shape[:-2]:
+        planes *= n
+    dt = dtype_code(x)
+    stream = _stream_ptr(x)
     flags = ((DWT2_FLAG_SPLIT if split else 0) | (DWT2_FLAG_SEPARABLE if separable else 0)
              | (DWT2_FLAG_FACTORED if factored else 0) | (DWT2_FLAG_POLYCONV if polyconv else 0)
              | (DWT2_FLAG_PERSISTENT if persistent else 0) | (DWT2_FLAG_FUSED if fused else 0))
     if config is None:
         config = tuned_config(_DIRECTIONS[name], wavelet, dt, H, W, levels)
-        scheme = ("split" if split else "separable" if separable else "factored" if factored
-                  else "polyconv" if polyconv else "fused")
-        if config is not None and not _config_ok(config, _DIRECTIONS[name], wavelet, scheme):
-            config = None                 # the library's default for this case
+        if config is not None:
+            scheme = ("split" if split else "separable" if separable else "factored" if factored
+                      else "polyconv" if polyconv else "fused")
+            if not _config_ok(config, _DIRECTIONS[name], wavelet, scheme):
+                config = None             # the library's default for this case
     if config is not None:
         flags |= DWT2_FLAG_KERNEL(config)
     # one call for all planes (at most 2^31 - 1 per call)
     step = (1 << 31) - 1
-    x_ptr, out_ptr, es = x2.data_ptr(), out.data_ptr(), x2.element_size()
-    xp, op = x2.stride(-2), out.stride(-2)                 # pitches
-    xs, os_ = (H * xp, H * op) if planes == 1 else (x2.stride(0), out.stride(0))
-    for p0 in range(0, planes, step):
+    x_ptr, out_ptr, es = x.data_ptr(), out.data_ptr(), x.element_size()
+    ps = H * W
+    for p0 in range(0, planes if ps else 1, step):         # an empty plane is the library's to refuse
         n = min(step, planes - p0)
-        w = ws if ws is not None else workspace(H, W, levels, dt, x2.device, n)
-        ws_ptr = ctypes.c_void_p(w.data_ptr() if w is not None else 0)
-        ws_n = w.numel() if w is not None else 0
-        st = fn(ctypes.c_void_p(x_ptr + p0 * xs * es), ctypes.c_void_p(out_ptr + p0 * os_ * es), n, xs, os_,
-                H, W, xp, op, dt, WAVELETS[wavelet], levels, DWT2_SYMMETRIC_WHOLE, flags, ws_ptr, ws_n, stream)
+        w = ws if ws is not None else workspace(H, W, levels, dt, x.device, n)
+        # plain integers: the argument types make the pointers (an object each
+        # costs the host more than the call's own checks)
+        st = fn(x_ptr + p0 * ps * es, out_ptr + p0 * ps * es, n, ps, ps, H, W, W, W, dt, WAVELETS[wavelet], levels,
+                DWT2_SYMMETRIC_WHOLE, flags, w.data_ptr() if w is not None else None,
+                w.numel() if w is not None else 0, stream)
         if st != DWT2_OK:
             raise DWT2Error(st, name)
-    return result
+    return out
 
 
 def fwd(x, wavelet: str = "cdf97", levels: int = 1, split: bool = False, out=None, config=None,

@@ -342,15 +342,14 @@ bool cached_output(dwt2::Direction dir, int32_t planes, int32_t h, int32_t w, si
 }
 
 // Levels the launch that starts at level l takes, in a call that names no
-// scheme and no kernel configuration: the last three, forward or inverse, while
-// their tiles all run at once (two work-groups on each of 256 CUs: 192 x 256 FP32
-// 10.3 us for 13.8 in two launches; past it the recomputed halo, three quarters
-// of a tile, costs more: 2048^2, 704 tiles, 19.8 for 17.4), else two where that
-// is the faster way.
+// scheme and no kernel configuration: the last three while their tiles all run
+// at once (triple_rows), else two where that is the faster way (pair_pays).
 int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int wavelet, unsigned flags,
                      int32_t planes) {
     if (flags != 0 || wavelet == DWT2_DD137 || l + 1 >= p.levels) return 1;
-    if (l + 3 == p.levels && dwt2::triple_tiles(p.h[l], p.w[l], planes) <= 512) return 3;
+    if (l + 3 == p.levels && dwt2::triple_rows(dir, dwt2::triple_tiles(p.h[l], p.w[l], planes, 48),
+                                               dwt2::triple_tiles(p.h[l], p.w[l], planes, 64)) > 0)
+        return 3;
     return dwt2::pair_pays(dir, to_dtype(dtype), p.h[l], p.w[l], planes) ? 2 : 1;
 }
 
@@ -358,15 +357,17 @@ int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int w
 // stack of planes (levels_in_launch), on the sums over the images.
 struct BatchPairStats {
     uint64_t tiles32, tiles48;    // two-level tiles of 32 and of 48 block rows
-    uint64_t tiles3;              // three-level tiles
+    uint64_t tiles3[2];           // three-level tiles of 48 and of 64 block rows
     uint64_t cols112, cols128;    // tiles across, two-level and one-level, weighted by the image's rows
     uint64_t samples;
 };
 void add_pair_stats(int32_t h, int32_t w, int levels, BatchPairStats* st) {
     for (int l = 0; l + 1 < levels; ++l) {
         int32_t tx, ty;
-        dwt2::multi_tile_grid(h, w, 3, 0, &tx, &ty);
-        st[l].tiles3 += (uint64_t)tx * (uint64_t)ty;
+        for (int i = 0; i < 2; ++i) {
+            dwt2::multi_tile_grid(h, w, 3, 48 + 16 * i, &tx, &ty);
+            st[l].tiles3[i] += (uint64_t)tx * (uint64_t)ty;
+        }
         dwt2::multi_tile_grid(h, w, 2, 32, &tx, &ty);
         st[l].tiles32 += (uint64_t)tx * (uint64_t)ty;
         dwt2::multi_tile_grid(h, w, 2, 48, &tx, &ty);
@@ -774,15 +775,15 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
     uint32_t launch_tiles[32];
     for (int l = 0; l < levels; ++B.n) {
         const BatchPairStats& st = stats[l];
-        const int n = !pairs || l + 1 >= levels ? 1
-                      : l + 3 == levels && st.tiles3 <= 512 ? 3
-                      : batch_pair_pays(dtype, st) ? 2 : 1;
-        const int rows = n != 2 ? 0 : dwt2::pair_rows(dwt2::kForward, es, (int64_t)st.tiles32, (int64_t)st.tiles48,
-                                                      (int64_t)st.samples);
+        const int rows3 = !pairs || l + 3 != levels ? 0
+                          : dwt2::triple_rows(dwt2::kForward, (int64_t)st.tiles3[0], (int64_t)st.tiles3[1]);
+        const int n = !pairs || l + 1 >= levels ? 1 : rows3 ? 3 : batch_pair_pays(dtype, st) ? 2 : 1;
+        const int rows = n != 2 ? rows3 : dwt2::pair_rows(dwt2::kForward, es, (int64_t)st.tiles32, (int64_t)st.tiles48,
+                                                          (int64_t)st.samples);
         B.first[B.n] = (int8_t)l;
         B.levels[B.n] = (int8_t)n;
         B.rows[B.n] = (int8_t)rows;
-        launch_tiles[B.n] = (uint32_t)(n == 1 ? tiles[l] : n == 3 ? st.tiles3 : rows == 32 ? st.tiles32 : st.tiles48);
+        launch_tiles[B.n] = (uint32_t)(n == 1 ? tiles[l] : n == 3 ? st.tiles3[rows == 64] : rows == 32 ? st.tiles32 : st.tiles48);
         l += n;
     }
     return report(dwt2::launch_fwd_batched_levels(to_dtype(dtype), sch, cfg, B, device_images, count, levels,

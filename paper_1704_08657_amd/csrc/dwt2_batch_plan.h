@@ -156,7 +156,7 @@ __host__ __device__ inline size_t image_ll_bytes(int32_t h, int32_t w, int level
 //   LL area                              per image: buffer A (LL of levels
 //                                        1, 3, ...), buffer B (levels 2, 4, ...)
 // The launches: launch j takes levels[j] levels (1, 2 or 3) from level first[j]
-// on; two in tiles of rows[j] block rows (halo included).  tile_off's row j
+// on; two or three in tiles of rows[j] block rows (halo included).  tile_off's row j
 // then holds the tiles of launch j.  The LL band that leaves launch j (but the
 // last) lies in buffer A for even j, B for odd j: A holds any of the image's
 // bands, B any but the first level's.
@@ -166,7 +166,7 @@ struct BatchLaunches {
 };
 __host__ __device__ inline void multi_tile_grid(int32_t hl, int32_t wl, int levels, int rows, int32_t* tx, int32_t* ty) {
     const int32_t nEr = (hl + 1) / 2, nEc = (wl + 1) / 2;
-    const int32_t cx = levels == 3 ? kTripleCols : kPairCols, cy = levels == 3 ? kTripleRows : rows - 2 * kHalo2;
+    const int32_t cx = levels == 3 ? kTripleCols : kPairCols, cy = rows - 2 * (levels == 3 ? kHalo3 : kHalo2);
     *tx = (nEc + cx - 1) / cx;
     *ty = (nEr + cy - 1) / cy;
 }

@@ -373,7 +373,7 @@ batched_multi_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
     P.ll_pitch = b.ll_pitch;
     const int ty = tt / P.tiles_x;
     const int tx = tt - ty * P.tiles_x;
-    if constexpr (LEVELS == 3) pair::tile3<kForward, kCdf97, T, SCH>(P, tx, ty, lds, plane, lane, wv);
+    if constexpr (LEVELS == 3) pair::tile3<kForward, kCdf97, T, SCH, NW>(P, tx, ty, lds, plane, lane, wv);
     else pair::tile<kForward, kCdf97, T, SCH, NW, K>(P, tx, ty, lds, plane, lane, wv);
 }
 
@@ -608,8 +608,10 @@ hipError_t launch_levels_shape(const BatchLaunches& B, const dwt2_image* dev_img
                                count, levels, j, l, tiles[j], w);
         else if constexpr (SCH != kMultiScheme)
             return hipErrorInvalidValue;
+        else if (B.levels[j] == 3 && B.rows[j] == 48)
+            DWT2_MULTI(12, kTripleK, 3);
         else if (B.levels[j] == 3)
-            DWT2_MULTI(kTripleWaves, kTripleK, 3);
+            DWT2_MULTI(16, kTripleK, 3);
         else if (B.rows[j] == 32)
             DWT2_MULTI(8, 4, 2);
         else

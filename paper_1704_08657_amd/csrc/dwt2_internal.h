@@ -163,15 +163,25 @@ inline bool pair_pays(Direction dir, Dtype dt, int32_t h, int32_t w, int32_t pla
     if (2 * ((nc + kPairCols - 1) / kPairCols) >= 3 * ((nc + 2 * kLanes - 1) / (2 * kLanes))) return false;
     return !(dir == kForward && (dt == kBF16 || dt == kF16) && (int64_t)h * w * planes > (1 << 26));
 }
-// Three levels: tiles of 8 waves x 6 block rows with a halo
-// of kHalo3 blocks on every side.
+// Three levels: tiles of 12 or 16 waves x 4 block rows with a halo of kHalo3
+// blocks on every side.
 constexpr int kHalo3 = 16;
-constexpr int kTripleWaves = 8, kTripleK = 6;
-constexpr int kTripleRows = kTripleWaves * kTripleK - 2 * kHalo3;
+constexpr int kTripleK = 4;
 constexpr int kTripleCols = 2 * kLanes - 2 * kHalo3;
-inline int64_t triple_tiles(int32_t h, int32_t w, int32_t planes) {
-    return (int64_t)(((w + 1) / 2 + kTripleCols - 1) / kTripleCols) *
-           (((h + 1) / 2 + kTripleRows - 1) / kTripleRows) * planes;
+inline int64_t triple_tiles(int32_t h, int32_t w, int32_t planes, int rows) {
+    const int cy = rows - 2 * kHalo3;
+    return (int64_t)(((w + 1) / 2 + kTripleCols - 1) / kTripleCols) * (((h + 1) / 2 + cy - 1) / cy) * planes;
+}
+// Block rows of the tiles that take the last three levels in one launch, 0 if
+// two launches are faster.  48 (12 waves) while every tile has a CU to itself
+// (1024^2 FP32 forward 9.6 us, 64 rows 11.4); then 64 (16 waves), which recompute
+// half of a tile instead of two thirds (1500^2 11.9 us, 48 rows 13.9; two launches 14.4), as
+// long as they too run alone, forward up to three on two CUs (192 planes of
+// 128^2, 384 tiles, 16.7 us, two launches 20.4; 2200^2, 420 tiles, 22.0, 18.6;
+// inverse of 1800^2, 290 tiles, 18.8, 17.5).
+inline int triple_rows(Direction dir, int64_t tiles48, int64_t tiles64) {
+    if (tiles48 <= 256) return 48;
+    return tiles64 <= (dir == kForward ? 384 : 256) ? 64 : 0;
 }
 // Enqueue `levels` (2 or 3) levels with the wavelet's default scheme.
 hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes,

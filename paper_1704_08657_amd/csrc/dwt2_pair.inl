@@ -310,25 +310,6 @@ __device__ __forceinline__ void store_bands(typename St<T>::V (&a)[K][4 * BPL], 
             }
 }
 
-// The same for the third level: ROWS block rows from the tile's first wave on, K
-// a wave, so the last waves may hold none.
-template <typename T, int H, int ROWS, int K>
-__device__ __forceinline__ void store_bands3(typename St<T>::V (&a)[K][4], T* ll, int64_t ll_pitch, T* det,
-                                             int64_t pitch, const Geo& g, int lane, int wv) {
-#pragma unroll
-    for (int r = 0; r < K; ++r) {
-        const int tr = wv * K + r;
-        if (tr < H || tr >= ROWS - H) continue;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (g.gr0 + r >= (k >= 2 ? g.nOr : g.nEr) || g.gcL >= ((k & 1) ? g.nOc : g.nEc)) continue;
-            const typename St<T>::V v[1] = {a[r][k]};
-            store_band_row<T, 1>(lane_at(subband_row(ll, ll_pitch, det, pitch, g, k, g.gr0 + r) + g.cb0,
-                                         (uint32_t)lane * (uint32_t)sizeof(T)), v);
-        }
-    }
-}
-
 // The tile's core as image rows (inverse and adjoint).
 template <typename T, bool BORDER, int H, int NW, int BPL, int K>
 __device__ __forceinline__ void store_image(typename St<T>::V (&a)[K][4 * BPL], T* out, int64_t pitch, int h, int w,
@@ -480,25 +461,27 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
 // For the last three levels of small images, where a launch costs more than the
 // work: 192 x 256, 3 levels, took a two-level launch of 7.3 us and a one-level
 // launch of 6.  Levels l and l + 1 as above; level l + 2 takes its samples from
-// LDS, a block a lane (32 blocks across) and kRows3 block rows a wave, with the
+// LDS, a block a lane (32 blocks across) and a block row a wave, with the
 // symmetric extension applied in the read.  The halo is that of three levels, 14
 // block rows and columns of level 1, rounded up to whole blocks of level 3.
-constexpr int kRows3 = 2;
-
-// Tile (tx, ty) of levels l, l + 1 and l + 2: 8 waves x 6
-// rows, of which kTripleRows rows and kTripleCols block columns are stored.
-template <int DIR, int WAV, typename T, int SCH>
-__device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairLds<typename St<T>::V, kTripleWaves>& L,
-                                      PairPlane<typename St<T>::V, kTripleWaves * kTripleK>& S, int lane, int wv) {
+// Four rows a wave, the fewest that are whole blocks of level 3: what such a
+// launch costs is one wave's instructions, each fetched and waited for, so
+// 12 waves x 4 rows beat 8 x 6 at the same tile (192 x 256 FP32 forward 9.3 us
+// for 10.4, inverse 10.9 for 11.8).
+//
+// Tile (tx, ty) of levels l, l + 1 and l + 2: NW waves x 4 rows, of which all but
+// the halo and kTripleCols block columns are stored.
+template <int DIR, int WAV, typename T, int SCH, int NW>
+__device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairLds<typename St<T>::V, NW>& L,
+                                      PairPlane<typename St<T>::V, NW * kTripleK>& S, int lane, int wv) {
     using V = typename St<T>::V;
-    constexpr int NW = kTripleWaves, K = kTripleK, K2 = K / 2, R = NW * K, R2 = R / 2;
-    static_assert(NW * kRows3 >= R / 4, "level 3's block rows");
+    constexpr int K = kTripleK, K2 = K / 2, R = NW * K, R2 = R / 2;
     Geo g, g2, g3;
     const int h2 = (P.h + 1) >> 1, w2 = (P.w + 1) >> 1, h3 = (h2 + 1) >> 1, w3 = (w2 + 1) >> 1;
     g.nEr = h2; g.nOr = P.h >> 1; g.nEc = w2; g.nOc = P.w >> 1;
     g2.nEr = h3; g2.nOr = h2 >> 1; g2.nEc = w3; g2.nOc = w2 >> 1;
     g3.nEr = (h3 + 1) >> 1; g3.nOr = h3 >> 1; g3.nEc = (w3 + 1) >> 1; g3.nOc = w3 >> 1;
-    const int r0 = ty * kTripleRows - kHalo3, c0 = tx * kTripleCols - kHalo3;   // multiples of 4
+    const int r0 = ty * (R - 2 * kHalo3) - kHalo3, c0 = tx * kTripleCols - kHalo3;   // multiples of 4
     g.cb0 = c0;
     g.gcL = c0 + 2 * lane;
     g.gr0 = r0 + wv * K;
@@ -507,12 +490,12 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
     g2.gr0 = g.gr0 / 2;
     g3.cb0 = c0 / 4;
     g3.gcL = g3.cb0 + lane;
-    g3.gr0 = r0 / 4 + wv * kRows3;
+    g3.gr0 = r0 / 4 + wv;
     const bool interior = r0 >= 0 && c0 >= 0 && r0 + R <= g.nOr && c0 + 2 * kLanes <= g.nOc;
     constexpr int kEl = kHalo3 / 2;                // halo lanes of levels 1 and 2; half as many at level 3
     const bool core_lane = lane >= kEl && lane < kLanes - kEl;
     const bool core_lane3 = lane >= kEl / 2 && lane < kLanes / 2 - kEl / 2;
-    V a[K][8], b[K2][4], c[kRows3][4];
+    V a[K][8], b[K2][4], c[1][4];
     // LL samples of level 1 for level 2 (forward) or back (inverse), see tile()
     auto plane1 = [&](int row, int col) -> V& { return S.p[clamp_to(row - r0, R)][clamp_to(col - c0, 2 * kLanes)]; };
     // those of level 2 for level 3: R2 rows of 64, in the same LDS rows
@@ -550,38 +533,26 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
 #pragma unroll
         for (int r = 0; r < K2; ++r) S.p[wv * K2 + r][lane] = stored<T>(b[r][0]);
         __syncthreads();
-        int rows[2 * kRows3], cols[2];
-#pragma unroll
-        for (int i = 0; i < 2 * kRows3; ++i) rows[i] = 2 * g3.gr0 + i;
-        cols[0] = 2 * g3.gcL;
-        cols[1] = 2 * g3.gcL + 1;
+        int rows[2] = {2 * g3.gr0, 2 * g3.gr0 + 1}, cols[2] = {2 * g3.gcL, 2 * g3.gcL + 1};
         fold_both(rows, h3);
         fold_both(cols, w3);
 #pragma unroll
-        for (int r = 0; r < kRows3; ++r)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) c[r][k] = plane2(rows[2 * r + (k >> 1)], cols[k & 1]);
-        steps<DIR, WAV, SCH, NW, 1, kRows3>(c, L, lane, wv, g3);
-        if (core_lane3)
-            store_bands3<T, kHalo3 / 4, R / 4, kRows3>(c, static_cast<T*>(P.ll), P.ll_pitch, out, P.out_pitch, g3, lane,
-                                                       wv);
+        for (int k = 0; k < 4; ++k) c[0][k] = plane2(rows[k >> 1], cols[k & 1]);
+        steps<DIR, WAV, SCH, NW, 1, 1>(c, L, lane, wv, g3);
+        T* const ll = static_cast<T*>(P.ll);
+        if (core_lane3) store_bands<T, 0, kHalo3 / 4, NW, 1, 1>(c, ll, P.ll_pitch, out, P.out_pitch, g3, lane, wv);
     } else {
         constexpr bool kAdj = DIR == kAdjoint;
         const T* const det = static_cast<const T*>(P.in);
-        load_bands<T, kAdj, 0, 1, kRows3>(c, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h3, w3, g3, false,
+        load_bands<T, kAdj, 0, 1, 1>(c, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h3, w3, g3, false,
                                           lane);
         load_bands<T, kAdj, 1, 1, K2>(b, det, P.in_pitch, det, P.in_pitch, h2, w2, g2, interior, lane);
         load_bands<T, kAdj, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
-        steps<DIR, WAV, SCH, NW, 1, kRows3>(c, L, lane, wv, g3);
+        steps<DIR, WAV, SCH, NW, 1, 1>(c, L, lane, wv, g3);
         if constexpr (kAdj) scale_edges<0, 4, 1>(c, g3, h3, w3, 0.5f);
         if (lane < kLanes / 2) {
 #pragma unroll
-            for (int r = 0; r < kRows3; ++r)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int row = 2 * (wv * kRows3 + r) + (k >> 1);
-                    if (row < R2) S.p[row][2 * lane + (k & 1)] = stored<T>(c[r][k]);
-                }
+            for (int k = 0; k < 4; ++k) S.p[2 * wv + (k >> 1)][2 * lane + (k & 1)] = stored<T>(c[0][k]);
         }
         __syncthreads();
         // an interior tile's level 2 is free of border weights, as its loads are
@@ -636,7 +607,7 @@ __global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
     Q.in = static_cast<const T*>(P.in) + (int64_t)pl * P.in_ps;
     Q.out = static_cast<T*>(P.out) + (int64_t)pl * P.out_ps;
     Q.ll = static_cast<T*>(P.ll) + (int64_t)pl * P.ll_ps;
-    if constexpr (LEVELS == 3) tile3<DIR, WAV, T, SCH>(Q, tx, ty, L, S, lane, wv);
+    if constexpr (LEVELS == 3) tile3<DIR, WAV, T, SCH, NW>(Q, tx, ty, L, S, lane, wv);
     else tile<DIR, WAV, T, SCH, NW, K>(Q, tx, ty, L, S, lane, wv);
 }
 
@@ -644,7 +615,7 @@ __global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
 template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
 hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
     constexpr int CX = LEVELS == 3 ? kTripleCols : kPairCols;
-    constexpr int CY = LEVELS == 3 ? kTripleRows : NW * K - 2 * kHalo2;
+    constexpr int CY = NW * K - 2 * (LEVELS == 3 ? kHalo3 : kHalo2);
     p.tiles_x = ((p.w + 1) / 2 + CX - 1) / CX;
     p.tiles_y = ((p.h + 1) / 2 + CY - 1) / CY;
     // the tiles of all planes, rounded up to a multiple of 8 chunks; planes
@@ -670,7 +641,11 @@ hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
 
 template <int DIR, int WAV, typename T, int SCH>
 hipError_t launch(int levels, const PairParams& p, int planes, hipStream_t s) {
-    if (levels == 3) return launch_shape<DIR, WAV, T, SCH, kTripleWaves, kTripleK, 3>(p, planes, s);
+    if (levels == 3) {
+        const int rows = triple_rows((Direction)DIR, triple_tiles(p.h, p.w, planes, 48), triple_tiles(p.h, p.w, planes, 64));
+        if (rows == 48) return launch_shape<DIR, WAV, T, SCH, 12, kTripleK, 3>(p, planes, s);
+        return launch_shape<DIR, WAV, T, SCH, 16, kTripleK, 3>(p, planes, s);
+    }
     if (pair_rows((Direction)DIR, sizeof(T), pair_tiles(p.h, p.w, planes, 32), pair_tiles(p.h, p.w, planes, 48),
                   (int64_t)p.h * p.w * planes) == 48)
         return launch_shape<DIR, WAV, T, SCH, 8, 6>(p, planes, s);

@@ -26,3 +26,18 @@ def test_two_level_launches(tdt, count, lo, hi):
         print("batched pair", tdt, count, levels, flush=True)
         for y, z in zip(d.fwd_batched(xs, levels), d.fwd_batched(xs, levels, config=0)):
             assert torch.equal(y, z), (levels, tuple(y.shape))
+
+
+@pytest.mark.parametrize("tdt", [torch.float32, torch.bfloat16])
+def test_three_level_tall_tiles(tdt):
+    """150 small images: three levels in tiles 64 pixels high."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dev = torch.device("cuda", 0)
+    r = random.Random(3)
+    shapes = [(64, 192), (65, 193), (63, 194)] + [(r.randint(33, 80), r.randint(20, 200)) for _ in range(150)]
+    g = torch.Generator(device=dev).manual_seed(8)
+    xs = [torch.rand(s, device=dev, generator=g).to(tdt) for s in shapes]
+    print("batched triple", tdt, flush=True)
+    for y, z in zip(d.fwd_batched(xs, 3), d.fwd_batched(xs, 3, config=0)):
+        assert torch.equal(y, z), tuple(y.shape)

@@ -89,3 +89,11 @@ def test_strides(wavelet, tdt, levels):
                                     ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
         assert st == 0, st
         assert torch.equal(dst, out), name
+
+
+@pytest.mark.parametrize("wavelet,tdt", TYPES)
+@pytest.mark.parametrize("n,h,w", [(130, 63, 190), (130, 64, 192), (64, 66, 193), (86, 65, 194), (1, 1501, 1499)])
+def test_three_levels_tall_tiles(wavelet, tdt, n, h, w):
+    """Three levels in tiles 64 high: more than 256 of the tiles 32 high, at
+    most 256 (forward 384) of these."""
+    check(image(n, h, w, tdt, 105), wavelet, 3)

@@ -94,7 +94,11 @@ typedef enum {
                                Forward / inverse: by default on a register
                                tile kernel of its own; with a scheme flag or
                                a named configuration on DWT2_ALGO_LDS kernel
-                               configurations (bit-identical results).     */
+                               configurations.  FP32, and any storage with
+                               DWT2_FLAG_FUSED: bit-identical results; BF16 /
+                               FP16 by default in the factored form (see
+                               DWT2_FLAG_FUSED), equal up to FP32 rounding
+                               before the store.                           */
 } dwt2_wavelet;
 
 typedef enum {
@@ -148,7 +152,8 @@ typedef enum {
                                 paper's formulas).  Without any scheme flag the
                                 fused steps run, evaluated directly for 4-byte
                                 samples, and for BF16 / FP16 storage on
-                                DWT2_ALGO_TILE configurations in the factored
+                                DWT2_ALGO_TILE configurations (DD 13/7: without
+                                a named configuration) in the factored
                                 form of DWT2_FLAG_FACTORED (same steps and
                                 barriers, fewer operations: with half the bytes
                                 per pixel that kernel is bound by its

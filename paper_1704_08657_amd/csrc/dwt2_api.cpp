@@ -317,10 +317,12 @@ int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, i
             q.out = lp.out ? (char*)lp.out + (size_t)p0 * (size_t)lp.out_ps * es : nullptr;
             q.out_ll = lp.out_ll ? (char*)lp.out_ll + (size_t)p0 * (size_t)lp.out_ll_ps * es : nullptr;
         }
-        // DD 13/7 without a named configuration or scheme: the four-tap
-        // register tile kernel
+        // DD 13/7 without a named configuration or scheme (or with the fused
+        // one): the four-tap register tile kernel, whose steps are fused for FP32
+        // (memory-bound) and factored for 16-bit storage (bound by its arithmetic)
         const bool taps4 = wavelet == DWT2_DD137 && !(flags & ~DWT2_FLAG_FUSED);
-        const int rc = taps4 ? report(dwt2::launch_taps4(dir, to_dtype(dtype), q, n, s))
+        const dwt2::Scheme sch4 = flags || dtype == DWT2_F32 ? dwt2::kSchemeFused : dwt2::kSchemeFactored;
+        const int rc = taps4 ? report(dwt2::launch_taps4(dir, to_dtype(dtype), sch4, q, n, s))
                              : report(dwt2::launch_level(dir, to_wav(wavelet), to_dtype(dtype),
                                                  scheme_of(flags, dtype, wavelet, dir == dwt2::kAdjoint),
                                                  cfg, q, n, s));

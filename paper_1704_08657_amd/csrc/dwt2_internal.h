@@ -200,8 +200,9 @@ hipError_t launch_level(Direction dir, Wavelet wav, Dtype dt, Scheme scheme, int
 // of the float wavelets, fused / separable / polyconvolution schemes.
 hipError_t launch_lds(Direction dir, Wavelet wav, Dtype dt, Scheme scheme, int cfg, const LevelParams& p,
                       int planes, hipStream_t stream);
-// DD 13/7 with the fused steps, forward and inverse, on the four-tap register
-// tile kernel; sets the tile grid itself.  Bit-identical to the LDS-plane kernel.
-hipError_t launch_taps4(Direction dir, Dtype dt, const LevelParams& p, int planes, hipStream_t stream);
+// DD 13/7, forward and inverse, on the four-tap register tile kernel; sets the
+// tile grid itself.  The fused steps bit-identical to the LDS-plane kernel, or, for
+// 16-bit storage, as their two factors.
+hipError_t launch_taps4(Direction dir, Dtype dt, Scheme sch, const LevelParams& p, int planes, hipStream_t stream);
 
 }  // namespace dwt2

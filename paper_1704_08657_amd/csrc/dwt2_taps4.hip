@@ -1,6 +1,6 @@
 // Register tile kernel for the four-tap steps of DD 13/7 (Section
-// "Evaluation"): the fused predict T_P and update S_U of its one lifting pair,
-// forward and inverse, FP32 / BF16 / FP16 storage.
+// "Evaluation"): the predict T_P and update S_U of its one lifting pair, fused or
+// as their factors, forward and inverse, FP32 / BF16 / FP16 storage.
 //
 // Why not the LDS-plane kernel, which also runs them: there every step reads
 // about 25 and writes 4 LDS words per block, so LDS bounds it at a quarter of
@@ -19,11 +19,12 @@
 // away, where the two-tap kernel's packed halo lanes hold two.
 //
 // 4096^2 FP32, 3 levels forward: 115.6 us a call on the LDS-plane kernel,
-// 43.3 on this one; 3 x 2161 x 3841 BF16, 2 levels inverse: 192 and 37; one level of
-// 8192^2 FP32: 300 and 104 forward (5.2 TB/s), 409 and 98 inverse (5.5 TB/s).
-// What bounds it now is the memory system for FP32 and the vector units (25
-// operations per block and step, a quarter of them on halo rows) for 16-bit
-// storage.
+// 43.3 on this one; one level of 8192^2 FP32: 300 and 104 forward (5.2 TB/s), 409 and
+// 98 inverse (5.5 TB/s): the memory system.  With 16-bit storage the vector units
+// bound the fused steps (25 operations per block and step, a quarter of them on
+// halo rows), so without a scheme flag it takes their two 1-D factors, 16
+// operations (one level of 3 x 2161 x 3841: BF16 forward 27.0, factored 23.5 us,
+// inverse 25.8, 22.4; FP16 29.4, 24.3 and 26.7, 23.0).
 //
 // Tiles touching the image border load the whole-point symmetric extension
 // (forward: the reflected pixel; inverse: each subband sample at its
@@ -73,43 +74,54 @@ __device__ __forceinline__ void row_sums(const float (&row)[4 * BPL], int k, Tap
     for (int b = 0; b < BPL; ++b) s[b] = sum4(t, x[b], x[b + 1], x[b + 2], x[b + 3]);
 }
 
-// A row another wave needs: two components and the horizontal sum of one.
-template <int BPL> struct EdgeRow {
-    float v[3][BPL / 2][kLanes][2];
+// A row another wave needs: two components and, for the fused steps, the
+// horizontal sum of one.
+template <int BPL, int SCH> struct EdgeRow {
+    float v[SCH == kSchemeFused ? 3 : 2][BPL / 2][kLanes][2];
 };
-template <int BPL>
-__device__ __forceinline__ void put(EdgeRow<BPL>& E, const float (&row)[4 * BPL], int k0, const float (&s)[BPL],
-                                    int lane) {
+template <int BPL, int SCH>
+__device__ __forceinline__ void put(EdgeRow<BPL, SCH>& E, const float (&row)[4 * BPL], int k0, int lane) {
 #pragma unroll
     for (int b = 0; b < BPL; ++b) {
         E.v[0][b / 2][lane][b & 1] = row[4 * b + k0];
         E.v[1][b / 2][lane][b & 1] = row[4 * b + k0 + 1];
-        E.v[2][b / 2][lane][b & 1] = s[b];
     }
 }
 template <int BPL>
-__device__ __forceinline__ void get(const EdgeRow<BPL>& E, float (&x)[BPL], float (&y)[BPL], float (&s)[BPL],
-                                    int lane) {
+__device__ __forceinline__ void put(EdgeRow<BPL, kSchemeFused>& E, const float (&row)[4 * BPL], int k0,
+                                    const float (&s)[BPL], int lane) {
+    put(E, row, k0, lane);
+#pragma unroll
+    for (int b = 0; b < BPL; ++b) E.v[2][b / 2][lane][b & 1] = s[b];
+}
+template <int BPL, int SCH>
+__device__ __forceinline__ void get(const EdgeRow<BPL, SCH>& E, float (&x)[BPL], float (&y)[BPL], int lane) {
 #pragma unroll
     for (int b = 0; b < BPL; ++b) {
         x[b] = E.v[0][b / 2][lane][b & 1];
         y[b] = E.v[1][b / 2][lane][b & 1];
-        s[b] = E.v[2][b / 2][lane][b & 1];
     }
+}
+template <int BPL>
+__device__ __forceinline__ void get(const EdgeRow<BPL, kSchemeFused>& E, float (&x)[BPL], float (&y)[BPL],
+                                    float (&s)[BPL], int lane) {
+    get(E, x, y, lane);
+#pragma unroll
+    for (int b = 0; b < BPL; ++b) s[b] = E.v[2][b / 2][lane][b & 1];
 }
 
 // LDS of one work-group: slot w holds what wave w reads.  near2: the two rows
 // on the side the step reads two rows from, near1: the one on the other side.
 // The outermost waves' slots without a writer are never stored outputs'
 // operands (the tile's halo absorbs them).
-template <int NW, int BPL> struct Lds {
-    EdgeRow<BPL> near2[NW][2];
-    EdgeRow<BPL> near1[NW];
+template <int NW, int BPL, int SCH> struct Lds {
+    EdgeRow<BPL, SCH> near2[NW][2];
+    EdgeRow<BPL, SCH> near1[NW];
 };
 
 // T_P: x1 += P x0, x2 += P* x0, x3 += P P* x0 + P* x1 + P x2.
 template <bool NEG, int NW, int BPL, int K>
-__device__ __forceinline__ void predict(float (&a)[K][4 * BPL], Lds<NW, BPL>& L, int lane, int wv) {
+__device__ __forceinline__ void predict(float (&a)[K][4 * BPL], Lds<NW, BPL, kSchemeFused>& L, int lane, int wv) {
     constexpr Taps t = predict_taps<NEG>();
     float H[K + 3][BPL];                           // sums of x0, rows -1 .. K + 1 at index row + 1
 #pragma unroll
@@ -151,7 +163,7 @@ __device__ __forceinline__ void predict(float (&a)[K][4 * BPL], Lds<NW, BPL>& L,
 
 // S_U: x0 += U x1 + U* x2 + U U* x3, x1 += U* x3, x2 += U x3.
 template <bool NEG, int NW, int BPL, int K>
-__device__ __forceinline__ void update(float (&a)[K][4 * BPL], Lds<NW, BPL>& L, int lane, int wv) {
+__device__ __forceinline__ void update(float (&a)[K][4 * BPL], Lds<NW, BPL, kSchemeFused>& L, int lane, int wv) {
     constexpr Taps t = update_taps<NEG>();
     float H[K + 3][BPL];                           // sums of x3, rows -2 .. K at index row + 2
 #pragma unroll
@@ -189,6 +201,90 @@ __device__ __forceinline__ void update(float (&a)[K][4 * BPL], Lds<NW, BPL>& L, 
             dn2[b] = x2;
         }
     }
+}
+
+// The same steps as their two 1-D factors (16 operations per block and step, the
+// fused form 25): the horizontal one stays inside the wave, the vertical one
+// reads the edge rows.  FIRST: the first tap's offset, -1 or -2.
+__device__ __forceinline__ float add4(Taps t, float a, float b, float c, float d, float x) {
+    return fmaf(t.c3, d, fmaf(t.c2, c, fmaf(t.c1, b, fmaf(t.c0, a, x))));
+}
+template <int BPL, int FIRST>
+__device__ __forceinline__ void add_row(float (&row)[4 * BPL], int from, int to, Taps t) {
+    float x[BPL + 3];                              // blocks FIRST .. BPL + FIRST + 2 of the lane's window
+#pragma unroll
+    for (int i = 0; i < BPL + 3; ++i) {
+        const int b = i + FIRST;
+        if (b < 0) x[i] = from_left(row[4 * (b + BPL) + from]);
+        else if (b < BPL) x[i] = row[4 * b + from];
+        else x[i] = from_right(row[4 * (b - BPL) + from]);
+    }
+#pragma unroll
+    for (int b = 0; b < BPL; ++b) row[4 * b + to] = add4(t, x[b], x[b + 1], x[b + 2], x[b + 3], row[4 * b + to]);
+}
+
+// T_P^H: x1 += P x0, x3 += P x2; T_P^V: x2 += P* x0, x3 += P* x1.
+template <bool NEG, int NW, int BPL, int K>
+__device__ __forceinline__ void predict(float (&a)[K][4 * BPL], Lds<NW, BPL, kSchemeFactored>& L, int lane, int wv) {
+    constexpr Taps t = predict_taps<NEG>();
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        add_row<BPL, -1>(a[r], 0, 1, t);
+        add_row<BPL, -1>(a[r], 2, 3, t);
+    }
+    if (wv > 0) {
+        put(L.near2[wv - 1][0], a[0], 0, lane);
+        put(L.near2[wv - 1][1], a[1], 0, lane);
+    }
+    if (wv < NW - 1) put(L.near1[wv + 1], a[K - 1], 0, lane);
+    __syncthreads();
+    float u[2][BPL], d[2][2][BPL];                 // x0, x1 of row -1 and of rows K, K + 1
+    get(L.near1[wv], u[0], u[1], lane);
+    get(L.near2[wv][0], d[0][0], d[1][0], lane);
+    get(L.near2[wv][1], d[0][1], d[1][1], lane);
+#pragma unroll
+    for (int r = 0; r < K; ++r)
+#pragma unroll
+        for (int b = 0; b < BPL; ++b)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float x0 = r > 0 ? a[r > 0 ? r - 1 : 0][4 * b + k] : u[k][b];
+                const float x2 = r + 1 < K ? a[r + 1 < K ? r + 1 : 0][4 * b + k] : d[k][0][b];
+                const float x3 = r + 2 < K ? a[r + 2 < K ? r + 2 : 0][4 * b + k] : d[k][r + 2 - K == 1 ? 1 : 0][b];
+                a[r][4 * b + 2 + k] = add4(t, x0, a[r][4 * b + k], x2, x3, a[r][4 * b + 2 + k]);
+            }
+}
+
+// S_U^H: x0 += U x1, x2 += U x3; S_U^V: x0 += U* x2, x1 += U* x3.
+template <bool NEG, int NW, int BPL, int K>
+__device__ __forceinline__ void update(float (&a)[K][4 * BPL], Lds<NW, BPL, kSchemeFactored>& L, int lane, int wv) {
+    constexpr Taps t = update_taps<NEG>();
+#pragma unroll
+    for (int r = 0; r < K; ++r) {
+        add_row<BPL, -2>(a[r], 1, 0, t);
+        add_row<BPL, -2>(a[r], 3, 2, t);
+    }
+    if (wv < NW - 1) {
+        put(L.near2[wv + 1][0], a[K - 2], 2, lane);
+        put(L.near2[wv + 1][1], a[K - 1], 2, lane);
+    }
+    if (wv > 0) put(L.near1[wv - 1], a[0], 2, lane);
+    __syncthreads();
+    float u[2][2][BPL], d[2][BPL];                 // x2, x3 of rows -2, -1 and of row K
+    get(L.near2[wv][0], u[0][0], u[1][0], lane);
+    get(L.near2[wv][1], u[0][1], u[1][1], lane);
+    get(L.near1[wv], d[0], d[1], lane);
+#pragma unroll
+    for (int r = K - 1; r >= 0; --r)
+#pragma unroll
+        for (int b = 0; b < BPL; ++b)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const float x0 = r > 1 ? a[r > 1 ? r - 2 : 0][4 * b + 2 + k] : u[k][r == 1 ? 1 : 0][b];
+                const float x1 = r > 0 ? a[r > 0 ? r - 1 : 0][4 * b + 2 + k] : u[k][1][b];
+                const float x3 = r + 1 < K ? a[r + 1 < K ? r + 1 : 0][4 * b + 2 + k] : d[k][b];
+                a[r][4 * b + k] = add4(t, x0, x1, a[r][4 * b + 2 + k], x3, a[r][4 * b + k]);
+            }
 }
 
 // Columns left of the image: fold() takes positions down to -6, which is as
@@ -329,10 +425,10 @@ __device__ __forceinline__ void store(float (&a)[K][4 * BPL], const LevelParams&
     }
 }
 
-template <int DIR, typename T, int NW, int K, int BPL, int EL>
+template <int DIR, typename T, int SCH, int NW, int K, int BPL, int EL>
 __global__ void __launch_bounds__(NW * kLanes) taps4_kernel(LevelParams P0) {
     static_assert(K >= kHalo4 && BPL * EL >= kHalo4, "halo within the first and last wave / lanes");
-    __shared__ Lds<NW, BPL> lds;
+    __shared__ Lds<NW, BPL, SCH> lds;
     const int lane = threadIdx.x & (kLanes - 1);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     fetch_params(P0);
@@ -382,7 +478,7 @@ __global__ void __launch_bounds__(NW * kLanes) taps4_kernel(LevelParams P0) {
 constexpr int kWaves = 4, kBpl = 2, kEdge = 2;
 constexpr int kCols = (kLanes - 2 * kEdge) * kBpl;
 
-template <int DIR, typename T, int K>
+template <int DIR, typename T, int SCH, int K>
 hipError_t launch_rows(LevelParams p, int planes, hipStream_t s) {
     constexpr int CY = kWaves * K - 2 * kHalo4;
     p.tiles_x = ((p.w + 1) / 2 + kCols - 1) / kCols;
@@ -402,7 +498,7 @@ hipError_t launch_rows(LevelParams p, int planes, hipStream_t s) {
             if (q.out_ll) q.out_ll = static_cast<T*>(q.out_ll) + p0 * q.out_ll_ps;
         }
         const int64_t grid = (nt * q.planes + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
-        hipLaunchKernelGGL((taps4_kernel<DIR, T, kWaves, K, kBpl, kEdge>), dim3((unsigned)grid),
+        hipLaunchKernelGGL((taps4_kernel<DIR, T, SCH, kWaves, K, kBpl, kEdge>), dim3((unsigned)grid),
                            dim3(kWaves * kLanes), 0, s, q);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -413,18 +509,25 @@ hipError_t launch_rows(LevelParams p, int planes, hipStream_t s) {
 // A level whose tiles all run at once (four work-groups on each of 256 CUs)
 // takes one tile's time: the shorter tile.  Otherwise the one that recomputes
 // fewer halo rows.
-template <int DIR, typename T>
+template <int DIR, typename T, int SCH>
 hipError_t launch_t(const LevelParams& p, int planes, hipStream_t s) {
     const int64_t tiles = (int64_t)(((p.w + 1) / 2 + kCols - 1) / kCols) * (((p.h + 1) / 2 + 9) / 10) * planes;
-    return tiles <= 1024 ? launch_rows<DIR, T, 4>(p, planes, s) : launch_rows<DIR, T, 5>(p, planes, s);
+    return tiles <= 1024 ? launch_rows<DIR, T, SCH, 4>(p, planes, s) : launch_rows<DIR, T, SCH, 5>(p, planes, s);
 }
 
+template <int DIR, typename T>
+hipError_t launch_scheme(Scheme sch, const LevelParams& p, int planes, hipStream_t s) {
+    if (sch == kSchemeFused) return launch_t<DIR, T, kSchemeFused>(p, planes, s);
+    if constexpr (sizeof(T) == 2)
+        if (sch == kSchemeFactored) return launch_t<DIR, T, kSchemeFactored>(p, planes, s);
+    return hipErrorInvalidValue;
+}
 template <int DIR>
-hipError_t launch_dt(Dtype dt, const LevelParams& p, int planes, hipStream_t s) {
+hipError_t launch_dt(Dtype dt, Scheme sch, const LevelParams& p, int planes, hipStream_t s) {
     switch (dt) {
-        case kF32: return launch_t<DIR, float>(p, planes, s);
-        case kBF16: return launch_t<DIR, __hip_bfloat16>(p, planes, s);
-        case kF16: return launch_t<DIR, __half>(p, planes, s);
+        case kF32: return launch_scheme<DIR, float>(sch, p, planes, s);
+        case kBF16: return launch_scheme<DIR, __hip_bfloat16>(sch, p, planes, s);
+        case kF16: return launch_scheme<DIR, __half>(sch, p, planes, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -432,11 +535,11 @@ hipError_t launch_dt(Dtype dt, const LevelParams& p, int planes, hipStream_t s) 
 }  // namespace taps4
 }  // namespace kern
 
-hipError_t launch_taps4(Direction dir, Dtype dt, const LevelParams& p, int planes, hipStream_t s) {
+hipError_t launch_taps4(Direction dir, Dtype dt, Scheme sch, const LevelParams& p, int planes, hipStream_t s) {
     if (planes <= 0) return hipSuccess;
     switch (dir) {
-        case kForward: return kern::taps4::launch_dt<kForward>(dt, p, planes, s);
-        case kInverse: return kern::taps4::launch_dt<kInverse>(dt, p, planes, s);
+        case kForward: return kern::taps4::launch_dt<kForward>(dt, sch, p, planes, s);
+        case kInverse: return kern::taps4::launch_dt<kInverse>(dt, sch, p, planes, s);
         default: return hipErrorInvalidValue;
     }
 }

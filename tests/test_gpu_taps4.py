@@ -1,8 +1,9 @@
-"""DD 13/7 on the four-tap register tile kernel (calls that name no kernel
-configuration and no scheme): bit for bit the LDS-plane kernel's results, whose
-parity with the oracle tests/test_gpu_lds.py holds, at the ends of both
-kernels' tiles, for every storage type and direction; the smallest images
-against the oracle itself."""
+"""DD 13/7 on the four-tap register tile kernels (calls that name no kernel
+configuration and no scheme): the fused steps bit for bit the LDS-plane kernel's
+results, whose parity with the oracle tests/test_gpu_lds.py holds, at the ends of
+the kernels' tiles, for every storage type and direction; the factored ones (the
+default of 16-bit storage) within an ulp of them; several levels bit for bit the
+levels one by one; the smallest images against the oracle itself."""
 import numpy as np
 import pytest
 
@@ -24,6 +25,17 @@ def dev():
     return torch.device("cuda", 0)
 
 
+def one_by_one(direction, x, levels):
+    """The transform of several levels as one call for each."""
+    sizes = [x.shape[-2:]]
+    for _ in range(levels - 1):
+        sizes.append(tuple((n + 1) // 2 for n in sizes[-1]))
+    y = x.clone()
+    for h, w in sizes if direction is d.fwd else sizes[::-1]:
+        y[..., :h, :w] = direction(y[..., :h, :w].contiguous(), "dd137", 1)
+    return y
+
+
 @pytest.mark.parametrize("tdt", [torch.float32, torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("h,w,levels", [(20, 240, 1), (21, 241, 1), (27, 247, 2), (58, 486, 1), (111, 495, 2),
                                         (104, 480, 3), (200, 1000, 5), (2900, 2050, 2), (1, 1, 0)])
@@ -36,8 +48,17 @@ def test_equals_lds_plane_kernel(tdt, h, w, levels):
     x = torch.from_numpy(workloads.planes(n, h, w, seed=91)).to(dev()).to(tdt)
     for direction in (d.fwd, d.inv):
         print("taps4", tdt, (n, h, w), levels, direction.__name__, flush=True)
-        assert torch.equal(direction(x, "dd137", levels), direction(x, "dd137", levels, config=LDS_CONFIG))
-        assert torch.equal(direction(x, "dd137", levels, fused=True), direction(x, "dd137", levels))
+        fused = direction(x, "dd137", levels, fused=True)
+        assert torch.equal(fused, direction(x, "dd137", levels, config=LDS_CONFIG))
+        if tdt == torch.float32:
+            assert torch.equal(direction(x, "dd137", levels), fused)
+            continue
+        # one level: the same FP32 value up to its own rounding (1e-6 of the
+        # largest), rounded once: neighbours in the storage type at most
+        y, z = direction(x, "dd137", 1).float(), direction(x, "dd137", 1, fused=True).float()
+        ulp = 2.0 ** (-7 if tdt == torch.bfloat16 else -10)
+        assert bool(((y - z).abs() <= ulp * z.abs() + 1e-6 * z.abs().max()).all())
+        assert torch.equal(direction(x, "dd137", levels), one_by_one(direction, x, levels))
 
 
 @pytest.mark.parametrize("h", [2, 3, 4, 6, 7, 8, 9])

@@ -348,7 +348,9 @@ bool cached_output(dwt2::Direction dir, int32_t planes, int32_t h, int32_t w, si
 // at once (triple_rows), else two where that is the faster way (pair_pays).
 int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int wavelet, unsigned flags,
                      int32_t planes) {
-    if (flags != 0 || wavelet == DWT2_DD137 || l + 1 >= p.levels) return 1;
+    if (flags != 0 || l + 1 >= p.levels) return 1;
+    if (wavelet == DWT2_DD137)
+        return dwt2::taps4_pair_rows(dir, elem_size(dtype), p.h[l], p.w[l], planes) > 0 ? 2 : 1;
     if (l + 3 == p.levels && dwt2::triple_rows(dir, dwt2::triple_tiles(p.h[l], p.w[l], planes, 48),
                                                dwt2::triple_tiles(p.h[l], p.w[l], planes, 64)) > 0)
         return 3;

@@ -30,6 +30,7 @@ hipError_t launch_pair_adj(Wavelet wav, Dtype dt, int levels, const PairParams& 
 hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes,
                        hipStream_t stream) {
     if (planes <= 0) return hipSuccess;
+    if (wav == kDd137) return levels == 2 ? launch_taps4_pair(dir, dt, p, planes, stream) : hipErrorInvalidValue;
     switch (dir) {
         case kForward: return launch_pair_fwd(wav, dt, levels, p, planes, stream);
         case kInverse: return launch_pair_inv(wav, dt, levels, p, planes, stream);

@@ -187,6 +187,30 @@ inline int triple_rows(Direction dir, int64_t tiles48, int64_t tiles64) {
 hipError_t launch_pair(Direction dir, Wavelet wav, Dtype dt, int levels, const PairParams& p, int planes,
                        hipStream_t stream);
 
+// The same for DD 13/7 (forward and inverse, two levels): tiles of 48 block rows (8
+// waves x 6) or 64 (16 x 4) with a halo of kHalo4x2 above and below and of
+// kEdge4x2 lanes of two block columns on either side.
+constexpr int kHalo4x2 = 10;
+constexpr int kEdge4x2 = 5;
+constexpr int kCols4x2 = 2 * (kLanes - 2 * kEdge4x2);
+inline int64_t taps4_pair_tiles(int32_t h, int32_t w, int32_t planes, int rows) {
+    const int cy = rows - 2 * kHalo4x2;
+    return (int64_t)(((w + 1) / 2 + kCols4x2 - 1) / kCols4x2) * (((h + 1) / 2 + cy - 1) / cy) * planes;
+}
+// Block rows of the tiles that take two levels in one launch, 0 if a launch each is
+// faster.  The recomputed halo, half of a tile, is arithmetic, which is what
+// bounds the larger levels; where the tiles all run at once, two on a CU, it is hidden by
+// what a launch takes from load to store.  us, one launch each / both in one:
+// 2048^2, 370 tiles of 48 rows, FP32 16.9 / 14.5, inverse 16.6 / 15.1; 2400^2, 516,
+// 18.4 / 19.7; 8192^2 126 / 140.  The taller tiles, of which two fit a CU with
+// 16-bit storage only, pay forward: 2800^2 BF16, 416 tiles, 20.7 / 15.8 (inverse 2400^2
+// 16.4 / 17.6); 3200^2, 555, 22.6 / 21.9; 3 x 2161 x 3841 40.8 / 37.7, inverse 37.1 / 38.4.
+inline int taps4_pair_rows(Direction dir, size_t es, int32_t h, int32_t w, int32_t planes) {
+    if (taps4_pair_tiles(h, w, planes, 48) <= 512) return 48;
+    return dir == kForward && es == 2 && taps4_pair_tiles(h, w, planes, 64) <= 512 ? 64 : 0;
+}
+hipError_t launch_taps4_pair(Direction dir, Dtype dt, const PairParams& p, int planes, hipStream_t stream);
+
 // Enqueue one level for `planes` planes (1 <= planes <= kMaxGridPlanes).
 // Returns hipSuccess or the launch error.  `cfg` indexes kConfigs;
 // tiles_x / tiles_y (and seg_rows) of `p` must follow it: for kAlgoTile the

@@ -583,13 +583,10 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
     }
 }
 
-template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
-__global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
-    using V = typename St<T>::V;
-    __shared__ PairLds<V, NW> L;
-    __shared__ PairPlane<V, NW * K> S;
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+// The calling work-group's tile (tx, ty) and its plane's parameters Q; false past
+// the last tile (uniform over the work-group).
+template <typename T>
+__device__ __forceinline__ bool pick_tile(const PairParams& P, PairParams& Q, int& tx, int& ty) {
     // every kernel argument in one round trip, see fetch_params
     asm volatile("" ::"s"(P.in), "s"(P.in_pitch), "s"(P.in_ps), "s"(P.out), "s"(P.out_pitch), "s"(P.out_ps), "s"(P.ll),
                  "s"(P.ll_pitch), "s"(P.ll_ps), "s"(P.h), "s"(P.w), "s"(P.tiles_x), "s"(P.tiles_y), "s"(P.planes));
@@ -598,26 +595,39 @@ __global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
     const int chunk = kRemapRows * P.tiles_x;
     const int j = (int)(blockIdx.x >> 3);
     const int n = ((j / chunk) * 8 + (int)(blockIdx.x & 7)) * chunk + j % chunk;
-    if (n >= nt * P.planes) return;               // uniform over the work-group
+    if (n >= nt * P.planes) return false;
     const int pl = n / nt;
     const int t = n - pl * nt;
-    const int ty = t / P.tiles_x;
-    const int tx = t - ty * P.tiles_x;
-    PairParams Q = P;
+    ty = t / P.tiles_x;
+    tx = t - ty * P.tiles_x;
+    Q = P;
     Q.in = static_cast<const T*>(P.in) + (int64_t)pl * P.in_ps;
     Q.out = static_cast<T*>(P.out) + (int64_t)pl * P.out_ps;
     Q.ll = static_cast<T*>(P.ll) + (int64_t)pl * P.ll_ps;
+    return true;
+}
+
+template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
+__global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
+    using V = typename St<T>::V;
+    __shared__ PairLds<V, NW> L;
+    __shared__ PairPlane<V, NW * K> S;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    PairParams Q;
+    int tx, ty;
+    if (!pick_tile<T>(P, Q, tx, ty)) return;
     if constexpr (LEVELS == 3) tile3<DIR, WAV, T, SCH, NW>(Q, tx, ty, L, S, lane, wv);
     else tile<DIR, WAV, T, SCH, NW, K>(Q, tx, ty, L, S, lane, wv);
 }
 
 // ---- launch (host) ----------------------------------------------------------
-template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
-hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
-    constexpr int CX = LEVELS == 3 ? kTripleCols : kPairCols;
-    constexpr int CY = NW * K - 2 * (LEVELS == 3 ? kHalo3 : kHalo2);
-    p.tiles_x = ((p.w + 1) / 2 + CX - 1) / CX;
-    p.tiles_y = ((p.h + 1) / 2 + CY - 1) / CY;
+// `kernel` in work-groups of `waves` waves over tiles of cx x cy blocks (halo
+// excluded) of the launch's first level.
+template <typename T>
+hipError_t launch_tiles(void (*kernel)(PairParams), int cx, int cy, int waves, PairParams p, int planes, hipStream_t s) {
+    p.tiles_x = ((p.w + 1) / 2 + cx - 1) / cx;
+    p.tiles_y = ((p.h + 1) / 2 + cy - 1) / cy;
     // the tiles of all planes, rounded up to a multiple of 8 chunks; planes
     // beyond what one grid holds go to further launches
     const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
@@ -632,11 +642,16 @@ hipError_t launch_shape(PairParams p, int planes, hipStream_t s) {
         q.out = static_cast<T*>(p.out) + p0 * p.out_ps;
         q.ll = static_cast<T*>(p.ll) + p0 * p.ll_ps;
         const int64_t grid = (nt * q.planes + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
-        hipLaunchKernelGGL((pair_kernel<DIR, WAV, T, SCH, NW, K, LEVELS>), dim3((unsigned)grid), dim3(NW * kLanes), 0, s, q);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(waves * kLanes), 0, s, q);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
+}
+template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
+hipError_t launch_shape(const PairParams& p, int planes, hipStream_t s) {
+    return launch_tiles<T>(pair_kernel<DIR, WAV, T, SCH, NW, K, LEVELS>, LEVELS == 3 ? kTripleCols : kPairCols,
+                           NW * K - 2 * (LEVELS == 3 ? kHalo3 : kHalo2), NW, p, planes, s);
 }
 
 template <int DIR, int WAV, typename T, int SCH>

@@ -29,7 +29,7 @@
 // Tiles touching the image border load the whole-point symmetric extension
 // (forward: the reflected pixel; inverse: each subband sample at its
 // reflected pixel position).
-#include "dwt2_kernels.inl"
+#include "dwt2_pair.inl"
 
 namespace dwt2 {
 namespace kern {
@@ -58,18 +58,23 @@ __device__ __forceinline__ float sum4z(Taps t, float a, float b, float c, float 
     return fmaf(t.c3, d, fmaf(t.c2, c, fmaf(t.c1, b, fmaf(t.c0, a, 0.f))));
 }
 
+// Component k of block b of the lane's row, -2 <= b < BPL + 2.
+template <int BPL>
+__device__ __forceinline__ float block_at(const float (&row)[4 * BPL], int b, int k) {
+    if (b < -BPL) return from_left(from_left(row[4 * (b + 2 * BPL) + k]));
+    if (b < 0) return from_left(row[4 * (b + BPL) + k]);
+    if (b < BPL) return row[4 * b + k];
+    if (b < 2 * BPL) return from_right(row[4 * (b - BPL) + k]);
+    return from_right(from_right(row[4 * (b - 2 * BPL) + k]));
+}
+
 // Horizontal sums of component k of one register row: taps at offsets
 // FIRST .. FIRST + 3 (FIRST = -1 or -2).
 template <int BPL, int FIRST>
 __device__ __forceinline__ void row_sums(const float (&row)[4 * BPL], int k, Taps t, float (&s)[BPL]) {
     float x[BPL + 3];                              // blocks FIRST .. BPL + FIRST + 2 of the lane's window
 #pragma unroll
-    for (int i = 0; i < BPL + 3; ++i) {
-        const int b = i + FIRST;
-        if (b < 0) x[i] = from_left(row[4 * (b + BPL) + k]);
-        else if (b < BPL) x[i] = row[4 * b + k];
-        else x[i] = from_right(row[4 * (b - BPL) + k]);
-    }
+    for (int i = 0; i < BPL + 3; ++i) x[i] = block_at<BPL>(row, i + FIRST, k);
 #pragma unroll
     for (int b = 0; b < BPL; ++b) s[b] = sum4(t, x[b], x[b + 1], x[b + 2], x[b + 3]);
 }
@@ -77,14 +82,14 @@ __device__ __forceinline__ void row_sums(const float (&row)[4 * BPL], int k, Tap
 // A row another wave needs: two components and, for the fused steps, the
 // horizontal sum of one.
 template <int BPL, int SCH> struct EdgeRow {
-    float v[SCH == kSchemeFused ? 3 : 2][BPL / 2][kLanes][2];
+    float v[SCH == kSchemeFused ? 3 : 2][kLanes][BPL];
 };
 template <int BPL, int SCH>
 __device__ __forceinline__ void put(EdgeRow<BPL, SCH>& E, const float (&row)[4 * BPL], int k0, int lane) {
 #pragma unroll
     for (int b = 0; b < BPL; ++b) {
-        E.v[0][b / 2][lane][b & 1] = row[4 * b + k0];
-        E.v[1][b / 2][lane][b & 1] = row[4 * b + k0 + 1];
+        E.v[0][lane][b] = row[4 * b + k0];
+        E.v[1][lane][b] = row[4 * b + k0 + 1];
     }
 }
 template <int BPL>
@@ -92,14 +97,14 @@ __device__ __forceinline__ void put(EdgeRow<BPL, kSchemeFused>& E, const float (
                                     const float (&s)[BPL], int lane) {
     put(E, row, k0, lane);
 #pragma unroll
-    for (int b = 0; b < BPL; ++b) E.v[2][b / 2][lane][b & 1] = s[b];
+    for (int b = 0; b < BPL; ++b) E.v[2][lane][b] = s[b];
 }
 template <int BPL, int SCH>
 __device__ __forceinline__ void get(const EdgeRow<BPL, SCH>& E, float (&x)[BPL], float (&y)[BPL], int lane) {
 #pragma unroll
     for (int b = 0; b < BPL; ++b) {
-        x[b] = E.v[0][b / 2][lane][b & 1];
-        y[b] = E.v[1][b / 2][lane][b & 1];
+        x[b] = E.v[0][lane][b];
+        y[b] = E.v[1][lane][b];
     }
 }
 template <int BPL>
@@ -107,7 +112,7 @@ __device__ __forceinline__ void get(const EdgeRow<BPL, kSchemeFused>& E, float (
                                     float (&s)[BPL], int lane) {
     get(E, x, y, lane);
 #pragma unroll
-    for (int b = 0; b < BPL; ++b) s[b] = E.v[2][b / 2][lane][b & 1];
+    for (int b = 0; b < BPL; ++b) s[b] = E.v[2][lane][b];
 }
 
 // LDS of one work-group: slot w holds what wave w reads.  near2: the two rows
@@ -213,12 +218,7 @@ template <int BPL, int FIRST>
 __device__ __forceinline__ void add_row(float (&row)[4 * BPL], int from, int to, Taps t) {
     float x[BPL + 3];                              // blocks FIRST .. BPL + FIRST + 2 of the lane's window
 #pragma unroll
-    for (int i = 0; i < BPL + 3; ++i) {
-        const int b = i + FIRST;
-        if (b < 0) x[i] = from_left(row[4 * (b + BPL) + from]);
-        else if (b < BPL) x[i] = row[4 * b + from];
-        else x[i] = from_right(row[4 * (b - BPL) + from]);
-    }
+    for (int i = 0; i < BPL + 3; ++i) x[i] = block_at<BPL>(row, i + FIRST, from);
 #pragma unroll
     for (int b = 0; b < BPL; ++b) row[4 * b + to] = add4(t, x[b], x[b + 1], x[b + 2], x[b + 3], row[4 * b + to]);
 }
@@ -532,8 +532,150 @@ hipError_t launch_dt(Dtype dt, Scheme sch, const LevelParams& p, int planes, hip
     }
 }
 
+// ---- two levels in one launch -------------------------------------------------
+// As the two-tap wavelets' (dwt2_pair.inl): a lane's LL samples of level 1 are its
+// blocks of level 2.  The halo is 3 blocks of each level, 9 of level 1, rounded up to
+// whole blocks of level 2: kHalo4x2 block rows, kEdge4x2 lanes.  The edge rows of
+// both levels and the plane that carries a border tile's LL samples share LDS, a
+// barrier apart.  For levels whose tiles all run at once (taps4_pair_rows): 512^2
+// FP32, 2 levels, 13.4 us in two launches, 10.4 in one; 4096^2, 3 levels, 43.3 and 40.5.
+template <int NW, int K, int SCH> union PairLds {
+    Lds<NW, 2, SCH> l1;
+    Lds<NW, 1, SCH> l2;
+    pair::PairPlane<float, NW * K> ll;
+};
+
+template <int DIR, typename T, int SCH, int NW, int K>
+__global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P0) {
+    static_assert(K % 4 == 0 || K == 6, "a wave's rows are whole blocks of level 2, two at least");
+    static_assert(2 * kEdge4x2 >= 3 * kHalo4 && kHalo4x2 >= 3 * kHalo4, "halo of both levels");
+    constexpr int R = NW * K, K2 = K / 2;
+    __shared__ PairLds<NW, K, SCH> L;
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    PairParams P;
+    int tx, ty;
+    if (!pair::pick_tile<T>(P0, P, tx, ty)) return;
+    Geo g, g2;
+    const int h2 = (P.h + 1) >> 1, w2 = (P.w + 1) >> 1;
+    g.nEr = h2; g.nOr = P.h >> 1;
+    g.nEc = w2; g.nOc = P.w >> 1;
+    g2.nEr = (h2 + 1) >> 1; g2.nOr = h2 >> 1;
+    g2.nEc = (w2 + 1) >> 1; g2.nOc = w2 >> 1;
+    const int r0 = ty * (R - 2 * kHalo4x2) - kHalo4x2;
+    g.cb0 = tx * kCols4x2 - 2 * kEdge4x2;
+    g.gcL = g.cb0 + 2 * lane;
+    g.gr0 = r0 + wv * K;
+    g2.cb0 = g.cb0 >> 1;
+    g2.gcL = g2.cb0 + lane;
+    g2.gr0 = g.gr0 >> 1;
+    const bool interior = r0 >= 0 && g.cb0 >= 0 && r0 + R <= g.nOr && g.cb0 + 2 * kLanes <= g.nOc;
+    const bool core_lane = lane >= kEdge4x2 && lane < kLanes - kEdge4x2;
+    auto plane = [&](int row, int col) -> float& {
+        return L.ll.p[pair::clamp_to(row - r0, R)][pair::clamp_to(col - g.cb0, 2 * kLanes)];
+    };
+    float a[K][8], b[K2][4];
+    if constexpr (DIR == kForward) {
+        pair::load_image<T, 2, K>(a, static_cast<const T*>(P.in), P.in_pitch, P.h, P.w, g, interior, lane);
+        predict<false, NW, 2, K>(a, L.l1, lane, wv);
+        __syncthreads();
+        update<false, NW, 2, K>(a, L.l1, lane, wv);
+        pair::scale_bands<2, K>(a, kZ2, kZ2Inv);
+        T* const out = static_cast<T*>(P.out);
+        if (core_lane) pair::store_bands<T, 1, kHalo4x2, NW, 2, K>(a, out, 0, out, P.out_pitch, g, lane, wv);
+#pragma unroll
+        for (int r = 0; r < K2; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[r][k] = pair::stored<T>(a[2 * r + (k >> 1)][4 * (k & 1)]);
+        __syncthreads();
+        if (!interior) {
+#pragma unroll
+            for (int r = 0; r < K2; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) L.ll.p[wv * K + 2 * r + (k >> 1)][2 * lane + (k & 1)] = b[r][k];
+            __syncthreads();
+            int rows[K], cols[2] = {2 * g2.gcL, 2 * g2.gcL + 1};
+#pragma unroll
+            for (int i = 0; i < K; ++i) rows[i] = 2 * g2.gr0 + i;
+            pair::fold_both(rows, h2);
+            pair::fold_both(cols, w2);
+#pragma unroll
+            for (int r = 0; r < K2; ++r)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) b[r][k] = plane(rows[2 * r + (k >> 1)], cols[k & 1]);
+            __syncthreads();
+        }
+        predict<false, NW, 1, K2>(b, L.l2, lane, wv);
+        __syncthreads();
+        update<false, NW, 1, K2>(b, L.l2, lane, wv);
+        pair::scale_bands<1, K2>(b, kZ2, kZ2Inv);
+        T* const ll = static_cast<T*>(P.ll);
+        if (core_lane)
+            pair::store_bands<T, 0, kHalo4x2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
+    } else {
+        const T* const det = static_cast<const T*>(P.in);
+        pair::load_bands<T, false, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2,
+                                             interior, lane);
+        pair::load_bands<T, false, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        pair::scale_bands<1, K2>(b, kZ2Inv, kZ2);
+        update<true, NW, 1, K2>(b, L.l2, lane, wv);
+        __syncthreads();
+        predict<true, NW, 1, K2>(b, L.l2, lane, wv);
+#pragma unroll
+        for (int r = 0; r < K2; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a[2 * r + (k >> 1)][4 * (k & 1)] = pair::stored<T>(b[r][k]);
+        __syncthreads();
+        if (!interior) {
+#pragma unroll
+            for (int r = 0; r < K; ++r)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) L.ll.p[wv * K + r][2 * lane + c] = a[r][4 * c];
+            __syncthreads();
+            pair::reflect_ll<2, K, false>(a, g, P.h, P.w, 1.f, plane);
+            __syncthreads();
+        }
+        pair::scale_bands<2, K>(a, kZ2Inv, kZ2);
+        update<true, NW, 2, K>(a, L.l1, lane, wv);
+        __syncthreads();
+        predict<true, NW, 2, K>(a, L.l1, lane, wv);
+        if (core_lane) {
+            T* const out = static_cast<T*>(P.out);
+            if (interior) pair::store_image<T, false, kHalo4x2, NW, 2, K>(a, out, P.out_pitch, P.h, P.w, g, lane, wv);
+            else pair::store_image<T, true, kHalo4x2, NW, 2, K>(a, out, P.out_pitch, P.h, P.w, g, lane, wv);
+        }
+    }
+}
+
+template <int DIR, typename T>
+hipError_t launch_pair_t(const PairParams& p, int planes, hipStream_t s) {
+    constexpr int SCH = sizeof(T) == 4 ? kSchemeFused : kSchemeFactored;
+    if constexpr (DIR == kForward && sizeof(T) == 2)
+        if (taps4_pair_rows(kForward, sizeof(T), p.h, p.w, planes) == 64)
+            return pair::launch_tiles<T>(pair_kernel<DIR, T, SCH, 16, 4>, kCols4x2, 64 - 2 * kHalo4x2, 16, p, planes, s);
+    return pair::launch_tiles<T>(pair_kernel<DIR, T, SCH, 8, 6>, kCols4x2, 48 - 2 * kHalo4x2, 8, p, planes, s);
+}
+template <int DIR>
+hipError_t launch_pair_dt(Dtype dt, const PairParams& p, int planes, hipStream_t s) {
+    switch (dt) {
+        case kF32: return launch_pair_t<DIR, float>(p, planes, s);
+        case kBF16: return launch_pair_t<DIR, __hip_bfloat16>(p, planes, s);
+        case kF16: return launch_pair_t<DIR, __half>(p, planes, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
 }  // namespace taps4
 }  // namespace kern
+
+hipError_t launch_taps4_pair(Direction dir, Dtype dt, const PairParams& p, int planes, hipStream_t s) {
+    if (planes <= 0) return hipSuccess;
+    switch (dir) {
+        case kForward: return kern::taps4::launch_pair_dt<kForward>(dt, p, planes, s);
+        case kInverse: return kern::taps4::launch_pair_dt<kInverse>(dt, p, planes, s);
+        default: return hipErrorInvalidValue;
+    }
+}
 
 hipError_t launch_taps4(Direction dir, Dtype dt, Scheme sch, const LevelParams& p, int planes, hipStream_t s) {
     if (planes <= 0) return hipSuccess;

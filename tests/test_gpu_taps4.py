@@ -74,3 +74,15 @@ def test_small_images(h):
         want = lifting.inv(c, "dd137", lv)
         r = d.inv(torch.from_numpy(c).to(dev()), "dd137", lv).cpu().numpy()
         assert np.abs(r - want).max() <= TOL * np.abs(want).max(), w
+
+
+@pytest.mark.parametrize("tdt", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n,h,w,levels", [(1, 55, 215, 2), (1, 56, 216, 2), (2, 57, 217, 3), (1, 112, 432, 2),
+                                          (3, 115, 650, 4), (3, 7, 9, 2), (1, 2030, 2050, 3), (260, 88, 216, 2),
+                                          (130, 88, 217, 2), (1, 2801, 2799, 2)])
+def test_two_levels_in_one_launch(tdt, n, h, w, levels):
+    # tiles of both levels are 216 pixels wide and 56 high; 88 (16-bit storage, forward) beyond 512 of those
+    x = torch.from_numpy(workloads.planes(n, h, w, seed=92)).to(dev()).to(tdt)
+    for direction in (d.fwd, d.inv):
+        print("taps4 pair", tdt, (n, h, w), levels, direction.__name__, flush=True)
+        assert torch.equal(direction(x, "dd137", levels), one_by_one(direction, x, levels))

@@ -361,6 +361,7 @@ int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int w
 // stack of planes (levels_in_launch), on the sums over the images.
 struct BatchPairStats {
     uint64_t tiles32, tiles48;    // two-level tiles of 32 and of 48 block rows
+    uint64_t rows32;              // rows of the former
     uint64_t tiles3[2];           // three-level tiles of 48 and of 64 block rows
     uint64_t cols112, cols128;    // tiles across, two-level and one-level, weighted by the image's rows
     uint64_t samples;
@@ -374,6 +375,7 @@ void add_pair_stats(int32_t h, int32_t w, int levels, BatchPairStats* st) {
         }
         dwt2::multi_tile_grid(h, w, 2, 32, &tx, &ty);
         st[l].tiles32 += (uint64_t)tx * (uint64_t)ty;
+        st[l].rows32 += (uint64_t)ty;
         dwt2::multi_tile_grid(h, w, 2, 48, &tx, &ty);
         st[l].tiles48 += (uint64_t)tx * (uint64_t)ty;
         st[l].cols112 += (uint64_t)tx * (uint64_t)h;
@@ -787,6 +789,9 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
         B.first[B.n] = (int8_t)l;
         B.levels[B.n] = (int8_t)n;
         B.rows[B.n] = (int8_t)rows;
+        // a chunk of about kRemapRows tile rows of the images' mean width
+        const uint64_t near = n == 1 ? (uint64_t)dwt2::kLevelChunk : dwt2::kRemapRows * st.tiles32 / st.rows32;
+        B.near[B.n] = near < 16 ? 16 : near > 4096 ? 4096 : (int32_t)near;
         launch_tiles[B.n] = (uint32_t)(n == 1 ? tiles[l] : n == 3 ? st.tiles3[rows == 64] : rows == 32 ? st.tiles32 : st.tiles48);
         l += n;
     }

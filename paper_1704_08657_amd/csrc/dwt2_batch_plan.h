@@ -163,6 +163,7 @@ __host__ __device__ inline size_t image_ll_bytes(int32_t h, int32_t w, int level
 struct BatchLaunches {
     int32_t n;
     int8_t first[32], levels[32], rows[32];
+    int32_t near[32];      // see deal_tiles
 };
 __host__ __device__ inline void multi_tile_grid(int32_t hl, int32_t wl, int levels, int rows, int32_t* tx, int32_t* ty) {
     const int32_t nEr = (hl + 1) / 2, nEc = (wl + 1) / 2;
@@ -178,8 +179,8 @@ __host__ __device__ inline uint64_t launch_tile_count(int32_t h, int32_t w, int 
     multi_tile_grid(hl, wl, levels, rows, &tx, &ty);
     return (uint64_t)tx * (uint64_t)ty;
 }
-// The batched level kernel deals its grid over the 8 XCDs in chunks of this
-// many consecutive tiles.
+// The batched kernel of one level deals its tiles over the 8 XCDs in chunks of
+// about this many consecutive ones (deal_tiles).
 constexpr int kLevelChunk = 64;
 
 struct LevelBatchLayout {

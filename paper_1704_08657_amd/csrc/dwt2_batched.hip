@@ -250,8 +250,8 @@ level_plan_kernel(const dwt2_image* imgs, int count, int levels, BatchLaunches B
     }
 }
 
-// The tile of this work-group in launch j of `total` tiles (grid: a multiple of
-// 8 chunks of kLevelChunk tiles): its image and its index within the image.
+// The tile of this work-group in launch j of `total` tiles, dealt in chunks of
+// `chunk` (deal_tiles): its image and its index within the image.
 // Work-groups are dealt round-robin over the 8 XCDs, so XCD x takes chunks x,
 // x + 8, ... of consecutive tiles (row-major within an image, images in order)
 // and the halo re-reads of neighbouring tiles hit its L2.  False past the last
@@ -260,9 +260,9 @@ level_plan_kernel(const dwt2_image* imgs, int count, int levels, BatchLaunches B
 // trips count: the total comes with the launch, and up to 64 images one read
 // (a lane each) finds both the image and its first tile.
 __device__ __forceinline__ bool batched_tile(const unsigned char* ws, const LevelBatchLayout& L, int count, int j,
-                                             uint32_t total, int* image, int* index) {
+                                             uint32_t total, uint32_t chunk, int* image, int* index) {
     const uint32_t b = blockIdx.x >> 3;
-    const uint32_t t = ((b / kLevelChunk) * 8 + (blockIdx.x & 7)) * kLevelChunk + b % kLevelChunk;
+    const uint32_t t = ((b / chunk) * 8 + (blockIdx.x & 7)) * chunk + b % chunk;
     if (t >= total) return false;
     // off[] is strictly increasing (every image has a tile)
     const uint32_t* off = reinterpret_cast<const uint32_t*>(ws + L.off_tile) + (size_t)j * (count + 1);
@@ -311,7 +311,8 @@ __device__ __forceinline__ BatchedBuffers batched_buffers(const dwt2_image& im, 
 // boundaries of the stream: no work-group waits for another.
 template <typename T, int SCH, int NW, int K, int BPL>
 __global__ void __launch_bounds__(NW * kLanes)
-batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, unsigned char* ws) {
+batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, uint32_t chunk,
+                     unsigned char* ws) {
     using V = typename St<T>::V;
     constexpr int kCoreBY = NW * K - 2 * kHalo;
     __shared__ TileLds<V, NW, BPL, K> lds;
@@ -319,7 +320,7 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const LevelBatchLayout L = level_batch_layout(count, levels);
     int i, tt;
-    if (!batched_tile(ws, L, count, j, total, &i, &tt)) return;
+    if (!batched_tile(ws, L, count, j, total, chunk, &i, &tt)) return;
     const dwt2_image im = imgs[i];
     LevelParams P{};
     int32_t hl, wl;
@@ -346,7 +347,8 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
 // with a launch for each level and the earlier border tiles).
 template <typename T, int SCH, int NW, int K, int LEVELS>
 __global__ void __launch_bounds__(NW * kLanes)
-batched_multi_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, unsigned char* ws) {
+batched_multi_kernel(const dwt2_image* imgs, int count, int levels, int j, int l, uint32_t total, uint32_t chunk,
+                     unsigned char* ws) {
     using V = typename St<T>::V;
     __shared__ pair::PairLds<V, NW> lds;
     __shared__ pair::PairPlane<V, NW * K> plane;
@@ -354,7 +356,7 @@ batched_multi_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     const LevelBatchLayout L = level_batch_layout(count, levels);
     int i, tt;
-    if (!batched_tile(ws, L, count, j, total, &i, &tt)) return;
+    if (!batched_tile(ws, L, count, j, total, chunk, &i, &tt)) return;
     const dwt2_image im = imgs[i];
     PairParams P{};
     int32_t hl, wl, hx, wx;
@@ -597,15 +599,16 @@ hipError_t launch_levels_shape(const BatchLaunches& B, const dwt2_image* dev_img
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int j = 0; j < B.n; ++j) {
-        const uint32_t chunks = (tiles[j] + kLevelChunk - 1) / kLevelChunk;
-        const dim3 grid((chunks + 7u) / 8u * 8u * kLevelChunk);
+        const Deal deal = deal_tiles(tiles[j], B.near[j]);
+        const dim3 grid((unsigned)deal.grid);
+        const uint32_t chunk = (uint32_t)deal.chunk;
         const int l = B.first[j];
 #define DWT2_MULTI(NW_, K_, LEVELS_)                                                                        \
     hipLaunchKernelGGL((batched_multi_kernel<T, kMultiScheme, NW_, K_, LEVELS_>), grid, dim3((NW_) * kLanes), 0, s, \
-                       dev_imgs, count, levels, j, l, tiles[j], w)
+                       dev_imgs, count, levels, j, l, tiles[j], chunk, w)
         if (B.levels[j] == 1)
             hipLaunchKernelGGL((batched_level_kernel<T, SCH, NW, K, BPL>), grid, dim3(NW * kLanes), 0, s, dev_imgs,
-                               count, levels, j, l, tiles[j], w);
+                               count, levels, j, l, tiles[j], chunk, w);
         else if constexpr (SCH != kMultiScheme)
             return hipErrorInvalidValue;
         else if (B.levels[j] == 3 && B.rows[j] == 48)

@@ -66,9 +66,29 @@ constexpr int kDefaultLdsConfig = 8;
 // The four-tap register tile kernel (DD 13/7): a halo of kHalo4 block rows
 // above and below a tile.
 constexpr int kHalo4 = 3;
-// Tile kernels deal work over the 8 XCDs in chunks of kRemapRows tile rows;
+// Tile kernels deal work over the 8 XCDs in chunks of about kRemapRows tile rows;
 // the grid is a multiple of 8 chunks.
 constexpr int kRemapRows = 2;
+// How a list of tiles is dealt: work-groups go round-robin over the 8 XCDs, XCD x
+// takes the chunks x, x + 8, ... of consecutive tiles, so that neighbours' halo
+// re-reads hit its L2.  The chunk is about `near` tiles, the size that gives every
+// XCD as many chunks: with chunks of exactly two tile rows some XCDs had one
+// more than others, which a launch of few chunks waits for.  Up to 4096 tiles twice
+// that, whose rows the caches hold all the same; up to 1024, which run at once, one
+// chunk for each XCD.  Two levels, us, before and now: 8192^2 BF16 74.4 and 68.7, inverse
+// 67.1 and 60.4; 4096^2 FP32 28.2 and 25.9, inverse 25.9 and 24.9; 3469 x 5197 adjoint
+// 32.6 and 30.1; 8192^2 FP32 105.5 and 106.0; 60 uneven images of 64 ... 2048 152.8 and 146.2.
+struct Deal {
+    int64_t chunk, grid;
+};
+inline Deal deal_tiles(int64_t tiles, int64_t near) {
+    if (tiles <= 4096) near *= 2;
+    const int64_t rounds = tiles > 1024 && tiles > 4 * near ? (tiles + 4 * near) / (8 * near) : 1;
+    const int64_t chunk = (tiles + 8 * rounds - 1) / (8 * rounds);
+    return {chunk, 8 * rounds * chunk};
+}
+// The most tiles one launch is given (deal_tiles' grid is less than half as many again).
+constexpr int64_t kMaxTiles = 0x40000000;
 // output block rows / columns of one tile (kAlgoTile, kAlgoLds)
 constexpr int core_rows(KernelConfig c) { return c.algo == kAlgoLds ? c.cy : c.waves * c.rows - 2 * kHalo; }
 constexpr int core_cols(KernelConfig c) { return c.algo == kAlgoLds ? c.cx : kLanes * c.bpl; }
@@ -95,6 +115,7 @@ struct LevelParams {
     // the streaming kernel takes one grid row per plane).
     int64_t in_ps, in_ll_ps, out_ps, out_ll_ps;
     int32_t planes;
+    int32_t chunk;     // set by the launcher, see deal_tiles
     // CDF 9/7, a level whose output the call's next level reads (forward:
     // the LL band of every level but the last; inverse / adjoint: the image
     // of every level but the finest): interior tiles store it with ordinary
@@ -116,8 +137,9 @@ struct PairParams {
     void* ll;
     int64_t ll_pitch, ll_ps;
     int32_t h, w;
-    int32_t tiles_x, tiles_y;     // set by the launcher, as is planes
+    int32_t tiles_x, tiles_y;     // set by the launcher, as are planes and chunk
     int32_t planes;
+    int32_t chunk;                // see deal_tiles
 };
 
 // Its tiles: NW * K block rows of the first level with a halo of kHalo2 above

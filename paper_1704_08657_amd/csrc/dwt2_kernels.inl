@@ -1421,7 +1421,7 @@ __device__ __forceinline__ LevelParams plane_params(const LevelParams& P, int pl
 __device__ __forceinline__ void fetch_params(const LevelParams& P) {
     asm volatile("" ::"s"(P.in), "s"(P.in_pitch), "s"(P.in_ll), "s"(P.in_ll_pitch), "s"(P.out), "s"(P.out_pitch),
                  "s"(P.out_ll), "s"(P.out_ll_pitch), "s"(P.h), "s"(P.w), "s"(P.tiles_x), "s"(P.tiles_y),
-                 "s"(P.in_ps), "s"(P.in_ll_ps), "s"(P.out_ps), "s"(P.out_ll_ps), "s"(P.planes));
+                 "s"(P.in_ps), "s"(P.in_ll_ps), "s"(P.out_ps), "s"(P.out_ll_ps), "s"(P.planes), "s"(P.chunk));
 }
 
 template <int DIR, int WAV, typename T, int SCH, int NW, int K, int BPL, bool LLC = false>
@@ -1433,16 +1433,15 @@ __global__ void __launch_bounds__(NW * kLanes) level_kernel(LevelParams P) {
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     fetch_params(P);
     // Work-groups are dealt round-robin over the 8 XCDs.  XCD x takes chunks
-    // x, x + 8, x + 16, ... of kRemapRows whole tile rows: horizontal halo
+    // x, x + 8, x + 16, ... of about kRemapRows tile rows: horizontal halo
     // re-reads stay in that XCD's L2 (and vertical ones within a chunk),
     // while the 8 XCDs work on adjacent chunks, so the image is swept by
     // one narrow window (8 chunks tall) rather than 8 distant ones.
     // The tiles of a plane batch form one list, plane after plane, dealt
     // the same way: small planes do not each round up to 8 chunks.
     const int nt = P.tiles_x * P.tiles_y;
-    const int chunk = kRemapRows * P.tiles_x;
     const int j = (int)(blockIdx.x >> 3);
-    const int g = ((j / chunk) * 8 + (int)(blockIdx.x & 7)) * chunk + j % chunk;
+    const int g = ((j / P.chunk) * 8 + (int)(blockIdx.x & 7)) * P.chunk + j % P.chunk;
     if (g >= nt * P.planes) return;               // uniform over the work-group
     const int pl = g / nt;
     const int t = g - pl * nt;

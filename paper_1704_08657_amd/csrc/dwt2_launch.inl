@@ -7,14 +7,11 @@ namespace kern {
 
 template <int DIR, int WAV, typename T, int SCH, int NW, int K, int BPL, bool LLC = false>
 hipError_t launch_grid(const LevelParams& p, int planes, hipStream_t s) {
-    // the tiles of all planes, rounded up to a multiple of 8 chunks of
-    // kRemapRows tile rows (see level_kernel); planes beyond what one grid
+    // the tiles of all planes (see level_kernel); planes beyond what one grid
     // holds go to further launches
     const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
-    const int64_t chunk = (int64_t)kRemapRows * p.tiles_x;
-    const int64_t limit = 0x7fffffff - 8 * chunk;
-    if (nt < 1 || nt > limit) return hipErrorInvalidConfiguration;
-    const int64_t per = limit / nt;
+    if (nt < 1 || nt > kMaxTiles) return hipErrorInvalidConfiguration;
+    const int64_t per = kMaxTiles / nt;
     for (int64_t p0 = 0; p0 < planes; p0 += per) {
         LevelParams q = p;
         q.planes = (int32_t)(planes - p0 < per ? planes - p0 : per);
@@ -24,8 +21,9 @@ hipError_t launch_grid(const LevelParams& p, int planes, hipStream_t s) {
             if (q.out) q.out = static_cast<T*>(q.out) + p0 * q.out_ps;
             if (q.out_ll) q.out_ll = static_cast<T*>(q.out_ll) + p0 * q.out_ll_ps;
         }
-        const int64_t grid = (nt * q.planes + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
-        hipLaunchKernelGGL((level_kernel<DIR, WAV, T, SCH, NW, K, BPL, LLC>), dim3((unsigned)grid),
+        const Deal deal = deal_tiles(nt * q.planes, (int64_t)kRemapRows * p.tiles_x);
+        q.chunk = (int32_t)deal.chunk;
+        hipLaunchKernelGGL((level_kernel<DIR, WAV, T, SCH, NW, K, BPL, LLC>), dim3((unsigned)deal.grid),
                            dim3(NW * kLanes), 0, s, q);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

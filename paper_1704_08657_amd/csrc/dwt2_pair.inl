@@ -589,12 +589,12 @@ template <typename T>
 __device__ __forceinline__ bool pick_tile(const PairParams& P, PairParams& Q, int& tx, int& ty) {
     // every kernel argument in one round trip, see fetch_params
     asm volatile("" ::"s"(P.in), "s"(P.in_pitch), "s"(P.in_ps), "s"(P.out), "s"(P.out_pitch), "s"(P.out_ps), "s"(P.ll),
-                 "s"(P.ll_pitch), "s"(P.ll_ps), "s"(P.h), "s"(P.w), "s"(P.tiles_x), "s"(P.tiles_y), "s"(P.planes));
+                 "s"(P.ll_pitch), "s"(P.ll_ps), "s"(P.h), "s"(P.w), "s"(P.tiles_x), "s"(P.tiles_y), "s"(P.planes),
+                 "s"(P.chunk));
     // XCD remap of the tile list (all planes), as in the one-level kernel
     const int nt = P.tiles_x * P.tiles_y;
-    const int chunk = kRemapRows * P.tiles_x;
     const int j = (int)(blockIdx.x >> 3);
-    const int n = ((j / chunk) * 8 + (int)(blockIdx.x & 7)) * chunk + j % chunk;
+    const int n = ((j / P.chunk) * 8 + (int)(blockIdx.x & 7)) * P.chunk + j % P.chunk;
     if (n >= nt * P.planes) return false;
     const int pl = n / nt;
     const int t = n - pl * nt;
@@ -628,21 +628,19 @@ template <typename T>
 hipError_t launch_tiles(void (*kernel)(PairParams), int cx, int cy, int waves, PairParams p, int planes, hipStream_t s) {
     p.tiles_x = ((p.w + 1) / 2 + cx - 1) / cx;
     p.tiles_y = ((p.h + 1) / 2 + cy - 1) / cy;
-    // the tiles of all planes, rounded up to a multiple of 8 chunks; planes
-    // beyond what one grid holds go to further launches
+    // the tiles of all planes; planes beyond what one grid holds go to further launches
     const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
-    const int64_t chunk = (int64_t)kRemapRows * p.tiles_x;
-    const int64_t limit = 0x7fffffff - 8 * chunk;
-    if (nt < 1 || nt > limit) return hipErrorInvalidConfiguration;
-    const int64_t per = limit / nt;
+    if (nt < 1 || nt > kMaxTiles) return hipErrorInvalidConfiguration;
+    const int64_t per = kMaxTiles / nt;
     for (int64_t p0 = 0; p0 < planes; p0 += per) {
         PairParams q = p;
         q.planes = (int32_t)(planes - p0 < per ? planes - p0 : per);
         q.in = static_cast<const T*>(p.in) + p0 * p.in_ps;
         q.out = static_cast<T*>(p.out) + p0 * p.out_ps;
         q.ll = static_cast<T*>(p.ll) + p0 * p.ll_ps;
-        const int64_t grid = (nt * q.planes + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(waves * kLanes), 0, s, q);
+        const Deal deal = deal_tiles(nt * q.planes, (int64_t)kRemapRows * p.tiles_x);
+        q.chunk = (int32_t)deal.chunk;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)deal.grid), dim3(waves * kLanes), 0, s, q);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

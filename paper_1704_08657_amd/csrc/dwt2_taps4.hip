@@ -434,9 +434,8 @@ __global__ void __launch_bounds__(NW * kLanes) taps4_kernel(LevelParams P0) {
     fetch_params(P0);
     // XCD remap of the tile list (all planes), as in the two-tap tile kernel
     const int nt = P0.tiles_x * P0.tiles_y;
-    const int chunk = kRemapRows * P0.tiles_x;
     const int j = (int)(blockIdx.x >> 3);
-    const int n = ((j / chunk) * 8 + (int)(blockIdx.x & 7)) * chunk + j % chunk;
+    const int n = ((j / P0.chunk) * 8 + (int)(blockIdx.x & 7)) * P0.chunk + j % P0.chunk;
     if (n >= nt * P0.planes) return;              // uniform over the work-group
     const int pl = n / nt;
     const int t = n - pl * nt;
@@ -484,10 +483,8 @@ hipError_t launch_rows(LevelParams p, int planes, hipStream_t s) {
     p.tiles_x = ((p.w + 1) / 2 + kCols - 1) / kCols;
     p.tiles_y = ((p.h + 1) / 2 + CY - 1) / CY;
     const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
-    const int64_t chunk = (int64_t)kRemapRows * p.tiles_x;
-    const int64_t limit = 0x7fffffff - 8 * chunk;
-    if (nt < 1 || nt > limit) return hipErrorInvalidConfiguration;
-    const int64_t per = limit / nt;
+    if (nt < 1 || nt > kMaxTiles) return hipErrorInvalidConfiguration;
+    const int64_t per = kMaxTiles / nt;
     for (int64_t p0 = 0; p0 < planes; p0 += per) {
         LevelParams q = p;
         q.planes = (int32_t)(planes - p0 < per ? planes - p0 : per);
@@ -497,8 +494,9 @@ hipError_t launch_rows(LevelParams p, int planes, hipStream_t s) {
             if (q.out) q.out = static_cast<T*>(q.out) + p0 * q.out_ps;
             if (q.out_ll) q.out_ll = static_cast<T*>(q.out_ll) + p0 * q.out_ll_ps;
         }
-        const int64_t grid = (nt * q.planes + 8 * chunk - 1) / (8 * chunk) * (8 * chunk);
-        hipLaunchKernelGGL((taps4_kernel<DIR, T, SCH, kWaves, K, kBpl, kEdge>), dim3((unsigned)grid),
+        const Deal deal = deal_tiles(nt * q.planes, (int64_t)kRemapRows * p.tiles_x);
+        q.chunk = (int32_t)deal.chunk;
+        hipLaunchKernelGGL((taps4_kernel<DIR, T, SCH, kWaves, K, kBpl, kEdge>), dim3((unsigned)deal.grid),
                            dim3(kWaves * kLanes), 0, s, q);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -216,7 +216,7 @@ int dwt2_workspace_bytes(int32_t height, int32_t width, int levels,
 /* Forward transform (Section "Proposed Schemes", non-separable lifting):
  * src = image (height x width, src_pitch), dst = Mallat pyramid
  * (height x width, dst_pitch).  Multi-level: levels >= 1, one launch per
- * level, or (calls with flags 0, where it is the faster way) per two levels,
+ * level, or (calls with flags 0, where it is the faster way) per two or three,
  * with the same results (DWT2_FLAG_PERSISTENT: one persistent launch for all
  * levels). */
 int dwt2_fwd(const void* src, void* dst, int32_t height, int32_t width,
@@ -297,7 +297,7 @@ int dwt2_workspace_bytes_batched(const dwt2_image* images, int count, dwt2_dtype
  * applied to each image as dwt2_fwd would): `count` independent images of any
  * (uneven) sizes, every one transformed to `levels` levels, on `stream`.  By
  * default a planner launch plus one launch per level, or (flags 0, where it is
- * the faster way) per two levels, each covering the tiles of all images.  With DWT2_FLAG_PERSISTENT: a planner
+ * the faster way) per two or three, each covering the tiles of all images.  With DWT2_FLAG_PERSISTENT: a planner
  * launch plus one persistent launch for every level; its work-groups take
  * tiles (of every image) from work queues, level after level, and a tile of
  * level l >= 1 first waits until the tiles of level l - 1 whose LL rows it

@@ -317,7 +317,7 @@ def fwd(x, wavelet: str = "cdf97", levels: int = 1, split: bool = False, out=Non
         separable: bool = False, factored: bool = False, polyconv: bool = False, persistent: bool = False,
         workspace=None, fused: bool = False):
     """Forward transform of every [H, W] plane of x into a Mallat pyramid
-    (all planes in one call: one launch per level or two levels, or with `persistent` one
+    (all planes in one call: one launch per level, two or three, or with `persistent` one
     persistent launch for every level).  `workspace`: a uint8 device tensor of at least
     dwt2_workspace_bytes_planes bytes to use instead of a fresh one (its
     status can be read with workspace_status afterwards).  `config` selects a
@@ -421,7 +421,7 @@ class BatchedForward:
 
 def fwd_batched(images, levels: int = 1, split: bool = False, config=None, outs=None, persistent: bool = False):
     """Forward CDF 9/7 of a list of [H, W] images of any sizes (a planner
-    launch plus one launch per level or two levels, or with `persistent` one persistent
+    launch plus one launch per level, two or three, or with `persistent` one persistent
     launch for every level); returns the list of Mallat pyramids."""
     return BatchedForward(images, levels, split, config, outs, persistent).run()
 

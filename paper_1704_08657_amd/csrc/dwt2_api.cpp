@@ -702,7 +702,7 @@ int dwt2_workspace_bytes_batched(const dwt2_image* images, int count, dwt2_dtype
         if (im.height < 2 || im.width < 2 || im.height > kMaxSide || im.width > kMaxSide) return DWT2_E_SHAPE;
         if (levels < 1 || levels > max_levels(im.height, im.width)) return DWT2_E_LEVELS;
     }
-    // one launch per level: tile tables and ping-pong LL buffers; the
+    // one launch per level, two or three: tile tables and ping-pong LL buffers; the
     // persistent launch: work tables and one LL band per level
     const dwt2::LevelBatchLayout L = dwt2::level_batch_layout(count, levels);
     size_t n = L.off_ll;

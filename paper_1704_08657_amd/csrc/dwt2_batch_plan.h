@@ -1,7 +1,7 @@
 // Work plans of the batched forward transform, shared by the host (argument
 // checks, workspace size, grid sizes), the planner and transform kernels,
 // and the host checks in tests/host, so all of them derive the same tables
-// from the image shapes.  Two plans: one launch per level for all images
+// from the image shapes.  Two plans: one launch per level, two or three for all images
 // (default), and one persistent launch for every level (a batch of images of
 // any sizes, or a stack of equal planes).
 //
@@ -146,7 +146,7 @@ __host__ __device__ inline size_t image_ll_bytes(int32_t h, int32_t w, int level
     return ll_band_offset(h, w, levels - 1, es);
 }
 
-// ---- one launch per level (the default path of dwt2_fwd_batched) ----------
+// ---- one launch per level, two or three (the default path) ----------------
 // Workspace, from its start:
 //   uint32 tile_off[levels][count + 1]   first tile of image i within the
 //                                        launch l (of one, two or three

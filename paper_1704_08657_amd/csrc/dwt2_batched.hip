@@ -343,7 +343,7 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
 
 // Launch j: levels l and l + 1, or l to l + 2, of every image.  60 uneven images
 // of 64 ... 2048 pixels a side, FP32, 5 levels: 240 us a call with a launch for
-// each level, 193 in three (2, 2, 1 levels); 16 of 64 ... 300: 25.6 us in two (88
+// each level, 188 in three (2, 2, 1 levels); 16 of 64 ... 300: 25.6 us in two (88
 // with a launch for each level and the earlier border tiles).
 template <typename T, int SCH, int NW, int K, int LEVELS>
 __global__ void __launch_bounds__(NW * kLanes)

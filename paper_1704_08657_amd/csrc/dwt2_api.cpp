@@ -318,9 +318,9 @@ int launch_planes(dwt2::Direction dir, int wavelet, int dtype, unsigned flags, i
             q.out_ll = lp.out_ll ? (char*)lp.out_ll + (size_t)p0 * (size_t)lp.out_ll_ps * es : nullptr;
         }
         // DD 13/7 without a named configuration or scheme (or with the fused
-        // one): the four-tap register tile kernel, whose steps are fused for FP32
+        // one), unless its tiles are too many: the four-tap register tile kernel, whose steps are fused for FP32
         // (memory-bound) and factored for 16-bit storage (bound by its arithmetic)
-        const bool taps4 = wavelet == DWT2_DD137 && !(flags & ~DWT2_FLAG_FUSED);
+        const bool taps4 = wavelet == DWT2_DD137 && !(flags & ~DWT2_FLAG_FUSED) && dwt2::taps4_fits(lp.h, lp.w);
         const dwt2::Scheme sch4 = flags || dtype == DWT2_F32 ? dwt2::kSchemeFused : dwt2::kSchemeFactored;
         const int rc = taps4 ? report(dwt2::launch_taps4(dir, to_dtype(dtype), sch4, q, n, s))
                              : report(dwt2::launch_level(dir, to_wav(wavelet), to_dtype(dtype),

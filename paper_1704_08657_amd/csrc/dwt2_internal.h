@@ -66,6 +66,8 @@ constexpr int kDefaultLdsConfig = 8;
 // The four-tap register tile kernel (DD 13/7): a halo of kHalo4 block rows
 // above and below a tile.
 constexpr int kHalo4 = 3;
+// Waves of its work-groups, and the block columns and rows of its taller tile.
+constexpr int kWaves4 = 4, kCols4 = 120, kRows4 = 14;
 // Tile kernels deal work over the 8 XCDs in chunks of about kRemapRows tile rows;
 // the grid is a multiple of 8 chunks.
 constexpr int kRemapRows = 2;
@@ -78,20 +80,47 @@ constexpr int kRemapRows = 2;
 // chunk for each XCD.  Two levels, us, before and now: 8192^2 BF16 74.4 and 68.7, inverse
 // 67.1 and 60.4; 4096^2 FP32 28.2 and 25.9, inverse 25.9 and 24.9; 3469 x 5197 adjoint
 // 32.6 and 30.1; 8192^2 FP32 105.5 and 106.0; 60 uneven images of 64 ... 2048 152.8 and 146.2.
+// A grid beyond `most` work-groups gives way to one chunk for each XCD, of fewer
+// than 8 work-groups more than tiles.
 struct Deal {
     int64_t chunk, grid;
 };
-inline Deal deal_tiles(int64_t tiles, int64_t near) {
+inline Deal deal_tiles(int64_t tiles, int64_t near, int64_t most = 0x7fffffff) {
     if (tiles <= 4096) near *= 2;
-    const int64_t rounds = tiles > 1024 && tiles > 4 * near ? (tiles + 4 * near) / (8 * near) : 1;
+    int64_t rounds = tiles > 1024 && tiles > 4 * near ? (tiles + 4 * near) / (8 * near) : 1;
+    if (8 * rounds * ((tiles + 8 * rounds - 1) / (8 * rounds)) > most) rounds = 1;
     const int64_t chunk = (tiles + 8 * rounds - 1) / (8 * rounds);
     return {chunk, 8 * rounds * chunk};
 }
-// The most tiles one launch is given (deal_tiles' grid is less than half as many again).
-constexpr int64_t kMaxTiles = 0x40000000;
+// A launch is of fewer than 2^32 work-items: the work-groups of `waves` waves it
+// may have, and the tiles it is then given (see deal_tiles).
+constexpr int64_t max_groups(int waves) { return (((int64_t)1 << 32) - 1) / (waves * kLanes); }
+constexpr int64_t max_tiles(int waves) { return max_groups(waves) - 7; }
+constexpr int64_t kMaxTiles = max_tiles(1);
+static_assert(max_groups(1) <= 0x7fffffff, "tile and work-group numbers fit 32 bits");
+// The launches that cover `planes` planes of nt tiles each, as many planes in each
+// as it may have: launch(first plane, planes, deal) for one after the other, up to an error.
+template <typename F>
+inline hipError_t for_each_launch(int64_t nt, int64_t near, int waves, int64_t planes, const F& launch) {
+    if (nt < 1 || nt > max_tiles(waves)) return hipErrorInvalidConfiguration;
+    const int64_t per = max_tiles(waves) / nt;
+    for (int64_t p0 = 0; p0 < planes; p0 += per) {
+        const int64_t n = planes - p0 < per ? planes - p0 : per;
+        const hipError_t e = launch(p0, (int32_t)n, deal_tiles(nt * n, near, max_groups(waves)));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 // output block rows / columns of one tile (kAlgoTile, kAlgoLds)
 constexpr int core_rows(KernelConfig c) { return c.algo == kAlgoLds ? c.cy : c.waves * c.rows - 2 * kHalo; }
 constexpr int core_cols(KernelConfig c) { return c.algo == kAlgoLds ? c.cx : kLanes * c.bpl; }
+
+// Whether a launch may have the tiles of one h x w plane on that kernel.  The
+// LDS-plane kernel, whose tiles are 16 rows, takes the narrow images up to 2^29
+// rows that are beyond.
+inline bool taps4_fits(int32_t h, int32_t w) {
+    return (int64_t)(((w + 1) / 2 + kCols4 - 1) / kCols4) * (((h + 1) / 2 + kRows4 - 1) / kRows4) <= max_tiles(kWaves4);
+}
 
 // One level of a transform.  Forward: `in` is the h x w image of this level,
 // `out` the origin of this level's region of the Mallat pyramid (details are
@@ -179,8 +208,10 @@ inline int pair_rows(Direction dir, size_t es, int64_t tiles32, int64_t tiles48,
 //   * 16-bit storage, forward, up to 2^26 samples: beyond, the recomputed
 //     halo costs what the LL band saves (3 x 8192^2 BF16 188 / 193,
 //     3 x 4096^2 56 / 53, inverse 198 / 176).
+// Never when one plane has more tiles than a launch may.
 inline bool pair_pays(Direction dir, Dtype dt, int32_t h, int32_t w, int32_t planes) {
     if (pair_tiles(h, w, planes, 32) <= 640) return true;
+    if (pair_tiles(h, w, 1, 32) > max_tiles(8)) return false;
     const int32_t nc = (w + 1) / 2;
     if (2 * ((nc + kPairCols - 1) / kPairCols) >= 3 * ((nc + 2 * kLanes - 1) / (2 * kLanes))) return false;
     return !(dir == kForward && (dt == kBF16 || dt == kF16) && (int64_t)h * w * planes > (1 << 26));

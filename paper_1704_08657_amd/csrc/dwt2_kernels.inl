@@ -1412,6 +1412,15 @@ __device__ __forceinline__ LevelParams plane_params(const LevelParams& P, int pl
     Q.out_ll = plane_ptr<T>(P.out_ll, pl, P.out_ll_ps);
     return Q;
 }
+// The same on the host: the parameters of the planes from p0 on.
+template <typename T>
+LevelParams from_plane(LevelParams p, int64_t p0) {
+    if (p.in) p.in = static_cast<const T*>(p.in) + p0 * p.in_ps;
+    if (p.in_ll) p.in_ll = static_cast<const T*>(p.in_ll) + p0 * p.in_ll_ps;
+    if (p.out) p.out = static_cast<T*>(p.out) + p0 * p.out_ps;
+    if (p.out_ll) p.out_ll = static_cast<T*>(p.out_ll) + p0 * p.out_ll_ps;
+    return p;
+}
 
 // Every field of the level parameters is taken into SGPRs here, before the
 // first branch and before any value derived from them: the scalar loads of

@@ -7,28 +7,17 @@ namespace kern {
 
 template <int DIR, int WAV, typename T, int SCH, int NW, int K, int BPL, bool LLC = false>
 hipError_t launch_grid(const LevelParams& p, int planes, hipStream_t s) {
-    // the tiles of all planes (see level_kernel); planes beyond what one grid
-    // holds go to further launches
-    const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
-    if (nt < 1 || nt > kMaxTiles) return hipErrorInvalidConfiguration;
-    const int64_t per = kMaxTiles / nt;
-    for (int64_t p0 = 0; p0 < planes; p0 += per) {
-        LevelParams q = p;
-        q.planes = (int32_t)(planes - p0 < per ? planes - p0 : per);
-        if (p0 > 0) {
-            if (q.in) q.in = static_cast<const T*>(q.in) + p0 * q.in_ps;
-            if (q.in_ll) q.in_ll = static_cast<const T*>(q.in_ll) + p0 * q.in_ll_ps;
-            if (q.out) q.out = static_cast<T*>(q.out) + p0 * q.out_ps;
-            if (q.out_ll) q.out_ll = static_cast<T*>(q.out_ll) + p0 * q.out_ll_ps;
-        }
-        const Deal deal = deal_tiles(nt * q.planes, (int64_t)kRemapRows * p.tiles_x);
+    // the tiles of all planes (see level_kernel); planes beyond what one launch
+    // may have go to further ones
+    return for_each_launch((int64_t)p.tiles_x * p.tiles_y, (int64_t)kRemapRows * p.tiles_x, NW, planes,
+                           [&](int64_t p0, int32_t n, Deal deal) {
+        LevelParams q = from_plane<T>(p, p0);
+        q.planes = n;
         q.chunk = (int32_t)deal.chunk;
         hipLaunchKernelGGL((level_kernel<DIR, WAV, T, SCH, NW, K, BPL, LLC>), dim3((unsigned)deal.grid),
                            dim3(NW * kLanes), 0, s, q);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+        return hipGetLastError();
+    });
 }
 
 // A CDF 9/7 level whose output the next level of the call reads may store it

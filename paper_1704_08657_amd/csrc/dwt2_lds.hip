@@ -493,7 +493,8 @@ template <int DIR, int WAV, int SCH, typename T, int CX, int CY>
 hipError_t launch_t(const LevelParams& p, int planes, hipStream_t s) {
     const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
     const int64_t chunk = (int64_t)kRemapRows * p.tiles_x;
-    const int64_t limit = 0x7fffffff - 8 * chunk;
+    // whole rounds of 8 chunks, of at most max_groups work-groups together
+    const int64_t limit = max_groups(kThreads / kLanes) / (8 * chunk) * (8 * chunk);
     if (nt < 1 || nt > limit) return hipErrorInvalidConfiguration;
     const int64_t per = limit / nt;
     for (int64_t p0 = 0; p0 < planes; p0 += per) {

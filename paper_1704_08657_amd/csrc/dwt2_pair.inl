@@ -628,23 +628,18 @@ template <typename T>
 hipError_t launch_tiles(void (*kernel)(PairParams), int cx, int cy, int waves, PairParams p, int planes, hipStream_t s) {
     p.tiles_x = ((p.w + 1) / 2 + cx - 1) / cx;
     p.tiles_y = ((p.h + 1) / 2 + cy - 1) / cy;
-    // the tiles of all planes; planes beyond what one grid holds go to further launches
-    const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
-    if (nt < 1 || nt > kMaxTiles) return hipErrorInvalidConfiguration;
-    const int64_t per = kMaxTiles / nt;
-    for (int64_t p0 = 0; p0 < planes; p0 += per) {
+    // the tiles of all planes; planes beyond what one launch may have go to further ones
+    return for_each_launch((int64_t)p.tiles_x * p.tiles_y, (int64_t)kRemapRows * p.tiles_x, waves, planes,
+                           [&](int64_t p0, int32_t n, Deal deal) {
         PairParams q = p;
-        q.planes = (int32_t)(planes - p0 < per ? planes - p0 : per);
+        q.planes = n;
         q.in = static_cast<const T*>(p.in) + p0 * p.in_ps;
         q.out = static_cast<T*>(p.out) + p0 * p.out_ps;
         q.ll = static_cast<T*>(p.ll) + p0 * p.ll_ps;
-        const Deal deal = deal_tiles(nt * q.planes, (int64_t)kRemapRows * p.tiles_x);
         q.chunk = (int32_t)deal.chunk;
         hipLaunchKernelGGL(kernel, dim3((unsigned)deal.grid), dim3(waves * kLanes), 0, s, q);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+        return hipGetLastError();
+    });
 }
 template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
 hipError_t launch_shape(const PairParams& p, int planes, hipStream_t s) {

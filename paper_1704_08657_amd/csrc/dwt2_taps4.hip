@@ -476,32 +476,22 @@ __global__ void __launch_bounds__(NW * kLanes) taps4_kernel(LevelParams P0) {
 // less time from launch to end, taller ones recompute fewer halo rows.
 constexpr int kWaves = 4, kBpl = 2, kEdge = 2;
 constexpr int kCols = (kLanes - 2 * kEdge) * kBpl;
+static_assert(kCols == kCols4 && kWaves == kWaves4 && kWaves * 5 - 2 * kHalo4 == kRows4, "taps4_fits");
 
 template <int DIR, typename T, int SCH, int K>
 hipError_t launch_rows(LevelParams p, int planes, hipStream_t s) {
     constexpr int CY = kWaves * K - 2 * kHalo4;
     p.tiles_x = ((p.w + 1) / 2 + kCols - 1) / kCols;
     p.tiles_y = ((p.h + 1) / 2 + CY - 1) / CY;
-    const int64_t nt = (int64_t)p.tiles_x * p.tiles_y;
-    if (nt < 1 || nt > kMaxTiles) return hipErrorInvalidConfiguration;
-    const int64_t per = kMaxTiles / nt;
-    for (int64_t p0 = 0; p0 < planes; p0 += per) {
-        LevelParams q = p;
-        q.planes = (int32_t)(planes - p0 < per ? planes - p0 : per);
-        if (p0 > 0) {
-            if (q.in) q.in = static_cast<const T*>(q.in) + p0 * q.in_ps;
-            if (q.in_ll) q.in_ll = static_cast<const T*>(q.in_ll) + p0 * q.in_ll_ps;
-            if (q.out) q.out = static_cast<T*>(q.out) + p0 * q.out_ps;
-            if (q.out_ll) q.out_ll = static_cast<T*>(q.out_ll) + p0 * q.out_ll_ps;
-        }
-        const Deal deal = deal_tiles(nt * q.planes, (int64_t)kRemapRows * p.tiles_x);
+    return for_each_launch((int64_t)p.tiles_x * p.tiles_y, (int64_t)kRemapRows * p.tiles_x, kWaves, planes,
+                           [&](int64_t p0, int32_t n, Deal deal) {
+        LevelParams q = from_plane<T>(p, p0);
+        q.planes = n;
         q.chunk = (int32_t)deal.chunk;
         hipLaunchKernelGGL((taps4_kernel<DIR, T, SCH, kWaves, K, kBpl, kEdge>), dim3((unsigned)deal.grid),
                            dim3(kWaves * kLanes), 0, s, q);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+        return hipGetLastError();
+    });
 }
 
 // A level whose tiles all run at once (four work-groups on each of 256 CUs)

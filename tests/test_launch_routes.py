@@ -1,0 +1,66 @@
+"""Which kernels the calls launch, and in what grids: tests/host/launch_trace.cpp runs the
+library's entry points on the host and records the launches in place of making them."""
+import os
+import subprocess
+
+import pytest
+
+import paper_1704_08657_amd as d
+from test_batch_plan import ROOT, build_and_run, needs_tools
+
+pytestmark = [needs_tools,
+              pytest.mark.skipif(not os.path.exists(d.LIB_PATH), reason="the library is not built")]
+DTYPES = {"f32": d.DWT2_F32, "bf16": d.DWT2_BF16, "f16": d.DWT2_F16, "i32": d.DWT2_I32}
+
+
+@pytest.fixture(scope="module")
+def trace(tmp_path_factory):
+    """trace(calls): for each call its status and its launches (kernel, work-groups, threads)."""
+    exe = tmp_path_factory.mktemp("host") / "launch_trace"
+    subprocess.run(["g++", "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "host", "launch_trace.cpp"),
+                    "-rdynamic", "-ldl", "-o", str(exe)], check=True)
+    names = {}
+    for line in subprocess.run(["nm", "-C", d.LIB_PATH], capture_output=True, text=True, check=True).stdout.splitlines():
+        f = line.split(" ", 2)
+        if len(f) == 3 and f[0] and "_kernel" in f[2] and "device_stub" not in f[2]:
+            names[int(f[0], 16)] = f[2].split("(dwt2::")[0]
+
+    def run(calls):
+        r = subprocess.run([str(exe), d.LIB_PATH], input="\n".join(calls) + "\n", capture_output=True, text=True,
+                           timeout=300)
+        assert r.returncode == 0, r.stderr
+        out = []
+        for line in r.stdout.splitlines():
+            st, *launches = line.split()
+            out.append((int(st), [(names[int(a, 16)], int(g), int(t)) for a, g, t in
+                                  (x.split(":") for x in launches)]))
+        assert len(out) == len(calls)
+        return out
+    return run
+
+
+def planes(direction, wavelet, dtype, n, h, w, levels, flags=0):
+    return f"planes {direction} {d.WAVELETS[wavelet]} {DTYPES[dtype]} {n} {h} {w} {levels} {flags}"
+
+
+def test_split_of_a_plane_stack(tmp_path):
+    r = build_and_run(tmp_path, "launch_limit_check")
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert "bad 0" in r.stdout
+
+
+@pytest.mark.parametrize("wavelet,dtype", [("cdf97", "f32"), ("cdf97", "bf16"), ("cdf53", "i32"), ("cdf53f", "f16"),
+                                           ("dd137", "f32"), ("dd137", "bf16")])
+def test_launches_stay_below_the_work_item_limit(trace, wavelet, dtype):
+    """Stacks of 2^23 planes and more, and single narrow images of very many tiles: every
+    launch is of fewer than 2^32 work-items."""
+    shapes = [((1 << 23) - 1, 4, 4, 2), (1 << 23, 4, 4, 2), (9000000, 4, 4, 1), (9000000, 16, 8, 3), (40000000, 4, 4, 2),
+              (70000000, 2, 2, 1), (3000000, 100, 4, 2), (1, 1 << 27, 2, 1), (1, 1 << 27, 3, 2), (1, 330000000, 3, 2),
+              (1, 390000000, 3, 2), (1, 460000000, 2, 1)]
+    calls = [planes(direction, wavelet, dtype, *s) for s in shapes for direction in ("fwd", "inv", "adj")
+             if direction != "adj" or wavelet == "cdf97"]
+    for call, (st, launches) in zip(calls, trace(calls)):
+        assert st == 0 and launches, call
+        for name, groups, threads in launches:
+            assert groups * threads < 1 << 32, (call, name, groups, threads)

@@ -315,7 +315,9 @@ int dwt2_workspace_bytes_batched(const dwt2_image* images, int count, dwt2_dtype
  * overlap the workspace, and no image's dst may overlap the dst or the src of
  * any image (sources may overlap one another): every such batch is rejected
  * with DWT2_E_ALIAS.  The sum over the images of one level's tiles must stay
- * below 2^31 - 2^16 (else DWT2_E_SHAPE).  Results equal dwt2_fwd on each
+ * below 2^31 - 2^16 and, without DWT2_FLAG_PERSISTENT, take fewer than 2^32
+ * threads in one launch (16.7 million tiles of 4 waves; else DWT2_E_SHAPE).
+ * Results equal dwt2_fwd on each
  * image (bit-identical for the same configuration). */
 int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_images, int count,
                      dwt2_dtype dtype, dwt2_wavelet wavelet, int levels, dwt2_boundary boundary,

@@ -387,7 +387,7 @@ void add_pair_stats(int32_t h, int32_t w, int levels, BatchPairStats* st) {
 }
 bool batch_pair_pays(int dtype, const BatchPairStats& st) {
     if (st.tiles32 <= 640) return true;
-    if (st.tiles32 > 0x7fff0000ull) return false;
+    if (st.tiles32 > (uint64_t)dwt2::max_tiles(8)) return false;    // more than a launch may have
     if (2 * st.cols112 >= 3 * st.cols128) return false;
     return !(dtype != DWT2_F32 && st.samples > (1 << 26));
 }
@@ -756,6 +756,7 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
         all_tiles += t;
     }
     if (batch_spans_alias(host_images, count, es)) return DWT2_E_ALIAS;
+    const bool persistent = (flags & DWT2_FLAG_PERSISTENT) && levels > 1;
     // ticket numbers and counters are 32-bit
     for (int l = 0; l < levels; ++l)
         if (tiles[l] > 0x7fff0000ull) return DWT2_E_SHAPE;
@@ -771,7 +772,7 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
             return DWT2_E_ALIAS;
     }
     const dwt2::Scheme sch = scheme_of(flags, dtype, wavelet, false);
-    if ((flags & DWT2_FLAG_PERSISTENT) && levels > 1) {
+    if (persistent) {
         const dwt2::ImageSet S{device_images, nullptr, nullptr, 0, 0, 0, 0, 0, 0};
         const dwt2::BatchLayout L = dwt2::batch_layout(count, levels, chunks);
         return report(dwt2::launch_fwd_persistent(to_dtype(dtype), sch, cfg, S, count, levels, workspace, L,
@@ -786,6 +787,7 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
         const int n = !pairs || l + 1 >= levels ? 1 : rows3 ? 3 : batch_pair_pays(dtype, st) ? 2 : 1;
         const int rows = n != 2 ? rows3 : dwt2::pair_rows(dwt2::kForward, es, (int64_t)st.tiles32, (int64_t)st.tiles48,
                                                           (int64_t)st.samples);
+        if (n == 1 && tiles[l] > (uint64_t)dwt2::max_tiles(kc.waves)) return DWT2_E_SHAPE;
         B.first[B.n] = (int8_t)l;
         B.levels[B.n] = (int8_t)n;
         B.rows[B.n] = (int8_t)rows;

@@ -599,7 +599,8 @@ hipError_t launch_levels_shape(const BatchLaunches& B, const dwt2_image* dev_img
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int j = 0; j < B.n; ++j) {
-        const Deal deal = deal_tiles(tiles[j], B.near[j]);
+        const int waves = B.levels[j] == 1 ? NW : B.levels[j] == 2 ? 8 : B.rows[j] / kTripleK;
+        const Deal deal = deal_tiles(tiles[j], B.near[j], max_groups(waves));
         const dim3 grid((unsigned)deal.grid);
         const uint32_t chunk = (uint32_t)deal.chunk;
         const int l = B.first[j];

@@ -5,7 +5,7 @@
 //
 // launch_trace LIB, then one call a line on stdin:
 //   planes fwd|inv|adj WAVELET DTYPE PLANES H W LEVELS FLAGS
-//   batch DTYPE LEVELS FLAGS H W [H W ...]
+//   batch DTYPE LEVELS FLAGS COUNT H W [H W ...]      (COUNT times these sizes)
 // prints for each call its status and per launch "offset:work-groups:threads",
 // offset being the kernel's symbol within the library.
 #include <dlfcn.h>
@@ -79,13 +79,16 @@ int main(int argc, char** argv) {
         } else if (kind == "batch") {
             int dt, levels;
             unsigned flags;
-            in >> dt >> levels >> flags;
+            int64_t count, h, w, at = 0;
+            in >> dt >> levels >> flags >> count;
             std::vector<dwt2_image> imgs;
-            int64_t h, w, at = 0;
-            while (in >> h >> w) {
-                imgs.push_back({src + at, dst + at, (int32_t)h, (int32_t)w, w, w});
-                at += h * w * 4;
-            }
+            std::vector<std::pair<int64_t, int64_t>> sizes;
+            while (in >> h >> w) sizes.push_back({h, w});
+            for (int64_t k = 0; k < count; ++k)
+                for (const auto& s : sizes) {
+                    imgs.push_back({src + at, dst + at, (int32_t)s.first, (int32_t)s.second, s.second, s.second});
+                    at += s.first * s.second * 4;
+                }
             auto fn = (decltype(&dwt2_fwd_batched))dlsym(lib, "dwt2_fwd_batched");
             if (fn)
                 st = fn(imgs.data(), (const dwt2_image*)ws, (int)imgs.size(), (dwt2_dtype)dt, DWT2_CDF97, levels,

@@ -64,3 +64,23 @@ def test_launches_stay_below_the_work_item_limit(trace, wavelet, dtype):
         assert st == 0 and launches, call
         for name, groups, threads in launches:
             assert groups * threads < 1 << 32, (call, name, groups, threads)
+
+
+def batch(dtype, levels, count, *sizes, flags=0):
+    return f"batch {DTYPES[dtype]} {levels} {flags} {count} " + " ".join(f"{h} {w}" for h, w in sizes)
+
+
+def test_batched_launches_stay_below_the_work_item_limit(trace):
+    """9 million small images: one launch a level where two levels of them are too many
+    work-items for one; 17 million, too many either way, are refused before any launch."""
+    calls = [batch("f32", 2, 9000000, (4, 4)), batch("bf16", 3, 4500000, (5, 7), (6, 9)), batch("f32", 1, 9000000, (2, 3)),
+             batch("f32", 1, 9000000, (2, 3), flags=d.DWT2_FLAG_KERNEL(1))]
+    for call, (st, launches) in zip(calls, trace(calls)):
+        if call is calls[3]:                              # a configuration of 512 threads a tile
+            assert (st, launches) == (-2, []), call
+            continue
+        assert st == 0 and len(launches) > 1, call
+        for name, groups, threads in launches:
+            assert groups * threads < 1 << 32, (call, name, groups, threads)
+    (st, launches), = trace([batch("f16", 2, 17000000, (4, 4))])
+    assert (st, launches) == (-2, [])

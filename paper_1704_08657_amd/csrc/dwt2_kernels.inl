@@ -1028,21 +1028,25 @@ __device__ __forceinline__ void fold(int (&p)[N], int n) {
 // extension and D = 2 at the two ends of each axis (4 in the corners).  So a
 // border tile doubles those samples after its load (f = 2), runs the same steps
 // as an interior tile and halves them before its store (f = 1/2); both are exact,
-// and every value is the weighted step's, bit for bit (up to overflow and
-// subnormal numbers at the ends).  A border step program with the weights cost a
+// and every value is the weighted step's, bit for bit (up to subnormal numbers at
+// the ends).  So that a doubled sample does not overflow, a border tile that holds a
+// sample of 2^96 or more takes all of its samples at a quarter (all = 1/4; a corner
+// then is what it was), which is exact beside that sample's magnitude; see
+// tile_scale().  A border step program with the weights cost a
 // dozen operations more a block and step and twice the code: 192 planes of 256^2
 // FP32, 3 levels, took 46.8 us, now 39.2; 8192^2, 2 levels, 112.7, now 101.6 (BF16
 // 102, now 73).
 // rows, cols: the (folded) positions of a's samples; components K0 .. K1 - 1.
+// all: the factor of every sample.
 template <int K0, int K1, int BPL, int K, typename V>
 __device__ __forceinline__ void scale_edges(V (&a)[K][4 * BPL], const int (&rows)[2 * K], const int (&cols)[2 * BPL],
-                                            int h, int w, float f) {
+                                            int h, int w, float f, float all) {
 #pragma unroll
     for (int b = 0; b < BPL; ++b)
 #pragma unroll
         for (int k = K0; k < K1; ++k) {
             const int c = cols[2 * b + (k & 1)];
-            const float s = c == 0 || c == w - 1 ? f : 1.f;
+            const float s = c == 0 || c == w - 1 ? f * all : all;
 #pragma unroll
             for (int r = 0; r < K; ++r) a[r][4 * b + k] *= s;
         }
@@ -1061,14 +1065,41 @@ __device__ __forceinline__ void scale_edges(V (&a)[K][4 * BPL], const int (&rows
 }
 // The same at the positions of the lane's blocks as they are (not folded).
 template <int K0, int K1, int BPL, int K, typename V>
-__device__ __forceinline__ void scale_edges(V (&a)[K][4 * BPL], const Geo& g, int h, int w, float f) {
+__device__ __forceinline__ void scale_edges(V (&a)[K][4 * BPL], const Geo& g, int h, int w, float f, float all) {
     int rows[2 * K], cols[2 * BPL];
 #pragma unroll
     for (int i = 0; i < 2 * K; ++i) rows[i] = 2 * g.gr0 + i;
 #pragma unroll
     for (int i = 0; i < 2 * BPL; ++i) cols[i] = 2 * g.gcL + i;
-    scale_edges<K0, K1, BPL>(a, rows, cols, h, w, f);
+    scale_edges<K0, K1, BPL>(a, rows, cols, h, w, f, all);
 }
+// The largest magnitude of the components K0 .. 3, and m.
+template <int K0, int BPL, int K, typename V>
+__device__ __forceinline__ V largest(const V (&a)[K][4 * BPL], V m) {
+#pragma unroll
+    for (int r = 0; r < K; ++r)
+#pragma unroll
+        for (int i = 0; i < 4 * BPL; ++i)
+            if ((i & 3) >= K0) m = fmaxf(m, fabsf(a[r][i]));
+    return m;
+}
+// A border tile's factor `all`, from the largest magnitude m of each lane of the
+// work-group.  gone(wave): whether that wave has left the tile.  FP16 samples are no
+// match for FP32's range.  The barrier costs 0.3 us (one level of 256^2 FP32 5.6
+// us, now 6.0); running the steps first and again if need be cost more, in
+// registers (3 x 2160 x 3840 FP32, two levels, 36 us, 40; with the barrier 37).
+template <typename T> struct MayOverflow { static constexpr bool value = true; };
+template <> struct MayOverflow<__half> { static constexpr bool value = false; };
+template <typename T, int NW, typename V, typename F>
+__device__ __forceinline__ float tile_scale(V m, int lane, int wv, const F& gone) {
+    if constexpr (!MayOverflow<T>::value) return 1.f;
+    __shared__ uint32_t large[NW];
+    const bool mine = __ballot(m >= 0x1p96f) != 0;
+    if (lane == 0) large[wv] = mine;
+    __syncthreads();
+    return __ballot(lane < NW && !gone(lane) && large[lane < NW ? lane : 0] != 0) != 0 ? 0.25f : 1.f;
+}
+__device__ __forceinline__ float undo(float all) { return all < 1.f ? 4.f : 1.f; }
 
 // The lane's sample `off` bytes into a uniform row: the row pointer stays in
 // SGPRs and the lane's offset, the same for every row, in one VGPR.
@@ -1096,6 +1127,14 @@ __device__ __forceinline__ Q* subband_row(Q* ll, int64_t ll_pitch, Q* det, int64
         default: return det + (int64_t)(g.nEr + row) * pitch + g.nEc;
     }
 }
+
+// Whether all rows of a wave, the first of which is block row r of an image h
+// high, lie below what the image's outputs read: four steps read 4 positions
+// past the last.  Such a wave of a tile that reaches past the image leaves before
+// its first load; a barrier waits for the waves that are left only.
+// Planes less high than a tile consist of such tiles: one level of the adjoint of
+// 65536 planes of 16^2 FP32 423 us, now 367; 1048576 planes of 4^2 7.2 ms, now 4.6.
+__device__ __forceinline__ bool below_image(int r, int h) { return 2 * r > h + 3; }
 
 // Interior tile into registers: the core rows of the lane (a) and, in the
 // halo lanes, the lane's halo blocks (e).
@@ -1163,7 +1202,8 @@ __device__ __forceinline__ void load_tile(typename St<T>::V (&a)[K][Lay<BPL>::BX
 // clamps.  Each step keeps the extension symmetric, and every sum a step
 // forms pairs the same two values as the clamped step at the same place, so
 // every coefficient equals the clamped computation bit for bit.  The
-// adjoint takes the inverse's extension, of samples scale_edges() has doubled.
+// adjoint takes the inverse's extension, of samples that scale_edges() doubles,
+// and returns their factor.
 // A wave's rows are uniform, so their extension costs scalar instructions
 // only, and every lane whose columns lie inside the image loads vectors; a
 // lane at or past the right end loads single samples.  Small levels consist
@@ -1171,10 +1211,10 @@ __device__ __forceinline__ void load_tile(typename St<T>::V (&a)[K][Lay<BPL>::BX
 // instructions issued: with the extension computed per sample (a reciprocal
 // and a dozen instructions each) 192 x 256 FP32, 3 levels, took 30.9 us a
 // call, now 19.1; the inverse of 3 x 2160 x 3840 FP16, 4 levels, 89.6, now 48.4.
-template <int DIR, typename T, int BPL, int K>
-__device__ __forceinline__ void load_tile_border(typename St<T>::V (&a)[K][Lay<BPL>::BX], typename St<T>::V (&e)[8],
-                                                 const LevelParams& P, const Geo& g, const TileGeo<BPL>& tg,
-                                                 int lane) {
+template <int DIR, typename T, int NW, int BPL, int K>
+__device__ __forceinline__ float load_tile_border(typename St<T>::V (&a)[K][Lay<BPL>::BX], typename St<T>::V (&e)[8],
+                                                  const LevelParams& P, const Geo& g, const TileGeo<BPL>& tg,
+                                                  int lane, int wv) {
     using V = typename St<T>::V;
     const bool halo_lane = lane < 32 && tg.re < K;
     int rows[2 * K], cols[2 * BPL], hr[2], hc[4];
@@ -1254,11 +1294,16 @@ __device__ __forceinline__ void load_tile_border(typename St<T>::V (&a)[K][Lay<B
             }
         }
         if constexpr (DIR == kAdjoint) {
-            scale_edges<0, 4, BPL>(a, rows, cols, P.h, P.w, 2.f);
             V(&h)[1][8] = reinterpret_cast<V(&)[1][8]>(e);
-            scale_edges<0, 4, 2>(h, hr, hc, P.h, P.w, 2.f);
+            const int first = g.gr0 - wv * K;
+            const float all = tile_scale<T, NW>(largest<0, BPL>(a, largest<0, 2>(h, V(0))), lane, wv,
+                                                [&](int v) { return below_image(first + v * K, P.h); });
+            scale_edges<0, 4, BPL>(a, rows, cols, P.h, P.w, 2.f, all);
+            scale_edges<0, 4, 2>(h, hr, hc, P.h, P.w, 2.f, all);
+            return all;
         }
     }
+    return 1.f;
 }
 
 // Store the core of the tile: the core blocks of every lane, halo rows
@@ -1334,14 +1379,6 @@ __device__ __forceinline__ void store_tile(typename St<T>::V (&a)[K][Lay<BPL>::B
     }
 }
 
-// Whether all rows of a wave, the first of which is block row r of an image h
-// high, lie below what the image's outputs read: four steps read 4 positions
-// past the last.  Such a wave of a tile that reaches past the image leaves before
-// its first load; a barrier waits for the waves that are left only.
-// Planes less high than a tile consist of such tiles: one level of the adjoint of
-// 65536 planes of 16^2 FP32 423 us, now 367; 1048576 planes of 4^2 7.2 ms, now 4.6.
-__device__ __forceinline__ bool below_image(int r, int h) { return 2 * r > h + 3; }
-
 // One tile (tx, ty) of one level: load, the fused steps, store.  The LDS
 // belongs to the calling work-group.  Interior and border tiles differ in
 // their loads and stores only, so the step program is compiled once: half
@@ -1383,17 +1420,18 @@ __device__ __forceinline__ void tile_body(const LevelParams& P, int tx, int ty,
             run<DIR, WAV, SCH, NW, BPL>(a, e, lds, lane, wv, g, tg);
             store_tile<DIR, T, false, NW, BPL, K, LLC, LLX>(a, P, g, lane, wv);
         } else {
-            load_tile_border<DIR, T, BPL>(a, e, P, g, tg, lane);
+            load_tile_border<DIR, T, NW, BPL>(a, e, P, g, tg, lane, wv);
             run<DIR, WAV, kSchemeFused, NW, BPL>(a, e, lds, lane, wv, g, tg);
             store_tile<DIR, T, true, NW, BPL, K, false, LLX>(a, P, g, lane, wv);
         }
     } else {
+        float all = 1.f;
         if (interior) load_tile<DIR, T, BPL>(a, e, P, g, tg, lane);
-        else load_tile_border<DIR, T, BPL>(a, e, P, g, tg, lane);
+        else all = load_tile_border<DIR, T, NW, BPL>(a, e, P, g, tg, lane, wv);
         run<DIR, WAV, SCH, NW, BPL>(a, e, lds, lane, wv, g, tg);
         if (interior) store_tile<DIR, T, false, NW, BPL, K, LLC, LLX>(a, P, g, lane, wv);
         else {
-            if constexpr (DIR == kAdjoint) scale_edges<0, 4, BPL>(a, g, P.h, P.w, 0.5f);
+            if constexpr (DIR == kAdjoint) scale_edges<0, 4, BPL>(a, g, P.h, P.w, 0.5f, undo(all));
             store_tile<DIR, T, true, NW, BPL, K, false, LLX>(a, P, g, lane, wv);
         }
     }

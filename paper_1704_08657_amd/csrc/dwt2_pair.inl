@@ -230,18 +230,16 @@ __device__ __forceinline__ void store_band_row(T* p, const typename St<T>::V (&v
     else p[0] = St<T>::store(v[0]);
 }
 
-// The bands K0 .. 3 of a tile of a pyramid level (h x w; inverse and adjoint).
-// ADJ: the adjoint's, the end samples of each axis doubled in a border tile.
-template <typename T, bool ADJ, int K0, int BPL, int K>
+// The bands K0 .. 3 of a tile of a pyramid level (h x w; inverse and adjoint), and
+// the (folded) positions of a's samples.
+template <typename T, int K0, int BPL, int K>
 __device__ __forceinline__ void load_bands(typename St<T>::V (&a)[K][4 * BPL], const T* ll, int64_t ll_pitch,
                                            const T* det, int64_t pitch, int h, int w, const Geo& g, bool interior,
-                                           int lane) {
+                                           int lane, int (&rows)[2 * K], int (&cols)[2 * BPL]) {
     using V = typename St<T>::V;
-    int rows[2 * K];
 #pragma unroll
     for (int i = 0; i < 2 * K; ++i) rows[i] = 2 * g.gr0 + i;
     if (!interior) fold_both(rows, h);
-    int cols[2 * BPL];
 #pragma unroll
     for (int i = 0; i < 2 * BPL; ++i) cols[i] = 2 * g.gcL + i;
     if (interior || (cols[0] >= 0 && cols[2 * BPL - 1] < w)) {
@@ -266,9 +264,6 @@ __device__ __forceinline__ void load_bands(typename St<T>::V (&a)[K][4 * BPL], c
 #pragma unroll
                 for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = load_at(row, cols[2 * b + (k & 1)] >> 1);
             }
-    }
-    if constexpr (ADJ) {
-        if (!interior) scale_edges<K0, 4, BPL>(a, rows, cols, h, w, 2.f);
     }
 }
 
@@ -341,9 +336,10 @@ __device__ __forceinline__ int clamp_to(int x, int n) { return x < 0 ? 0 : x < n
 
 // LL samples of a border tile's blocks (inverse and adjoint): each at its
 // reflected pixel position of the h x w level, `ll(row, col)` being the block's;
-// the adjoint's doubled at the ends of an axis (adj: 2, see scale_edges()).
+// the adjoint's times f at the ends of an axis and `all` (see scale_edges()).
 template <int BPL, int K, bool ADJ, typename V, typename F>
-__device__ __forceinline__ void reflect_ll(V (&a)[K][4 * BPL], const Geo& g, int h, int w, float adj, const F& ll) {
+__device__ __forceinline__ void reflect_ll(V (&a)[K][4 * BPL], const Geo& g, int h, int w, float f, float all,
+                                           const F& ll) {
     int rows[K], cols[BPL];
 #pragma unroll
     for (int i = 0; i < K; ++i) rows[i] = 2 * (g.gr0 + i);
@@ -357,8 +353,8 @@ __device__ __forceinline__ void reflect_ll(V (&a)[K][4 * BPL], const Geo& g, int
         for (int b = 0; b < BPL; ++b) {
             a[r][4 * b] = ll(rows[r] >> 1, cols[b] >> 1);
             if constexpr (ADJ) {
-                a[r][4 * b] *= rows[r] == 0 || rows[r] == h - 1 ? adj : 1.f;
-                a[r][4 * b] *= cols[b] == 0 || cols[b] == w - 1 ? adj : 1.f;
+                a[r][4 * b] *= rows[r] == 0 || rows[r] == h - 1 ? f * all : all;
+                a[r][4 * b] *= cols[b] == 0 || cols[b] == w - 1 ? f : 1.f;
             }
         }
 }
@@ -390,8 +386,11 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
     // Waves below both levels' images leave (see below_image), if there are two of
     // them: 65536 planes of 16^2 FP32 forward 623 us, now 477.  One of eight leaving
     // alone cost 4096 planes of 64^2 5 to 8 % (adjoint 96 us for 90).
-    const int first = r0 + (wv < NW - 2 ? wv : NW - 2) * K;
-    if (below_image(first, P.h) && below_image(first >> 1, h2)) return;
+    auto gone = [&](int v) {
+        const int first = r0 + (v < NW - 2 ? v : NW - 2) * K;
+        return below_image(first, P.h) && below_image(first >> 1, h2);
+    };
+    if (gone(wv)) return;
     const bool interior = r0 >= 0 && g.cb0 >= 0 && r0 + R <= g.nOr && g.cb0 + 2 * kLanes <= g.nOc;
     const bool core_lane = lane >= kEdge2 && lane < kLanes - kEdge2;
     V a[K][8], b[K2][4];
@@ -429,12 +428,31 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
     } else {
         constexpr bool kAdj = DIR == kAdjoint;
         const T* const det = static_cast<const T*>(P.in);
-        load_bands<T, kAdj, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2, interior,
-                                      lane);
-        load_bands<T, kAdj, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        int rows[2 * K], cols[4], rows2[2 * K2], cols2[2];
+        load_bands<T, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2, interior, lane,
+                                rows2, cols2);
+        load_bands<T, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane, rows, cols);
+        float all = 1.f;
+        if constexpr (kAdj) {
+            if (!interior) {
+                all = tile_scale<T, NW>(largest<1, 2>(a, largest<0, 1>(b, V(0))), lane, wv, gone);
+                // the columns anew: kept from the load they take 85 registers in all
+                // of the 80 that six waves a SIMD may have (8 x 6)
+                int gc = g.gcL;
+                asm volatile("" : "+v"(gc));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) cols[i] = 2 * gc + i;
+                cols2[0] = gc;
+                cols2[1] = gc + 1;
+                fold_both(cols, P.w);
+                fold_both(cols2, w2);
+                scale_edges<0, 4, 1>(b, rows2, cols2, h2, w2, 2.f, all);
+                scale_edges<1, 4, 2>(a, rows, cols, P.h, P.w, 2.f, all);
+            }
+        }
         steps<DIR, WAV, SCH, NW, 1, K2>(b, L, lane, wv, g2);
         if constexpr (kAdj) {
-            if (!interior) scale_edges<0, 4, 1>(b, g2, h2, w2, 0.5f);
+            if (!interior) scale_edges<0, 4, 1>(b, g2, h2, w2, 0.5f, undo(all));
         }
 #pragma unroll
         for (int r = 0; r < K2; ++r)
@@ -446,13 +464,13 @@ __device__ __forceinline__ void tile(const PairParams& P, int tx, int ty, PairLd
 #pragma unroll
                 for (int c = 0; c < 2; ++c) S.p[wv * K + r][2 * lane + c] = a[r][4 * c];
             __syncthreads();
-            reflect_ll<2, K, kAdj>(a, g, P.h, P.w, 2.f, [&](int row, int col) -> V {
+            reflect_ll<2, K, kAdj>(a, g, P.h, P.w, 2.f, all, [&](int row, int col) -> V {
                 return S.p[clamp_to(row - r0, R)][clamp_to(col - g.cb0, 2 * kLanes)];
             });
         }
         steps<DIR, WAV, SCH, NW, 2, K>(a, L, lane, wv, g);
         if constexpr (kAdj) {
-            if (!interior) scale_edges<0, 4, 2>(a, g, P.h, P.w, 0.5f);
+            if (!interior) scale_edges<0, 4, 2>(a, g, P.h, P.w, 0.5f, undo(all));
         }
         if (core_lane) {
             T* const out = static_cast<T*>(P.out);
@@ -496,7 +514,11 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
     g3.cb0 = c0 / 4;
     g3.gcL = g3.cb0 + lane;
     g3.gr0 = r0 / 4 + wv;
-    if (below_image(g.gr0, P.h) && below_image(g2.gr0, h2) && below_image(g3.gr0, h3)) return;
+    auto gone = [&](int v) {
+        const int first = r0 + v * K;
+        return below_image(first, P.h) && below_image(first / 2, h2) && below_image(r0 / 4 + v, h3);
+    };
+    if (gone(wv)) return;
     const bool interior = r0 >= 0 && c0 >= 0 && r0 + R <= g.nOr && c0 + 2 * kLanes <= g.nOc;
     constexpr int kEl = kHalo3 / 2;                // halo lanes of levels 1 and 2; half as many at level 3
     const bool core_lane = lane >= kEl && lane < kLanes - kEl;
@@ -550,22 +572,35 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
     } else {
         constexpr bool kAdj = DIR == kAdjoint;
         const T* const det = static_cast<const T*>(P.in);
-        load_bands<T, kAdj, 0, 1, 1>(c, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h3, w3, g3, false,
-                                          lane);
-        load_bands<T, kAdj, 1, 1, K2>(b, det, P.in_pitch, det, P.in_pitch, h2, w2, g2, interior, lane);
-        load_bands<T, kAdj, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        int rows[2 * K], cols[4], rows2[2 * K2], cols2[2], rows3[2], cols3[2];
+        load_bands<T, 0, 1, 1>(c, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h3, w3, g3, false, lane,
+                               rows3, cols3);
+        load_bands<T, 1, 1, K2>(b, det, P.in_pitch, det, P.in_pitch, h2, w2, g2, interior, lane, rows2, cols2);
+        load_bands<T, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane, rows, cols);
+        float all = 1.f;
+        if constexpr (kAdj) {
+            if (!interior) {
+                all = tile_scale<T, NW>(largest<1, 2>(a, largest<1, 1>(b, largest<0, 1>(c, V(0)))), lane, wv, gone);
+                scale_edges<0, 4, 1>(c, rows3, cols3, h3, w3, 2.f, all);
+                scale_edges<1, 4, 1>(b, rows2, cols2, h2, w2, 2.f, all);
+                scale_edges<1, 4, 2>(a, rows, cols, P.h, P.w, 2.f, all);
+            }
+        }
         steps<DIR, WAV, SCH, NW, 1, 1>(c, L, lane, wv, g3);
-        if constexpr (kAdj) scale_edges<0, 4, 1>(c, g3, h3, w3, 0.5f);
+        if constexpr (kAdj) {
+            if (!interior) scale_edges<0, 4, 1>(c, g3, h3, w3, 0.5f, undo(all));
+        }
         if (lane < kLanes / 2) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) S.p[2 * wv + (k >> 1)][2 * lane + (k & 1)] = stored<T>(c[0][k]);
         }
         __syncthreads();
-        // an interior tile's level 2 is free of border weights, as its loads are
-        reflect_ll<1, K2, kAdj>(b, g2, h2, w2, interior ? 1.f : 2.f, plane2);
+        // an interior tile is free of border weights: an end of level 2 or 3 that it
+        // holds lies in its halo, further out than its outputs read
+        reflect_ll<1, K2, kAdj>(b, g2, h2, w2, interior ? 1.f : 2.f, all, plane2);
         steps<DIR, WAV, SCH, NW, 1, K2>(b, L, lane, wv, g2);
         if constexpr (kAdj) {
-            if (!interior) scale_edges<0, 4, 1>(b, g2, h2, w2, 0.5f);
+            if (!interior) scale_edges<0, 4, 1>(b, g2, h2, w2, 0.5f, undo(all));
         }
 #pragma unroll
         for (int r = 0; r < K2; ++r)
@@ -578,11 +613,11 @@ __device__ __forceinline__ void tile3(const PairParams& P, int tx, int ty, PairL
 #pragma unroll
                 for (int q = 0; q < 2; ++q) S.p[wv * K + r][2 * lane + q] = a[r][4 * q];
             __syncthreads();
-            reflect_ll<2, K, kAdj>(a, g, P.h, P.w, 2.f, plane1);
+            reflect_ll<2, K, kAdj>(a, g, P.h, P.w, 2.f, all, plane1);
         }
         steps<DIR, WAV, SCH, NW, 2, K>(a, L, lane, wv, g);
         if constexpr (kAdj) {
-            if (!interior) scale_edges<0, 4, 2>(a, g, P.h, P.w, 0.5f);
+            if (!interior) scale_edges<0, 4, 2>(a, g, P.h, P.w, 0.5f, undo(all));
         }
         if (core_lane)
             store_image<T, true, kHalo3, NW, 2, K>(a, static_cast<T*>(P.out), P.out_pitch, P.h, P.w, g, lane, wv);
@@ -613,8 +648,10 @@ __device__ __forceinline__ bool pick_tile(const PairParams& P, PairParams& Q, in
     return true;
 }
 
+// The adjoint's tiles of 8 x 6 are held to the 80 registers that six waves a SIMD may
+// have (83 otherwise: 3 x 2160 x 3840 FP32, two levels, 41.8 us for 37.2).
 template <int DIR, int WAV, typename T, int SCH, int NW, int K, int LEVELS = 2>
-__global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P) {
+__global__ void __launch_bounds__(NW * kLanes, DIR == kAdjoint && K == 6 ? 6 : (NW + 3) / 4) pair_kernel(PairParams P) {
     using V = typename St<T>::V;
     __shared__ PairLds<V, NW> L;
     __shared__ PairPlane<V, NW * K> S;

@@ -602,9 +602,10 @@ __global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P0) {
             pair::store_bands<T, 0, kHalo4x2 / 2, NW, 1, K2>(b, ll, P.ll_pitch, out, P.out_pitch, g2, lane, wv);
     } else {
         const T* const det = static_cast<const T*>(P.in);
-        pair::load_bands<T, false, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2,
-                                             interior, lane);
-        pair::load_bands<T, false, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane);
+        int rows[2 * K], cols[4], rows2[2 * K2], cols2[2];
+        pair::load_bands<T, 0, 1, K2>(b, static_cast<const T*>(P.ll), P.ll_pitch, det, P.in_pitch, h2, w2, g2, interior,
+                                      lane, rows2, cols2);
+        pair::load_bands<T, 1, 2, K>(a, det, P.in_pitch, det, P.in_pitch, P.h, P.w, g, interior, lane, rows, cols);
         pair::scale_bands<1, K2>(b, kZ2Inv, kZ2);
         update<true, NW, 1, K2>(b, L.l2, lane, wv);
         __syncthreads();
@@ -620,7 +621,7 @@ __global__ void __launch_bounds__(NW * kLanes) pair_kernel(PairParams P0) {
 #pragma unroll
                 for (int c = 0; c < 2; ++c) L.ll.p[wv * K + r][2 * lane + c] = a[r][4 * c];
             __syncthreads();
-            pair::reflect_ll<2, K, false>(a, g, P.h, P.w, 1.f, plane);
+            pair::reflect_ll<2, K, false>(a, g, P.h, P.w, 1.f, 1.f, plane);
             __syncthreads();
         }
         pair::scale_bands<2, K>(a, kZ2Inv, kZ2);

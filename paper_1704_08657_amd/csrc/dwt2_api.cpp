@@ -167,20 +167,6 @@ bool persistent_ok(int wavelet, int dtype, unsigned flags, int32_t planes) {
            dwt2::persist_config_supported(config_of(flags, wavelet));
 }
 
-// Chunks and tiles of one image over all levels, for tile configuration cfg.
-void image_work(int32_t h, int32_t w, int levels, int cfg, uint64_t* chunks, uint64_t* tiles) {
-    const dwt2::KernelConfig c = dwt2::kConfigs[cfg];
-    *chunks = 0;
-    *tiles = 0;
-    for (int l = 0; l < levels; ++l) {
-        int32_t hl, wl, tx, ty;
-        dwt2::level_size(h, w, l, &hl, &wl);
-        dwt2::level_tiles(hl, wl, dwt2::core_cols(c), dwt2::core_rows(c), &tx, &ty);
-        *chunks += (uint64_t)dwt2::chunk_count(ty);
-        *tiles += (uint64_t)tx * (uint64_t)ty;
-    }
-}
-
 // Workspace of a persistent call on `count` images (a plane stack when
 // imgs == nullptr: `count` planes of h x w): the work tables and every
 // image's LL bands.  The tables depend on the tile shape, so the size is the
@@ -189,10 +175,15 @@ size_t persist_bytes(const dwt2_image* imgs, int count, int32_t h, int32_t w, in
     size_t tables = 0;
     for (int cfg = 0; cfg < dwt2::kNumConfigs; ++cfg) {
         if (!dwt2::persist_config_supported(cfg)) continue;
+        bool seen = false;                       // tiles of the same height: the same chunks
+        for (int k = 0; k < cfg; ++k)
+            seen |= dwt2::persist_config_supported(k) &&
+                    dwt2::core_rows(dwt2::kConfigs[k]) == dwt2::core_rows(dwt2::kConfigs[cfg]);
+        if (seen) continue;
         uint64_t chunks = 0;
         for (int i = 0; i < (imgs ? count : 1); ++i) {
-            uint64_t c, t;
-            image_work(imgs ? imgs[i].height : h, imgs ? imgs[i].width : w, levels, cfg, &c, &t);
+            const uint64_t c = dwt2::image_chunks(imgs ? imgs[i].height : h, levels,
+                                                  dwt2::core_rows(dwt2::kConfigs[cfg]));
             chunks += imgs ? c : c * (uint64_t)count;
         }
         const size_t off = dwt2::batch_layout(count, levels, chunks).off_ll;
@@ -357,35 +348,9 @@ int levels_in_launch(dwt2::Direction dir, const Plan& p, int l, int dtype, int w
     return dwt2::pair_pays(dir, to_dtype(dtype), p.h[l], p.w[l], planes) ? 2 : 1;
 }
 
-// Two or three levels in one launch for a whole batch: the same choice as for a
-// stack of planes (levels_in_launch), on the sums over the images.
-struct BatchPairStats {
-    uint64_t tiles32, tiles48;    // two-level tiles of 32 and of 48 block rows
-    uint64_t rows32;              // rows of the former
-    uint64_t tiles3[2];           // three-level tiles of 48 and of 64 block rows
-    uint64_t cols112, cols128;    // tiles across, two-level and one-level, weighted by the image's rows
-    uint64_t samples;
-};
-void add_pair_stats(int32_t h, int32_t w, int levels, BatchPairStats* st) {
-    for (int l = 0; l + 1 < levels; ++l) {
-        int32_t tx, ty;
-        for (int i = 0; i < 2; ++i) {
-            dwt2::multi_tile_grid(h, w, 3, 48 + 16 * i, &tx, &ty);
-            st[l].tiles3[i] += (uint64_t)tx * (uint64_t)ty;
-        }
-        dwt2::multi_tile_grid(h, w, 2, 32, &tx, &ty);
-        st[l].tiles32 += (uint64_t)tx * (uint64_t)ty;
-        st[l].rows32 += (uint64_t)ty;
-        dwt2::multi_tile_grid(h, w, 2, 48, &tx, &ty);
-        st[l].tiles48 += (uint64_t)tx * (uint64_t)ty;
-        st[l].cols112 += (uint64_t)tx * (uint64_t)h;
-        st[l].cols128 += (uint64_t)(((w + 1) / 2 + 2 * dwt2::kLanes - 1) / (2 * dwt2::kLanes)) * (uint64_t)h;
-        st[l].samples += (uint64_t)h * (uint64_t)w;
-        h = (h + 1) / 2;
-        w = (w + 1) / 2;
-    }
-}
-bool batch_pair_pays(int dtype, const BatchPairStats& st) {
+// Two levels in one launch for a whole batch: the same choice as for a stack of planes
+// (levels_in_launch), on the sums over the images.
+bool batch_pair_pays(int dtype, const dwt2::BatchSums::Level& st) {
     if (st.tiles32 <= 640) return true;
     if (st.tiles32 > (uint64_t)dwt2::max_tiles(8)) return false;    // more than a launch may have
     if (2 * st.cols112 >= 3 * st.cols128) return false;
@@ -402,12 +367,12 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
     // one level is one launch either way (and needs no workspace)
     if ((flags & DWT2_FLAG_PERSISTENT) && levels > 1) {
         const int cfg = config_of(flags, wavelet);
-        uint64_t chunks, tiles;
-        image_work(h, w, levels, cfg, &chunks, &tiles);
+        dwt2::BatchSums sums{};
+        dwt2::add_image(h, w, levels, dwt2::kConfigs[cfg], false, &sums);
         const dwt2::ImageSet S{nullptr, src, dst, sps, dps, sp, dp, h, w};
-        const dwt2::BatchLayout L = dwt2::batch_layout(planes, levels, chunks * (uint64_t)planes);
+        const dwt2::BatchLayout L = dwt2::batch_layout(planes, levels, sums.chunks * (uint64_t)planes);
         return report(dwt2::launch_fwd_persistent(to_dtype(dtype), scheme_of(flags, dtype, wavelet, false), cfg, S,
-                                                  planes, levels, ws, L, tiles * (uint64_t)planes, s));
+                                                  planes, levels, ws, L, sums.tiles * (uint64_t)planes, s));
     }
     Plan p;
     plan_levels(h, w, levels, &p);
@@ -735,8 +700,7 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
     if (!dwt2::persist_config_supported(cfg)) return DWT2_E_FLAGS;
     const size_t es = elem_size(dtype);
     const dwt2::KernelConfig kc = dwt2::kConfigs[cfg];
-    uint64_t tiles[32] = {0}, chunks = 0, all_tiles = 0;
-    BatchPairStats stats[32] = {};
+    dwt2::BatchSums sums{};
     const bool pairs = flags == 0;
     for (int i = 0; i < count; ++i) {
         const dwt2_image& im = host_images[i];
@@ -747,20 +711,14 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
         if (ranges_overlap(im.src, span_bytes(im.height, im.width, im.src_pitch, es), im.dst,
                            span_bytes(im.height, im.width, im.dst_pitch, es)))
             return DWT2_E_ALIAS;
-        for (int l = 0; l < levels; ++l)
-            tiles[l] += dwt2::level_tile_count(im.height, im.width, l, dwt2::core_cols(kc), dwt2::core_rows(kc));
-        if (pairs) add_pair_stats(im.height, im.width, levels, stats);
-        uint64_t c, t;
-        image_work(im.height, im.width, levels, cfg, &c, &t);
-        chunks += c;
-        all_tiles += t;
+        dwt2::add_image(im.height, im.width, levels, kc, pairs, &sums);
     }
     if (batch_spans_alias(host_images, count, es)) return DWT2_E_ALIAS;
     const bool persistent = (flags & DWT2_FLAG_PERSISTENT) && levels > 1;
     // ticket numbers and counters are 32-bit
     for (int l = 0; l < levels; ++l)
-        if (tiles[l] > 0x7fff0000ull) return DWT2_E_SHAPE;
-    if (chunks > 0x7fff0000ull) return DWT2_E_SHAPE;
+        if (sums.level[l].tiles > 0x7fff0000ull) return DWT2_E_SHAPE;
+    if (sums.chunks > 0x7fff0000ull) return DWT2_E_SHAPE;
     size_t need = 0;
     const int st = dwt2_workspace_bytes_batched(host_images, count, dtype, levels, &need);
     if (st) return st;
@@ -774,27 +732,27 @@ int dwt2_fwd_batched(const dwt2_image* host_images, const dwt2_image* device_ima
     const dwt2::Scheme sch = scheme_of(flags, dtype, wavelet, false);
     if (persistent) {
         const dwt2::ImageSet S{device_images, nullptr, nullptr, 0, 0, 0, 0, 0, 0};
-        const dwt2::BatchLayout L = dwt2::batch_layout(count, levels, chunks);
+        const dwt2::BatchLayout L = dwt2::batch_layout(count, levels, sums.chunks);
         return report(dwt2::launch_fwd_persistent(to_dtype(dtype), sch, cfg, S, count, levels, workspace, L,
-                                                  all_tiles, (hipStream_t)stream));
+                                                  sums.tiles, (hipStream_t)stream));
     }
     dwt2::BatchLaunches B{};
     uint32_t launch_tiles[32];
     for (int l = 0; l < levels; ++B.n) {
-        const BatchPairStats& st = stats[l];
+        const dwt2::BatchSums::Level& st = sums.level[l];
         const int rows3 = !pairs || l + 3 != levels ? 0
                           : dwt2::triple_rows(dwt2::kForward, (int64_t)st.tiles3[0], (int64_t)st.tiles3[1]);
         const int n = !pairs || l + 1 >= levels ? 1 : rows3 ? 3 : batch_pair_pays(dtype, st) ? 2 : 1;
         const int rows = n != 2 ? rows3 : dwt2::pair_rows(dwt2::kForward, es, (int64_t)st.tiles32, (int64_t)st.tiles48,
                                                           (int64_t)st.samples);
-        if (n == 1 && tiles[l] > (uint64_t)dwt2::max_tiles(kc.waves)) return DWT2_E_SHAPE;
+        if (n == 1 && st.tiles > (uint64_t)dwt2::max_tiles(kc.waves)) return DWT2_E_SHAPE;
         B.first[B.n] = (int8_t)l;
         B.levels[B.n] = (int8_t)n;
         B.rows[B.n] = (int8_t)rows;
         // a chunk of about kRemapRows tile rows of the images' mean width
         const uint64_t near = n == 1 ? (uint64_t)dwt2::kLevelChunk : dwt2::kRemapRows * st.tiles32 / st.rows32;
         B.near[B.n] = near < 16 ? 16 : near > 4096 ? 4096 : (int32_t)near;
-        launch_tiles[B.n] = (uint32_t)(n == 1 ? tiles[l] : n == 3 ? st.tiles3[rows == 64] : rows == 32 ? st.tiles32 : st.tiles48);
+        launch_tiles[B.n] = (uint32_t)(n == 1 ? st.tiles : n == 3 ? st.tiles3[rows == 64] : rows == 32 ? st.tiles32 : st.tiles48);
         l += n;
     }
     return report(dwt2::launch_fwd_batched_levels(to_dtype(dtype), sch, cfg, B, device_images, count, levels,

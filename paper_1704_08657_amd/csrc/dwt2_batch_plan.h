@@ -179,6 +179,62 @@ __host__ __device__ inline uint64_t launch_tile_count(int32_t h, int32_t w, int 
     multi_tile_grid(hl, wl, levels, rows, &tx, &ty);
     return (uint64_t)tx * (uint64_t)ty;
 }
+// What the host sums over a batch's images, level by level, to check the call and to
+// choose its launches.  One pass over an image's levels: with a pass for each of these
+// sums, the planning of 1000 images, 5 levels, took 254 us, now 135.
+struct BatchSums {
+    struct Level {
+        uint64_t tiles;               // one-level tiles of the call's configuration
+        // where two or three levels in a launch are a choice:
+        uint64_t tiles32, tiles48;    // two-level tiles of 32 and of 48 block rows
+        uint64_t rows32;              // rows of the former
+        uint64_t tiles3[2];           // three-level tiles of 48 and of 64 block rows
+        uint64_t cols112, cols128;    // tiles across, two-level and one-level, weighted by the image's rows
+        uint64_t samples;
+    } level[32];
+    uint64_t tiles, chunks;           // over all levels
+};
+inline void add_image(int32_t h, int32_t w, int levels, const KernelConfig& c, bool multi, BatchSums* s) {
+    const uint32_t cx = (uint32_t)core_cols(c), cy = (uint32_t)core_rows(c);
+    uint32_t hl = (uint32_t)h, wl = (uint32_t)w;
+    for (int l = 0; l < levels; ++l) {
+        const uint32_t nEr = (hl + 1) / 2, nEc = (wl + 1) / 2, ty = (nEr + cy - 1) / cy;
+        const uint64_t t = (uint64_t)((nEc + cx - 1) / cx) * ty;
+        BatchSums::Level& v = s->level[l];
+        v.tiles += t;
+        s->tiles += t;
+        s->chunks += (uint64_t)chunk_count((int32_t)ty);
+        if (multi && l + 1 < levels) {
+            int32_t tx, ry;
+            multi_tile_grid((int32_t)hl, (int32_t)wl, 2, 32, &tx, &ry);
+            v.tiles32 += (uint64_t)tx * (uint64_t)ry;
+            v.rows32 += (uint64_t)ry;
+            v.cols112 += (uint64_t)tx * hl;
+            v.cols128 += (uint64_t)((nEc + 2 * kLanes - 1) / (2 * kLanes)) * hl;
+            multi_tile_grid((int32_t)hl, (int32_t)wl, 2, 48, &tx, &ry);
+            v.tiles48 += (uint64_t)tx * (uint64_t)ry;
+            v.samples += (uint64_t)hl * wl;
+            if (l + 3 == levels)      // the last three levels only
+                for (int i = 0; i < 2; ++i) {
+                    multi_tile_grid((int32_t)hl, (int32_t)wl, 3, 48 + 16 * i, &tx, &ry);
+                    v.tiles3[i] += (uint64_t)tx * (uint64_t)ry;
+                }
+        }
+        hl = nEr;
+        wl = nEc;
+    }
+}
+// Chunks of an image over all levels, in tiles of `rows` block rows.
+inline uint64_t image_chunks(int32_t h, int levels, int rows) {
+    uint64_t n = 0;
+    uint32_t hl = (uint32_t)h;
+    for (int l = 0; l < levels; ++l) {
+        hl = (hl + 1) / 2;
+        n += (uint64_t)chunk_count((int32_t)((hl + (uint32_t)rows - 1) / (uint32_t)rows));
+    }
+    return n;
+}
+
 // The batched kernel of one level deals its tiles over the 8 XCDs in chunks of
 // about this many consecutive ones (deal_tiles).
 constexpr int kLevelChunk = 64;

@@ -5,8 +5,9 @@ Times every kernel configuration that the library offers for a case
 current GPU, beside the library's own choice (which picks a kernel per level
 and may run two levels in one launch), and records a configuration that beats
 it in a JSON cache.  The binding consults the cache when a call does not name
-a configuration; all configurations compute bit-identical results, so the
-choice affects speed only.
+a configuration.  The choice affects speed only: all configurations compute
+bit-identical results, but for DD 13/7 with 16-bit storage, whose default
+(factored steps) and configurations (fused steps) round differently.
 
     python -m paper_1704_08657_amd.autotune [--out FILE] [--quick]
 
@@ -76,20 +77,25 @@ def lookup(direction: str, wavelet: str, dtype: str, h: int, w: int, levels: int
 
 def tune_case(direction: str, wavelet: str, dtype: str, h: int, w: int, levels: int, run, configs=None,
               steps: int = 8, warm: int = 3):
-    """Time `run(config, i)` for every kernel configuration (or `configs`) and
-    for the library's own choice (None) on the current GPU and stream, record
-    the fastest in the in-memory cache under this case's key, so calls that
-    name no configuration use it, and return (best, {config: ms})."""
+    """Time `run(config, i)` for every kernel configuration (or `configs`) on
+    the current GPU and stream and return (best, {config: ms}).  The fastest is
+    recorded in the in-memory cache under this case's key, so calls that name
+    no configuration use it, unless the library's own choice is faster:
+    `run(None, i)`, where `run` takes a None."""
     import torch
     import paper_1704_08657_amd as d
     if configs is None:
         configs = [c for c in range(d.DWT2_NUM_KERNEL_CONFIGS) if d.config_supports(c, direction, wavelet)]
+    k = key(arch_name(), direction, wavelet, dtype, h, w, levels)
     # None must mean the library's choice here, not an earlier entry
-    _record(key(arch_name(), direction, wavelet, dtype, h, w, levels), None)
-    configs = [None, *configs]
+    _record(k, None)
     times = {c: _time(torch, lambda i, c=c: run(c, i), steps=steps, warm=warm) for c in configs}
     best = min(times, key=times.get)
-    _record(key(arch_name(), direction, wavelet, dtype, h, w, levels), best)
+    try:
+        own = _time(torch, lambda i: run(None, i), steps=steps, warm=warm)
+    except TypeError:                  # it takes configuration indices only
+        own = float("inf")
+    _record(k, best if times[best] < own else None)
     return best, times
 
 

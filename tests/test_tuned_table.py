@@ -20,3 +20,33 @@ def test_table_leaves_the_choice_to_the_library(gfx950, h, w, levels):
     for direction in ("fwd", "inv", "adj"):
         for dtype in (d.DWT2_F32, d.DWT2_BF16, d.DWT2_F16):
             assert d.tuned_config(direction, "cdf97", dtype, h, w, levels) is None
+
+
+def _timer(ms):
+    """A _time that runs the call once and takes its time from `ms`."""
+    def time(torch, fn, steps=0, warm=0):
+        return ms[fn(0)]
+    return time
+
+
+def test_tune_case_times_the_given_configurations(gfx950, monkeypatch):
+    """run(config, i) is called with indices; they alone are returned, and the fastest is recorded."""
+    monkeypatch.setattr(autotune, "_time", _timer({0: 3.0, 2: 1.0, 4: 2.0}))
+    seen = []
+
+    def run(config, i):
+        seen.append(config)
+        return (d.DWT2_FLAG_KERNEL(config) >> d.DWT2_FLAG_KERNEL_SHIFT) - 1     # an index, or a TypeError
+
+    best, times = autotune.tune_case("fwd", "cdf97", "f32", 512, 512, 1, run, configs=[0, 2, 4])
+    assert best == 2 and times == {0: 3.0, 2: 1.0, 4: 2.0} and sorted(times) == [0, 2, 4]
+    assert seen[:3] == [0, 2, 4]
+    assert d.tuned_config("fwd", "cdf97", d.DWT2_F32, 512, 512, 1) == 2
+
+
+@pytest.mark.parametrize("own,recorded", [(0.5, None), (1.5, 2)])
+def test_tune_case_leaves_a_faster_choice_of_the_library(gfx950, monkeypatch, own, recorded):
+    monkeypatch.setattr(autotune, "_time", _timer({0: 3.0, 2: 1.0, None: own}))
+    best, times = autotune.tune_case("fwd", "cdf97", "f32", 512, 512, 5, lambda config, i: config, configs=[0, 2])
+    assert best == 2 and times == {0: 3.0, 2: 1.0}
+    assert d.tuned_config("fwd", "cdf97", d.DWT2_F32, 512, 512, 5) == recorded

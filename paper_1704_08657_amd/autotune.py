@@ -197,6 +197,8 @@ def tune(sizes=(256, 1024, 4096, 8192), levels=(1, 5), quick=False, out=CACHE_PA
         json.dump(result, f, indent=1, sort_keys=True)
     global _cache
     _cache = result
+    from . import _tuned               # the timed calls left the library's choice there
+    _tuned.clear()
     return result
 
 

@@ -50,3 +50,25 @@ def test_tune_case_leaves_a_faster_choice_of_the_library(gfx950, monkeypatch, ow
     best, times = autotune.tune_case("fwd", "cdf97", "f32", 512, 512, 5, lambda config, i: config, configs=[0, 2])
     assert best == 2 and times == {0: 3.0, 2: 1.0}
     assert d.tuned_config("fwd", "cdf97", d.DWT2_F32, 512, 512, 5) == recorded
+
+
+@pytest.mark.gpu
+def test_calls_after_tune_use_its_result(tmp_path, monkeypatch):
+    """Calls of the process that ran tune() go by what it found, not by what its timed calls used."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    ms = iter(range(1000, 0, -1))       # every configuration faster than the one before
+
+    def time(torch, fn, steps=0, warm=0):
+        fn(0)
+        return next(ms)
+
+    monkeypatch.setattr(autotune, "_time", time)
+    monkeypatch.setattr(autotune, "_cache", {})
+    monkeypatch.setattr(d, "_tuned", {})
+    result = autotune.tune(sizes=(64,), levels=(1,), quick=True, out=str(tmp_path / "t.json"),
+                           log=lambda line: None, dtypes=("i32",))
+    for direction in ("fwd", "inv"):
+        best = result[autotune.key(autotune.arch_name(), direction, "cdf53", "i32", 64, 64, 1)]
+        assert best is not None and d.tuned_config(direction, "cdf53", d.DWT2_I32, 64, 64, 1) == best

@@ -94,3 +94,36 @@ def test_low_planes_take_the_low_tile(trace):
             i = ["fwd", "inv", "adj"].index(call.split()[1])
             assert st == 0
             assert [x[0] for x in launches] == [f"void dwt2::kern::pair::pair_kernel<{i}, 0, {t.format(0 if i == 2 else 3)}, 8, 4, 2>"], call
+
+
+# the shapes of the GPU tests that compare the default calls with one launch a level
+PAIR_SHAPES = [(1, 40, 224, 3), (2, 41, 225, 2), (3, 83, 460, 5), (130, 64, 192, 3), (64, 66, 193, 3), (1, 1501, 1499, 3),
+               (3, 1079, 2017, 3), (3, 1080, 2016, 2), (3, 1083, 2050, 5), (1, 4099, 8201, 3), (1, 8192, 4096, 2)]
+TAPS4_SHAPES = [(1, 27, 247, 2), (1, 111, 495, 2), (1, 200, 1000, 5), (1, 2900, 2050, 2), (3, 333, 1211, 4)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "i32"])
+def test_every_multi_level_tile_is_compared_on_the_gpu(trace, dtype):
+    """Among the shapes of tests/test_gpu_pair.py each tile of each direction is launched."""
+    wavelet = "cdf53" if dtype == "i32" else "cdf97"
+    for i, direction in enumerate(("fwd", "inv", "adj")):
+        if direction == "adj" and dtype == "i32":
+            continue
+        seen = {name.split(", ", 4)[4] for call in trace([planes(direction, wavelet, dtype, *s) for s in PAIR_SHAPES])
+                for name, _, _ in call[1] if f"pair::pair_kernel<{i}, " in name}
+        assert seen >= {"8, 4, 2>", "8, 6, 2>", "12, 4, 3>", "16, 4, 3>"}, (direction, seen)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_every_four_tap_tile_is_compared_on_the_gpu(trace, dtype):
+    """Among the shapes of tests/test_gpu_taps4.py: one level in both heights, two levels in
+    48 block rows and, forward with 16-bit storage, 64."""
+    for i, direction in enumerate(("fwd", "inv")):
+        calls = [planes(direction, "dd137", dtype, *s) for s in TAPS4_SHAPES]
+        calls += [planes(direction, "dd137", dtype, *s, flags=d.DWT2_FLAG_FUSED) for s in TAPS4_SHAPES]
+        names = {name for call in trace(calls) for name, _, _ in call[1]}
+        assert all(f"taps4::" in n and f"_kernel<{i}, " in n for n in names), names
+        two = {n.split(", ", 3)[3] for n in names if "pair_kernel" in n}
+        one = {n.split(", ", 4)[3:][0] + ", " + n.split(", ", 4)[4] for n in names if "taps4_kernel" in n}
+        assert two >= ({"8, 6>", "16, 4>"} if (direction, dtype) == ("fwd", "bf16") else {"8, 6>"}), two
+        assert one >= {"4, 4, 2, 2>", "4, 5, 2, 2>"}, one

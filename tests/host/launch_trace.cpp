@@ -48,6 +48,19 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t,
     return hipSuccess;
 }
 hipError_t hipGetLastError(void) { return hipSuccess; }
+// what a persistent launch asks for
+hipError_t hipGetDevice(int* dev) {
+    *dev = 0;
+    return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t a, int) {
+    *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 100000;
+    return hipSuccess;
+}
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
+    *n = 2;
+    return hipSuccess;
+}
 }
 
 int main(int argc, char** argv) {

@@ -24,7 +24,7 @@ def trace(tmp_path_factory):
     for line in subprocess.run(["nm", "-C", d.LIB_PATH], capture_output=True, text=True, check=True).stdout.splitlines():
         f = line.split(" ", 2)
         if len(f) == 3 and f[0] and "_kernel" in f[2] and "device_stub" not in f[2]:
-            names[int(f[0], 16)] = f[2].split("(dwt2::")[0]
+            names[int(f[0], 16)] = f[2].split("(dwt2::Level")[0].split("(dwt2::Pair")[0].split("(dwt2_image")[0]
 
     def run(calls):
         r = subprocess.run([str(exe), d.LIB_PATH], input="\n".join(calls) + "\n", capture_output=True, text=True,
@@ -127,3 +127,14 @@ def test_every_four_tap_tile_is_compared_on_the_gpu(trace, dtype):
         one = {n.split(", ", 4)[3:][0] + ", " + n.split(", ", 4)[4] for n in names if "taps4_kernel" in n}
         assert two >= ({"8, 6>", "16, 4>"} if (direction, dtype) == ("fwd", "bf16") else {"8, 6>"}), two
         assert one >= {"4, 4, 2, 2>", "4, 5, 2, 2>"}, one
+
+
+@pytest.mark.parametrize("flags", [0, d.DWT2_FLAG_PERSISTENT])
+def test_low_images_take_the_low_tile(trace, flags):
+    """A batch whose images all fit the height of the lower one-level tile takes that one."""
+    levels = 2 if flags else 1
+    calls = [batch("f16", levels, 700, (4, 16), (h, 5), flags=flags) for h in (7, 24, 25, 300)]
+    for h, (st, launches) in zip((7, 24, 25, 300), trace(calls)):
+        assert st == 0 and len(launches) == 2
+        name, _, threads = launches[1]
+        assert ("<__half, 3, 4, 4, 2>" if h <= 24 else "<__half, 3, 4, 6, 2>") in name, (h, name)

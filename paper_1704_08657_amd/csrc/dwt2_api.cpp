@@ -366,7 +366,10 @@ int run_forward(const void* src, void* dst, int32_t planes, int64_t sps, int64_t
                 hipStream_t s) {
     // one level is one launch either way (and needs no workspace)
     if ((flags & DWT2_FLAG_PERSISTENT) && levels > 1) {
-        const int cfg = config_of(flags, wavelet);
+        // without a named configuration the taller tile beyond 2^22 samples (8192^2
+        // FP32, 5 levels, 455 us, the lower one 483; 3 x 4096^2 285, 319; but 2048^2 175, 162)
+        const bool named = flags & DWT2_FLAG_KERNEL_MASK;
+        const int cfg = !named && (int64_t)planes * h * w > (1 << 22) ? dwt2::kLargeConfig : config_of(flags, wavelet);
         dwt2::BatchSums sums{};
         dwt2::add_image(h, w, levels, dwt2::kConfigs[cfg], false, &sums);
         const dwt2::ImageSet S{nullptr, src, dst, sps, dps, sp, dp, h, w};

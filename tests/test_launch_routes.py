@@ -138,3 +138,13 @@ def test_low_images_take_the_low_tile(trace, flags):
         assert st == 0 and len(launches) == 2
         name, _, threads = launches[1]
         assert ("<__half, 3, 4, 4, 2>" if h <= 24 else "<__half, 3, 4, 6, 2>") in name, (h, name)
+
+
+@pytest.mark.parametrize("n,h,w,rows", [(1, 1024, 1024, 4), (1, 2048, 2048, 4), (1, 3000, 3000, 6), (1, 8192, 8192, 6),
+                                        (512, 256, 256, 6)])
+def test_persistent_launch_takes_the_tall_tile_for_large_calls(trace, n, h, w, rows):
+    for levels in (2, 5):
+        (st, launches), = trace([planes("fwd", "cdf97", "f32", n, h, w, levels, d.DWT2_FLAG_PERSISTENT)])
+        assert st == 0 and f"persist_fwd_kernel<float, 0, 4, {rows}, 2>" in launches[1][0]
+    (st, launches), = trace([planes("fwd", "cdf97", "f32", n, h, w, 2, d.DWT2_FLAG_PERSISTENT | d.DWT2_FLAG_KERNEL(1))])
+    assert st == 0 and "persist_fwd_kernel<float, 0, 8, 4, 2>" in launches[1][0]

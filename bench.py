@@ -275,8 +275,8 @@ def main():
 
     from paper_1704_08657_amd import autotune
 
-    # tile shape: the autotuner's committed cache (tuned_configs.json), or
-    # with --tune every kernel configuration timed on this GPU first (untimed,
+    # tile shape: the library's choice (the committed cache, tuned_configs.json,
+    # names none), or with --tune every kernel configuration timed on this GPU first (untimed,
     # before the warmup) and the fastest used
     tuned = {}
 
@@ -354,7 +354,7 @@ def main():
         # the three schemes of Section "Proposed Schemes" side by side --
         # polyconvolution (one step per lifting pair: 2 barriers), fused
         # lifting (4) and separable lifting (8) -- and DD 13/7 (Section
-        # "Evaluation"), which only this kernel runs
+        # "Evaluation"), whose default is a register tile kernel of its own
         lds_cfg = next(c for c in range(d.DWT2_NUM_KERNEL_CONFIGS)
                        if d.dwt2_kernel_config(c)[1] == d.DWT2_ALGO_LDS)
         for sch, kw in (("polyconvolution (2 barriers)", {"polyconv": True}), ("fused (4 barriers)", {}),
@@ -365,6 +365,9 @@ def main():
                  lambda i, c, kw=kw: d.inv(ys[i % pairs], "cdf97", 1, out=xs[i % pairs], config=lds_cfg, **kw), 1, 4)
         form("cdf97 fwd f32 5 levels, LDS-plane kernel, polyconvolution (2 barriers)",
              lambda i, c: d.fwd(xs[i % pairs], "cdf97", 5, out=ys[i % pairs], config=lds_cfg, polyconv=True), 5, 4)
+        form("dd137 fwd f32 1 level", lambda i, c: d.fwd(xs[i % pairs], "dd137", 1, out=ys[i % pairs]), 1, 4)
+        form("dd137 inv f32 1 level", lambda i, c: d.inv(ys[i % pairs], "dd137", 1, out=xs[i % pairs]), 1, 4)
+        form("dd137 fwd f32 5 levels", lambda i, c: d.fwd(xs[i % pairs], "dd137", 5, out=ys[i % pairs]), 5, 4)
         for sch, kw in (("fused (2 barriers)", {}), ("separable (4 barriers)", {"separable": True})):
             form(f"dd137 fwd f32 1 level, LDS-plane kernel, {sch}",
                  lambda i, c, kw=kw: d.fwd(xs[i % pairs], "dd137", 1, out=ys[i % pairs], config=lds_cfg, **kw), 1, 4)

@@ -317,8 +317,11 @@ def fwd(x, wavelet: str = "cdf97", levels: int = 1, split: bool = False, out=Non
         separable: bool = False, factored: bool = False, polyconv: bool = False, persistent: bool = False,
         workspace=None, fused: bool = False):
     """Forward transform of every [H, W] plane of x into a Mallat pyramid
-    (all planes in one call: one launch per level, two or three, or with `persistent` one
-    persistent launch for every level).  `workspace`: a uint8 device tensor of at least
+    (all planes in one call: a launch for one level, two or three, or with
+    `persistent` one persistent launch for every level).  Several levels share a
+    launch only in calls that name no scheme and no configuration: `fused`, for
+    one, asks for the default steps of 4-byte samples with a launch each, the same
+    results.  `workspace`: a uint8 device tensor of at least
     dwt2_workspace_bytes_planes bytes to use instead of a fresh one (its
     status can be read with workspace_status afterwards).  `config` selects a
     kernel configuration index (None: tuned or library default).  At most

@@ -66,8 +66,9 @@ void plan_levels(int32_t h, int32_t w, int levels, Plan* p) {
 }
 
 // Two ping-pong buffers per plane for intermediate LL bands: buffer A is large
-// enough for any (level 1's), buffer B for any but level 1's.  All planes' A buffers come first (plane stride a), then all B
-// buffers (plane stride b); a and b are multiples of kWsAlign bytes.
+// enough for any (level 1's), buffer B for any but level 1's.  All planes' A
+// buffers come first (plane stride a), then all B buffers (plane stride b); a and
+// b are multiples of kWsAlign bytes.
 struct WsLayout {
     size_t a, b;        // bytes of one plane's buffer A / B
     size_t off_b;       // offset of the B region
@@ -129,8 +130,9 @@ bool batch_spans_alias(const dwt2_image* imgs, int count, size_t es) {
 }
 
 // Kernel configuration selected by the flags (0 in the field = the default:
-// the LDS-plane kernel for DD 13/7 and the polyconvolution, which only it
-// runs; the register tile kernel otherwise).
+// the LDS-plane kernel for the polyconvolution, which only it runs, and for
+// DD 13/7, where launch_planes() goes by the four-tap kernel first; the register
+// tile kernel otherwise).
 int config_of(unsigned flags, int wavelet) {
     const unsigned t = (flags & DWT2_FLAG_KERNEL_MASK) >> DWT2_FLAG_KERNEL_SHIFT;
     if (t != 0) return (int)t - 1;
@@ -228,8 +230,8 @@ int validate(const void* src, void* dst, int32_t planes, int64_t sps, int64_t dp
     if ((flags & DWT2_FLAG_POLYCONV) && wavelet != DWT2_CDF97) return DWT2_E_FLAGS;
     if ((flags & DWT2_FLAG_PERSISTENT) && (adjoint || !persistent_ok(wavelet, dtype, flags, planes)))
         return DWT2_E_FLAGS;
-    // the LDS-plane kernel: float wavelets, forward / inverse, fused,
-    // separable and polyconvolution schemes; it alone runs DD 13/7 and the
+    // the LDS-plane kernel: float wavelets, forward / inverse, fused, separable
+    // and polyconvolution schemes; no other configuration runs DD 13/7 or the
     // polyconvolution
     if (algo == dwt2::kAlgoLds &&
         (adjoint || wavelet == DWT2_CDF53_REV || (flags & (DWT2_FLAG_SPLIT | DWT2_FLAG_FACTORED))))

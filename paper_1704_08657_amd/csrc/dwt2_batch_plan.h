@@ -153,8 +153,7 @@ __host__ __device__ inline size_t image_ll_bytes(int32_t h, int32_t w, int level
 //                                        levels); [l][count] = its tiles
 //   uint64 ll_off[count]                 byte offset of image i's LL buffers
 //                                        in the LL area
-//   LL area                              per image: buffer A (LL of levels
-//                                        1, 3, ...), buffer B (levels 2, 4, ...)
+//   LL area                              per image: buffers A and B
 // The launches: launch j takes levels[j] levels (1, 2 or 3) from level first[j]
 // on; two or three in tiles of rows[j] block rows (halo included).  tile_off's row j
 // then holds the tiles of launch j.  The LL band that leaves launch j (but the

@@ -386,10 +386,11 @@ __device__ __forceinline__ float row_prev(float v) { return __int_as_float(row_p
 // the wave).  et / es: the same for the halo rows (per side: first block,
 // second block).  Wave w publishes to t[w], et[w], s[w + 1], es[w + 1] and
 // reads t[w + 1], et[w + 1], s[w], es[w]: the slots t[NW], s[0] (and the
-// halo ones) hold zeros for the outermost waves, which only reach tile rows
-// outside the core (a predict-shaped step carries values up one row, an
-// update-shaped one down one row, and the tile's 2-row halo absorbs the two
-// of each).  col / hal: per-wave exchange
+// halo ones) are not written: whatever the outermost waves read there only
+// reaches tile rows outside the core (a predict-shaped step carries values up
+// one row, an update-shaped one down one row, and the tile's 2-row halo absorbs
+// the two of each), as does what is read of a wave that has left (below_image()).
+// col / hal: per-wave exchange
 // between the core's edge lane and the halo lanes, indexed by block row.
 template <typename V, int NW, int BPL, int K> struct TileLds {
     static_assert(K % 2 == 0 && K <= 16, "K even, at most 16 rows per wave");
@@ -1034,8 +1035,8 @@ __device__ __forceinline__ void fold(int (&p)[N], int n) {
 // then is what it was), which is exact beside that sample's magnitude; see
 // tile_scale().  A border step program with the weights cost a
 // dozen operations more a block and step and twice the code: 192 planes of 256^2
-// FP32, 3 levels, took 46.8 us, now 39.2; 8192^2, 2 levels, 112.7, now 101.6 (BF16
-// 102, now 73).
+// FP32, 3 levels, took 46.8 us, now 40.8; 8192^2, 2 levels, 112.7, now 104 (BF16
+// 102, now 65).
 // rows, cols: the (folded) positions of a's samples; components K0 .. K1 - 1.
 // all: the factor of every sample.
 template <int K0, int K1, int BPL, int K, typename V>

@@ -21,15 +21,16 @@ namespace pair {
 // The halo is that of both levels, 2 blocks of each: kHalo2 = 6 block rows of
 // level 1 above and below, and the columns of kEdge2 lanes on either side,
 // which load and compute but do not store: 3 would do, but 4 leave 112 columns,
-// whose subband segments (448 bytes of FP32) are whole 64-byte sectors (8192^2
-// FP32, two levels forward: 114 us with 4, 126 with 3; BF16 3 x 8192^2: 218, 263).  Halo values come from the
-// neighbouring lane or wave like any others, so a step has no halo operands:
+// whose subband segments (448 bytes of FP32) are whole 64-byte sectors (two levels
+// forward take 10 % longer with 3 for 8192^2 FP32, 20 % for 3 x 8192^2 BF16).  Halo
+// values come from the neighbouring lane or wave like any others, so a step has no
+// halo operands:
 // horizontal neighbours are DPP shifts that fold into the adds, vertical ones
 // the lane's own rows or one LDS row per wave and step.
 //
-// Borders.  Level 1 runs on the symmetric extension of its input.  The LL samples this gives outside
-// the image are not what level 2 extends them to when a side is even, so a
-// border tile passes its LL samples through LDS and each lane takes the
+// Borders.  Level 1 runs on the symmetric extension of its input.  The LL samples
+// this gives outside the image are not what level 2 extends them to when a side is
+// even, so a border tile passes its LL samples through LDS and each lane takes the
 // reflected ones.  Every value is formed by the same operations in the same
 // order as by the one-level kernels: the results are theirs bit for bit.
 
@@ -224,7 +225,7 @@ template <typename T, int N>
 __device__ __forceinline__ void store_band_row(T* p, const typename St<T>::V (&v)[N]) {
     // a wave's row of single 16-bit samples is less than a line: an ordinary
     // store, so that the caches gather the rows' neighbours (3 x 8192^2 BF16,
-    // two levels forward: 193 us, 218 nontemporal)
+    // two levels forward, takes 13 % longer with nontemporal ones)
     if constexpr (N > 1) store_vec<T, N>(p, v);
     else if constexpr (sizeof(T) == 4) nt_store1<T>(p, St<T>::store(v[0]));
     else p[0] = St<T>::store(v[0]);

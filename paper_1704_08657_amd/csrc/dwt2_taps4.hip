@@ -287,15 +287,6 @@ __device__ __forceinline__ void update(float (&a)[K][4 * BPL], Lds<NW, BPL, kSch
             }
 }
 
-// Columns left of the image: fold() takes positions down to -6, which is as
-// far as an output reads; a lane further out takes the nearest of the same parity.
-template <int N>
-__device__ __forceinline__ void fold_columns(int (&p)[N], int n) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) p[i] = p[i] < -6 ? -6 + (p[i] & 1) : p[i];
-    fold(p, n);
-}
-
 // The tile into registers.  g.cb0: block column of lane 0's first block
 // (negative for the first tile of a row).
 template <int DIR, typename T, int BPL, int K>
@@ -323,7 +314,7 @@ __device__ __forceinline__ void load(float (&a)[K][4 * BPL], const LevelParams& 
                 for (int s = 0; s < 2 * BPL; ++s) a[i >> 1][4 * (s >> 1) + 2 * (i & 1) + (s & 1)] = v[s];
             }
         } else {
-            fold_columns(cols, P.w);
+            pair::fold_both(cols, P.w);
 #pragma unroll
             for (int i = 0; i < 2 * K; ++i)
 #pragma unroll
@@ -347,7 +338,7 @@ __device__ __forceinline__ void load(float (&a)[K][4 * BPL], const LevelParams& 
                     for (int b = 0; b < BPL; ++b) a[r][4 * b + k] = v[b];
                 }
         } else {
-            fold_columns(cols, P.w);
+            pair::fold_both(cols, P.w);
 #pragma unroll
             for (int r = 0; r < K; ++r)
 #pragma unroll

@@ -183,8 +183,8 @@ inline int64_t pair_tiles(int32_t h, int32_t w, int32_t planes, int rows) {
 }
 // Tile shape, in block rows of a tile (32: 8 waves x 4 rows, 48: 8 x 6).  Few
 // tiles, all on the chip at once (up to 2.5 work-groups of 8 waves on each of 256
-// CUs): the shape that takes the least time from load to store, 8 waves x 4 rows (1024^2 FP32 forward 7.3 us, 8 x 6: 9.2).  Beyond,
-// 8 x 6 recomputes 12 of 48 rows instead of 12 of 32, which counts where the
+// CUs): the shape that takes the least time from load to store, 8 waves x 4 rows
+// (1024^2 FP32 forward 7.3 us, 8 x 6: 9.2).  Beyond, 8 x 6 recomputes 12 of 48 rows instead of 12 of 32, which counts where the
 // vector units are the limit: 16-bit storage (3 x 8192^2 FP16 inverse 179 us,
 // 8 x 4: 200) and one round of tiles (3 x 1081 x 1921 FP32 forward 13.2, 14.5);
 // 8 x 4 has 60 registers to 82 and more work-groups on a CU, which counts where
